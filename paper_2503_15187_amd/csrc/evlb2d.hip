@@ -345,60 +345,81 @@ __global__ __launch_bounds__(FNT) void fields_kernel(Dev D, const double* __rest
 // columns, one distribution (F or G) and all 256 velocities, and marches
 // down a segment of rows
 // ---------------------------------------------------------------------------
-// Thread (wavefront w, lane L): column c = L & 7 of the strip and r = L >> 3;
-// it holds the two velocities (k, l) = (w, r) and (w, r + 8).  In the
-// node-major state a wavefront's 16 velocities of a node are one 128-byte
-// line, read as two halves by consecutive loads.  Every wavefront sees one
-// sign of p_k (k < 8: p_k < 0) and every register slot one sign of p_l, so
-// both upwind choices are uniform.
+// Thread (wavefront w, lane L): column c = L & 7 and r = L >> 3; it holds the
+// two velocities (k, l) = (w, r) and (w, 15 - r), a mirror pair: p_(15-l) =
+// -p_l.  This is the B operand and result layout of v_mfma_f64_4x4x4 (four
+// independent 4 x 4 blocks: block L >> 2 & 3, column L & 3, row or contraction
+// index L >> 4; an A operand has its row in L & 3 and its contraction index in
+// L >> 4), so a row's values enter the matrix units as they lie in registers:
+// block (L >> 2 & 1) + 2 (r & 1), index r >> 1.  In the node-major state a
+// wavefront's 16 velocities of a node are one 128-byte line, read as two
+// halves by consecutive loads.
+//
+// What bounds it: the instructions issued per row (four wavefronts per SIMD).
+// Against a version with 16 x 16 x 4 matrix instructions, right faces by DPP,
+// per-lane coefficients and addresses formed every row, this one runs a
+// 1024 x 1024 step (three stages and the entry sums) in 13.4 instead of 16.4
+// ms and 333 x 270 in 1.64 instead of 2.09 ms per step.
+//
+// Every wavefront sees one sign of p_k (k < 8: p_k < 0) and every register
+// slot one sign of p_l.  Wavefronts of p_k < 0 hold the strip mirrored (lane
+// column c is the strip's column 7 - c): the upwind side is then on the left
+// for every wavefront, x faces are one piece of code, and each lane's face
+// enters with |p_k|.
+//
+// The momentum derivatives use the mirror symmetry Dp[15-k][15-j] =
+// -Dp[k][j]: with f+- = f_j +- f_(15-j), j < 8, e = S f+ and o = A f-, where S,
+// A = (Dp[k][j] +- Dp[k][15-j]) / 2, (Dp f)_k = e + o and (Dp f)_(15-k) = o - e:
+// two 8 x 8 products for one of 16 x 16, half the matrix work (and the 4 x 4
+// blocks run at the rate of the 16 x 16 ones: 512 flops in 16 cycles).
 //
 // One barrier per row.  Iteration y is
 //  pre(y)   (each wavefront on its own 16 velocities, no data of another
 //           wavefront): the row to LDS with three halo columns each side;
 //           WENO-5 faces along y from a ring of five rows per velocity in
 //           registers; WENO-5 faces along x from the LDS row (each lane the
-//           face on its left, the one on its right from the next lane by
-//           DPP); (I x Dp) f on the f64 MFMA, every other row for that row
-//           and the one before it (whose term goes into acc(y - 1)); the
-//           Shakhov + J1 collision terms as a polynomial in xi_x and xi_y per
-//           node; everything but the (Dp x I) f term and the strip-edge face
-//           folded into acc(y).
+//           face on its left, the one on its right from the next lane
+//           through LDS); (I x Dp) f in registers; the Shakhov + J1 collision
+//           terms as a polynomial in xi_y; everything but the (Dp x I) f term
+//           and the strip-edge face folded into acc(y).
 //  barrier
 //  post(y)  the work that reads other wavefronts' rows or writes what they
 //           read: f^(s) of row y - 1 from acc(y - 1), the (Dp x I) f term and
-//           the strip-edge face of row y - 1, its store and its per-wavefront
-//           terms of the raw velocity sums (a weight matrix times the row's
-//           16 x 8 values on the MFMA);
-//           wavefront 0 the raw velocity sums of row y - 2, 1 the Hermite
-//           coefficients a_m(u, T) of row y + 3, 2 the expansions e_k(u_x),
-//           e_l(u_y) of row y + 2 (one MFMA chain over 8 nodes x 2 axes), 3
-//           the per-node collision coefficients of row y + 3, 4 - 7 the
-//           strip-edge faces of row y, 8 - 15 (Dp x I) f of row y
-//           (v_mfma_f64_16x16x4 takes B element [c][col] from lane col + 16 c
-//           and returns row 4 j + c, column col in register j of that lane;
-//           col = (column, l parity)).
+//           the strip-edge face of row y - 1, its store and its moments
+//           sum_l p_l^m f^(s), m < 4, over the wavefront's own velocities (a
+//           4 x 16 product of the registers on the matrix units);
+//           wavefront 0 the raw velocity sums of row y - 2 (the wavefronts'
+//           moments times powers of p_k, again on the matrix units), 1 the
+//           Hermite coefficients a_m(u, T) of row y + 4, 2 the expansions
+//           e_k(u_x), e_l(u_y) of row y + 3, 3 the per-node collision
+//           coefficients of row y + 4, 0 and 3 the collision polynomials per
+//           (k, node) of row y + 2, 4 - 7 the strip-edge faces of row y, 8 -
+//           15 (Dp x I) f of row y.
 // What one wavefront writes and another reads crosses exactly one barrier,
-// and every such buffer is double (quadruple for the collision
-// coefficients, read a full iteration after they are written), so that a
-// wavefront one half-iteration ahead never overwrites what a slower one
-// still reads.  The ring's next row, f^n and the halo columns of the next
-// row and the node fields of row y + 4 are in flight across an iteration.
+// and every such buffer is double (quadruple for what is read two rows
+// later), so that a wavefront one half-iteration ahead never overwrites what
+// a slower one still reads.  The ring's next row, f^n and the halo columns of
+// the next row and the node fields of row y + 5 are in flight across an
+// iteration.
 constexpr int SW = 8;            // columns per strip
 constexpr int SNW = 16;          // wavefronts per workgroup
 constexpr int SNT = 64 * SNW;    // threads per workgroup
 constexpr int NRAW = 11;         // raw velocity sums per node: 8 of F, 3 of G
-// LDS strides (doubles).  A lane (c, r) reads plane r + 8 j at column c + i:
-// a plane stride of 8 (mod 16) puts the 16 lanes of one LDS pass, and of 32
-// lanes, on distinct banks.
-constexpr int TS = 24;                 // T: columns x0 - 3 .. x0 + 10 at 0 .. 13, (I x Dp) f at 14 .. 21,
-                                       // the strip-edge face of rows of parity 0 / 1 at 22 / 23
-constexpr int FIS = 16 * SW + 3 * 16;  // FI per k: 16 l x 8 interior columns, then 16 l x 3 right halo columns
+// A row in LDS, doubles: velocity (k, l) at k KS + l PS, columns -3 .. 10 of
+// wavefront k's orientation at 0 .. 13 of it, its x faces and then (Dp x I) f
+// of columns 0 .. 7 at 14 .. 21, a zero at 22, the strip-edge face at 23.
+// Lanes of one LDS pass differ in the column and in r (PS = 24 = 8 mod 16) or
+// in the column and in k (KS = 8 mod 32): distinct banks either way.
+constexpr int PS = 24, KS = 16 * PS + 8;
+constexpr int CDX = 14, CZERO = 22, CEDGE = 23;
+constexpr int USLOT = Q * KS;
 // per-node coefficients of the collision terms: the row polynomial
 //   nu f^S + J1 = tf n e_k e_l (P0 + xi_y (P1 + xi_y (P2 + P3 xi_y)))
 // with P0 = c0 + xi_x (c1 + xi_x (c2 + c3 xi_x)), P1 = d0 + xi_x (d1 + d2 xi_x),
 // P2 = e0 + c3 xi_x, P3 = d2 (a rearrangement of the reduced Shakhov and J1
-// terms), plus u_x, u_y, tf n, nu, F_x, F_y
-enum { CF_C0, CF_C1, CF_C2, CF_C3, CF_D0, CF_D1, CF_D2, CF_E0, CF_UX, CF_UY, CF_TFN, CF_NU, CF_FX, CF_FY, NCF };
+// terms), plus u_x and, scaled by the stage's c, tf n; then what every lane of
+// the node takes: u_y, the factor b - c nu of f^(s-1), c F_x, c F_y
+enum { CF_C0, CF_C1, CF_C2, CF_C3, CF_D0, CF_D1, CF_D2, CF_E0, CF_UX, CF_TFN, CF_UY, CF_NUB, CF_FX, CF_FY, NCF };
 
 struct FusedArgs {
   const double* fs;   // f^(s-1)
@@ -407,48 +428,58 @@ struct FusedArgs {
   const double* fld;  // node fields [NF][ntot]
   double* raw;        // raw velocity sums of f^(s) [NRAW][ntot] (want_mom)
   double a, b, c;     // f^(s) = a f^n + b f^(s-1) + c L(f^(s-1))
+  double e3, e75;     // 0.3 and 0.75 weno_eps
   int first, want_mom;
   int nstrip, seglen;
 };
 
+// what the lanes of a row read of its node quantities
+struct RowTab {
+  double P[Q][SW][4];   // (k, node): c tf n e_k(u_x) (P0, P1, P2, P3)
+  double E[SW][SW][6];  // (r, node): u_y, b - c nu, c F_x, c F_y and e_l(u_y) for l = r, 15 - r
+};
+
 struct FusedSmem {
-  double T[V * TS];             // wavefront w's row, velocity (w, l) at 16 w + l (its own)
-  double FI[2][Q][FIS];         // row y: [k][8 l + (c ^ ((l >> 1) & 7))] interior (the swizzle spreads a
-                                // column of 16 l over the banks), [k][128 + 3 l + h] columns x0 + 8 + h
-  double DX[2][Q][16 * SW];     // (Dp x I) f^(s-1) of row y: [k][8 (l ^ 2 (k & 1)) + c] (the swizzle
-                                // puts the MFMA result rows k and k + 1 on distinct banks)
-  double AH[2][Q][16];          // Hermite coefficients a_m(u, T) of a row, column (node, axis)
-  double EK[2][2][Q][SW];       // unit-density expansions e_k(u_x) (axis 0), e_l(u_y) (axis 1)
-  double CF[4][NCF][SW];        // per-node coefficients of the collision row polynomial
-  double fl[2][NF][SW];         // node fields of a row
-  double mred[2][SNW][8][SW];   // per-wavefront terms of the raw velocity sums of a row (fixed k)
-  double aop[4][64];            // MFMA A operands Dp[i][c + 4 b] at lane i + 16 c
+  double U[2][USLOT];           // rows y, y - 1
+  RowTab tab[2];
+  double mred[2][SNW][48];      // per wavefront: moment m of column c at 8 m + c (48: distinct banks over k)
+  double fl[4][NF][SW];         // node fields of a row
+  double AH[4][Q][16];          // Hermite coefficients a_m(u, T) of a row, column (node, axis)
+  double EK[4][2][Q][SW];       // unit-density expansions e_k(u_x) (axis 0), e_l(u_y) (axis 1)
+  double CF[4][NCF][SW];        // collision coefficients of a row
   double eop[4][64];            // MFMA A operands meq[i][c + 4 b] at lane i + 16 c
+  double pw[4][64];             // MFMA A operands p_(4 t + k)^m at lane m + 16 k (all four blocks)
   double vel[Q];
 };
 static_assert(sizeof(FusedSmem) <= 160 * 1024, "fused stage LDS exceeds 160 KiB");
+static_assert(8 * (USLOT + PS) < 65536, "both row slots are reached by the 16-bit LDS offset");
 
 // WENO-5 (Jiang & Shu) value at a face from the five values v0 .. v4 ordered
 // from the upwind side (v2 is the node upwind of the face), written in the
 // first differences e_m = v_(m+1) - v_m.  The candidates less v2 are g0 =
-// (5 e1 - 2 e0) / 6, 6 g1 = e1 + 2 e2, 3 g2 = 2 e2 - e3 / 2; the
-// smoothness 12 beta_r = 13 a_r^2 + 3 b_r^2 expands in the squares and
-// neighbour products of the differences to 16 e0^2 - 44 e0 e1 + 40 e1^2,
-// 16 e1^2 - 20 e1 e2 + 16 e2^2 and 40 e2^2 - 44 e2 e3 + 16 e3^2.  The weights
-// d_r / (eps + beta_r)^2 normalised: with t_r = (12 eps + 12 beta_r)^2 and
+// (5 e1 - 2 e0) / 6, 6 g1 = e1 + 2 e2, 3 g2 = 2 e2 - e3 / 2; three quarters of
+// the smoothness indicators are the quadratic forms e0 (e0 - 11/4 e1) + 5/2
+// e1^2, e1 (e1 - 5/4 e2) + e2^2 and e3 (e3 - 11/4 e2) + 5/2 e2^2.  The weights
+// d_r / (eps + beta_r)^2 normalised: with t_r = (3/4 (eps + beta_r))^2 and
 // 10 d = (1, 6, 3) the value is v2 + (t1 t2 g0 + 6 t0 t2 g1 + 3 t0 t1 g2) /
 // (t1 t2 + 6 t0 t2 + 3 t0 t1) (every common factor cancels).  The division
-// goes through a hardware reciprocal refined by two Newton steps.
-__device__ __forceinline__ double weno5(double v0, double v1, double v2, double v3, double v4, double eps12) {
+// goes through a hardware reciprocal (within 2^-24.4 on this part) and one
+// third-order step r (1 + d + d^2), d = 1 - den r, which leaves the rounding of
+// its own operations.  36 vector instructions; the form it replaces, squares
+// and products expanded one by one and two Newton steps, took 42.
+// e75 = 3/4 eps; e3 = 2/5 of that, as it enters under the factor 5/2.  The
+// other constants come in scalar registers too: as literals the compiler puts
+// them into two-operand fused multiply-adds, each behind a register copy.
+struct WenoK {
+  double e3, e75, m275, m125, p25;
+};
+
+__device__ __forceinline__ double weno5(double v0, double v1, double v2, double v3, double v4, const WenoK& K) {
   const double e0 = v1 - v0, e1 = v2 - v1, e2 = v3 - v2, e3 = v4 - v3;
-  // eps12 enters through the squares: -eps12 / 64 on the outer two, eps12 / 32
-  // on the inner two sum to eps12 in every indicator (no accumulator copy)
-  const double lo = -eps12 * (1.0 / 64.0), hi = eps12 * (1.0 / 32.0);
-  const double s0 = fma(e0, e0, lo), s1 = fma(e1, e1, hi), s2 = fma(e2, e2, hi), s3 = fma(e3, e3, lo);
-  const double x01 = e0 * e1, x12 = e1 * e2, x23 = e2 * e3;
-  double t0 = fma(16.0, s0, fma(-44.0, x01, 40.0 * s1));
-  double t1 = fma(16.0, s1, fma(-20.0, x12, 16.0 * s2));
-  double t2 = fma(40.0, s2, fma(-44.0, x23, 16.0 * s3));
+  const double q1 = fma(e1, e1, K.e3), q2 = fma(e2, e2, K.e3);
+  double t0 = fma(e0, fma(K.m275, e1, e0), K.p25 * q1);
+  double t1 = fma(e1, fma(K.m125, e2, e1), fma(e2, e2, K.e75));
+  double t2 = fma(e3, fma(K.m275, e2, e3), K.p25 * q2);
   t0 *= t0;
   t1 *= t1;
   t2 *= t2;
@@ -458,36 +489,47 @@ __device__ __forceinline__ double weno5(double v0, double v1, double v2, double 
   const double g2x3 = fma(2.0, e2, -0.5 * e3);
   const double num = fma(u2, g2x3, fma(u1, g1x6, u0 * g0));
   const double den = fma(3.0, u2, fma(6.0, u1, u0));
-  double r = __builtin_amdgcn_rcp(den);
-  r = fma(r, fma(-den, r, 1.0), r);
-  r = fma(r, fma(-den, r, 1.0), r);
-  return fma(num, r, v2);
+  const double r = __builtin_amdgcn_rcp(den);
+  const double d = fma(-den, r, 1.0);
+  return fma(num, fma(r, fma(d, d, d), r), v2);
 }
 
-// DPP row_shl: lane i of every 16-lane row takes lane i + N's value (0 past
-// the row's end)
-template <int N>
-__device__ __forceinline__ double row_shl(double v) {
+// DPP row_ror:8: lane i of every 16-lane row takes lane i ^ 8's value
+__device__ __forceinline__ double row_half(double v) {
   const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, 0x100 + N, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), 0x100 + N, 0xf, 0xf, false);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, 0x128, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), 0x128, 0xf, 0xf, true);
   return __builtin_bit_cast(double, (unsigned long long)(unsigned)lo | ((unsigned long long)(unsigned)hi << 32));
 }
-__device__ __forceinline__ double row_next(double v) { return row_shl<1>(v); }
 
+typedef double dbl2 __attribute__((ext_vector_type(2)));
 typedef double dbl4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ double mfma4(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+
+// Dp applied along one mirror pair: g0, g1 = (Dp f)_r, (Dp f)_(15-r) from f0,
+// f1 = f_r, f_(15-r), r = L >> 3.  A block holds the indices of one parity of
+// r; those of the other come from the lane 8 away.  op: S, then A, each for
+// rows of the block's parity against indices of the same and of the other.
+__device__ __forceinline__ void mirror_dp(const double (&op)[4], double f0, double f1, double& g0, double& g1) {
+  const double a = f0 + f1, b = f0 - f1;
+  double x = mfma4(op[0], a, 0.0), y = mfma4(op[2], b, 0.0);
+  x = mfma4(op[1], row_half(a), x);
+  y = mfma4(op[3], row_half(b), y);
+  g0 = y + x;
+  g1 = y - x;
+}
 
 constexpr int BUF_DWORD3 = 0x00020000;
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const double* base) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, -1, BUF_DWORD3);
 }
-// A buffer of 2^31 bytes: an access at BUF_DROP (no scalar offset) is out of
-// range, so a store there is dropped and a load returns 0.
-constexpr unsigned BUF_DROP = 0xfffffff0u;
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf2g(const double* base) {
-  return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)0x80000000u, BUF_DWORD3);
-}
+// A buffer of 2^31 bytes: an access at BUF_DROP is out of range with any row
+// offset below 2^31, so a store there is dropped.
+constexpr unsigned BUF_DROP = 0x80000000u;
 __device__ __forceinline__ double bload(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so) {
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0));
 }
@@ -498,12 +540,12 @@ __device__ __forceinline__ void bstore(double v, __amdgpu_buffer_rsrc_t r, unsig
 
 // Hermite coefficients a_0 .. a_15 of the unit-density expansion along one
 // axis at node (column c, axis): a_0 = 1, a_1 = u, a_{m+1} = u a_m +
-// m (T - 1) a_{m-1}, into AH[buf][m][c + 8 axis] (the B operand layout of the
+// m (T - 1) a_{m-1}, into AH[s][m][c + 8 axis] (the B operand layout of the
 // expansion MFMA).
-__device__ __forceinline__ void fused_hermite(FusedSmem& S, int fb, int t) {
+__device__ __forceinline__ void fused_hermite(FusedSmem& S, int s, int t) {
   const int c = t & (SW - 1), axis = t >> 3;
-  const double u = S.fl[fb][axis == 0 ? F_UX : F_UY][c], Tm1 = S.fl[fb][F_T][c] - 1.0;
-  double* a = &S.AH[fb][0][t];
+  const double u = S.fl[s][axis == 0 ? F_UX : F_UY][c], Tm1 = S.fl[s][F_T][c] - 1.0;
+  double* a = &S.AH[s][0][t];
   double a0 = 1.0, a1 = u;
   a[0] = a0;
   a[16] = a1;
@@ -517,10 +559,10 @@ __device__ __forceinline__ void fused_hermite(FusedSmem& S, int fb, int t) {
 }
 
 // Per-node coefficients of the collision row polynomial of one
-// distribution (d: F or G) from the node fields of column c (fl[fb]) into
-// CF[cb].
-__device__ __forceinline__ void fused_coeffs(const Dev& D, FusedSmem& S, int fb, int cb, int c, int d) {
-  const double* fl = &S.fl[fb][0][0];
+// distribution (d: F or G) from the node fields of column c (fl[s]) into
+// CF[s]; bb: the factor of f^(s-1) outside L.
+__device__ __forceinline__ void fused_coeffs(const Dev& D, FusedSmem& S, int s, int c, int d, double bb, double cc) {
+  const double* fl = &S.fl[s][0][0];
 #define FL(i) fl[(i) * SW + c]
   const bool j0 = (D.term_mask & EVLB_TERM_J0) != 0;
   const bool j1 = (D.term_mask & EVLB_TERM_J1) != 0;
@@ -532,7 +574,7 @@ __device__ __forceinline__ void fused_coeffs(const Dev& D, FusedSmem& S, int fb,
   const double Sy = fma(nu, FL(F_SQY), 0.3 * pre * FL(F_BY));
   const double C = 0.2 * pre * (FL(F_UXX) + FL(F_UYY));
   const double W4 = 0.4 * pre * invT;
-  double* cf = &S.CF[cb][0][c];
+  double* cf = &S.CF[s][0][c];
   cf[CF_C0 * SW] = fma(-th0, C, nu);
   cf[CF_C1 * SW] = fma(-th0, Sx, pre * FL(F_AX));
   cf[CF_C2 * SW] = fma(invT, C, W4 * FL(F_UXX));
@@ -542,40 +584,77 @@ __device__ __forceinline__ void fused_coeffs(const Dev& D, FusedSmem& S, int fb,
   cf[CF_D2 * SW] = invT * Sy;
   cf[CF_E0 * SW] = fma(invT, C, W4 * FL(F_UYY));
   cf[CF_UX * SW] = FL(F_UX);
+  cf[CF_TFN * SW] = (j0 || j1) ? cc * (d == 0 ? 1.0 : 0.5 * T) * FL(F_N) : 0.0;
   cf[CF_UY * SW] = FL(F_UY);
-  cf[CF_TFN * SW] = (j0 || j1) ? (d == 0 ? 1.0 : 0.5 * T) * FL(F_N) : 0.0;
-  cf[CF_NU * SW] = nu;
-  cf[CF_FX * SW] = FL(F_FX);
-  cf[CF_FY * SW] = FL(F_FY);
+  cf[CF_NUB * SW] = fma(-cc, nu, bb);
+  cf[CF_FX * SW] = cc * FL(F_FX);
+  cf[CF_FY * SW] = cc * FL(F_FY);
 #undef FL
 }
 
 // e_k = sum_m meq[k][m] a_m for the 16 columns (node, axis) of a row on the
 // f64 MFMA (B element [c][col] = a_{c + 4 b}(col) from lane col + 16 c;
-// result e_{4 j + c}(col) in register j of that lane), into EK[buf].
-__device__ __forceinline__ void fused_expansions(FusedSmem& S, int fb, int L) {
+// result e_{4 j + c}(col) in register j of that lane), into EK[s].
+__device__ __forceinline__ void fused_expansions(FusedSmem& S, int s, int L) {
   const int c4 = L >> 4, col16 = L & 15;
   dbl4 e = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int b = 0; b < 4; ++b)
-    e = __builtin_amdgcn_mfma_f64_16x16x4f64(S.eop[b][L], S.AH[fb][c4 + 4 * b][col16], e, 0, 0, 0);
+    e = __builtin_amdgcn_mfma_f64_16x16x4f64(S.eop[b][L], S.AH[s][c4 + 4 * b][col16], e, 0, 0, 0);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) S.EK[fb][col16 >> 3][4 * j + c4][col16 & 7] = e[j];
+  for (int j = 0; j < 4; ++j) S.EK[s][col16 >> 3][4 * j + c4][col16 & 7] = e[j];
 }
 
-// Raw velocity sum s = t / SW of row y at column t % SW: the sum over the 16
-// wavefronts' terms.
-__device__ __forceinline__ void fused_raw_sum(const Dev& D, const FusedArgs& A, const FusedSmem& S, int d, int t,
+// Row table of a row: lane (k = 8 h + (L >> 3), node c = L & 7) forms the
+// polynomial of its (k, node) and copies e_l(u_y) of l = k and half of the
+// per-node values.
+__device__ __forceinline__ void fused_rowtab(FusedSmem& S, int s, RowTab& t, int h, int L) {
+  const int k = 8 * h + (L >> 3), c = L & 7;
+  const double* cf = &S.CF[s][0][c];
+  const double x = S.vel[k] - cf[CF_UX * SW];
+  const double c3 = cf[CF_C3 * SW], d2 = cf[CF_D2 * SW];
+  const double P0 = fma(x, fma(x, fma(c3, x, cf[CF_C2 * SW]), cf[CF_C1 * SW]), cf[CF_C0 * SW]);
+  const double P1 = fma(x, fma(d2, x, cf[CF_D1 * SW]), cf[CF_D0 * SW]);
+  const double P2 = fma(c3, x, cf[CF_E0 * SW]);
+  const double tfe = cf[CF_TFN * SW] * S.EK[s][0][k][c];
+  double* p = &t.P[k][c][0];
+  p[0] = tfe * P0;
+  p[1] = tfe * P1;
+  p[2] = tfe * P2;
+  p[3] = tfe * d2;
+  double* e = &t.E[h == 0 ? L >> 3 : 7 - (L >> 3)][c][0];
+  e[4 + h] = S.EK[s][1][k][c];
+  e[2 * h] = cf[(CF_UY + 2 * h) * SW];
+  e[2 * h + 1] = cf[(CF_UY + 2 * h + 1) * SW];
+}
+
+// Raw velocity sums of row y from the wavefronts' moments M_i(k) = sum_l p_l^i
+// f(k, l) in mred[s]: sum_k p_k^m M_i(k) on the matrix units, K = 16
+// wavefronts; lane L receives m = L >> 4 of column L & 7 for i = L >> 3 & 1
+// (first chain) and i + 2 (second).
+//   F: n 00, j_x 10, j_y 01, P_xx 20, P_xy 11, P_yy 02, r_x 30 + 12, r_y 21 + 03
+//   G: g0 00, h_x 10, h_y 01         (digits: m, i)
+__device__ __forceinline__ void fused_raw_sum(const Dev& D, const FusedArgs& A, const FusedSmem& S, int d, int s, int L,
                                               int x0, int y) {
-  const int s = t / SW, cc = t & (SW - 1);
-  if (x0 + cc >= D.nx) return;
-  const double* m = &S.mred[y & 1][0][s][cc];
-  double v[4];
+  const int m = L >> 4, i = (L >> 3) & 1, c = L & 7;
+  const double* mr = &S.mred[s][m][L & 15];  // element (k, L & 15) of index k = 4 t + (L >> 4)
+  double u = 0.0, v = 0.0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = m[i * 8 * SW];
-#pragma unroll
-  for (int l = 4; l < SNW; ++l) v[l & 3] += m[l * 8 * SW];
-  A.raw[(long long)((d == 0 ? 0 : 8) + s) * D.ntot + (long long)y * D.nx + x0 + cc] = (v[0] + v[1]) + (v[2] + v[3]);
+  for (int t = 0; t < 4; ++t) {
+    u = mfma4(S.pw[t][L], mr[192 * t], u);
+    if (d == 0) v = mfma4(S.pw[t][L], mr[192 * t + 16], v);
+  }
+  const double w = __shfl_xor(v, 32);  // m ^ 2 of the second chain
+  if (x0 + c >= D.nx) return;
+  double* raw = A.raw + (long long)y * D.nx + x0 + c;
+  if (d == 0) {
+    const int f = i == 0 ? (m == 0 ? 0 : (m == 1 ? 1 : (m == 2 ? 3 : 6))) : (m == 0 ? 2 : (m == 1 ? 4 : 7));
+    if (m == 3 - i) u += w;
+    if (i == 0 || m < 3) raw[f * D.ntot] = u;
+    if (i == 0 && m == 0) raw[5 * D.ntot] = v;
+  } else if (i + m < 2) {
+    raw[(8 + m + 2 * i) * D.ntot] = u;
+  }
 }
 
 template <int N>
@@ -587,10 +666,10 @@ template <bool ADV, bool FRC, bool FIRST>
 __global__ __launch_bounds__(SNT) void fused_kernel(Dev D, FusedArgs A, const double* __restrict__ velg,
                                                     const double* __restrict__ meqg,
                                                     const double* __restrict__ dpmg) {
-  __shared__ FusedSmem S;
-  const int tid0 = threadIdx.x;
-  const int w = __builtin_amdgcn_readfirstlane(tid0 >> 6);
-  const int L0 = tid0 & 63;
+  __shared__ __align__(16) FusedSmem S;
+  const int tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int L = tid & 63;
   const int nx = D.nx, ny = D.ny;
   // workgroup -> (segment, strip, distribution); contiguous ranges per XCD
   // put neighbouring strips, which share halo columns, on one L2
@@ -601,65 +680,71 @@ __global__ __launch_bounds__(SNT) void fused_kernel(Dev D, FusedArgs A, const do
   const int x0 = strip * SW;
   const int ya = seg * A.seglen;
   const int yb = min(ya + A.seglen, ny);
-  const double eps12 = 12.0 * D.weno_eps;
+  const double bb = FIRST ? A.a + A.b : A.b;  // the first stage has f^n = f^(s-1)
+  WenoK K{A.e3, A.e75, -2.75, -1.25, 2.5};
+  asm volatile("" : "+s"(K.m275), "+s"(K.m125), "+s"(K.p25));
 
-  if (tid0 < 256) {
-    const int e = (tid0 & 15) * Q + ((tid0 >> 4) & 3) + 4 * (tid0 >> 6);
-    S.aop[tid0 >> 6][tid0 & 63] = dpmg[e];
-    S.eop[tid0 >> 6][tid0 & 63] = meqg[e];
+  if (tid < 256) {
+    const int b = tid >> 6;
+    S.eop[b][L] = meqg[(L & 15) * Q + (L >> 4) + 4 * b];
+    const double p = velg[4 * b + (L >> 4)];
+    const int m = L & 3;
+    S.pw[b][L] = m == 0 ? 1.0 : (m == 1 ? p : (m == 2 ? p * p : p * p * p));
   }
-  if (tid0 < Q) S.vel[tid0] = velg[tid0];
+  if (tid < Q) S.vel[tid] = velg[tid];
+  if (tid < 2 * V) S.U[tid >> 8][((tid >> 4) & 15) * KS + (tid & 15) * PS + CZERO] = 0.0;
 
   const long long dofs = (long long)d * V * D.ntot;
-  const __amdgpu_buffer_rsrc_t rs = buf(A.fs + dofs), r0 = buf((FIRST ? A.fs : A.f0) + dofs);
-  const __amdgpu_buffer_rsrc_t ro = buf2g(A.out + dofs), rf = buf(A.fld);
+  const __amdgpu_buffer_rsrc_t rs = buf(A.fs + dofs), r0 = buf((FIRST ? A.fs : A.f0) + dofs), rf = buf(A.fld);
   auto wrapx = [&](int x) { x %= nx; return x < 0 ? x + nx : x; };
-  // per-lane byte offset of velocity (w, r) at the lane's column; (w, r + 8)
-  // is 64 bytes further, a row nx V doubles further
-  const unsigned vo = ((unsigned)wrapx(x0 + (L0 & 7)) * (unsigned)V + 16u * (unsigned)w + (unsigned)(L0 >> 3)) * 8u;
-  constexpr unsigned pso = 8u * 8u;
+  const bool mir = w < 8;
+  const int cl = L & 7, r = L >> 3;
+  auto colx = [&](int c) { return mir ? x0 + SW - 1 - c : x0 + c; };  // the wavefront's orientation
+  const int nc = mir ? SW - 1 - cl : cl;                                // node column of the lane
+  // byte offsets of the lane's velocities (w, r), (w, 15 - r) at its column;
+  // a row is rowb further; stores of columns past the domain are dropped
+  const unsigned vo0 = ((unsigned)wrapx(x0 + nc) * (unsigned)V + 16u * (unsigned)w + (unsigned)r) * 8u;
+  const unsigned vo1 = vo0 + (unsigned)(15 - 2 * r) * 8u;
+  const unsigned vs0 = x0 + nc < nx ? vo0 : BUF_DROP, vs1 = x0 + nc < nx ? vo1 : BUF_DROP;
   const unsigned rowb = (unsigned)nx * (unsigned)V * 8u;
   // the wavefront's halo, 16 velocities x 6 columns (a 128-byte line each):
-  // lane L takes l = L >> 2 of column x0 - 3, x0 - 2, x0 - 1, x0 + 8 for
-  // L & 3 = 0 .. 3, and l = (L & 31) >> 1 of column x0 + 9 + (L & 1) (lanes
-  // 32 - 63 repeat 0 - 31); each load still covers whole lines, and the LDS
-  // writes of a 16-lane pass fall on at least 8 banks
-  const unsigned hvoA = ((unsigned)wrapx((L0 & 3) < 3 ? x0 - 3 + (L0 & 3) : x0 + SW) * (unsigned)V +
-                         16u * (unsigned)w + (unsigned)(L0 >> 2)) * 8u;
-  const unsigned hvoB = ((unsigned)wrapx(x0 + SW + 1 + (L0 & 1)) * (unsigned)V + 16u * (unsigned)w +
-                         (unsigned)((L0 & 31) >> 1)) * 8u;
+  // lane L takes l = L >> 2 of column -3, -2, -1, 8 for L & 3 = 0 .. 3, and
+  // l = (L & 31) >> 1 of column 9 + (L & 1) (lanes 32 - 63 repeat 0 - 31)
+  const int hcA = (L & 3) < 3 ? (L & 3) - 3 : SW, hcB = SW + 1 + (L & 1);
+  const int hlA = L >> 2, hlB = (L & 31) >> 1;
+  const unsigned hvoA = ((unsigned)wrapx(colx(hcA)) * (unsigned)V + (unsigned)(16 * w + hlA)) * 8u;
+  const unsigned hvoB = ((unsigned)wrapx(colx(hcB)) * (unsigned)V + (unsigned)(16 * w + hlB)) * 8u;
   // node fields [NF][ntot]: thread t < NF SW loads field t / SW of column t % SW
-  const bool fthr = tid0 < NF * SW;
+  const bool fthr = tid < NF * SW;
   const unsigned fvo =
-      fthr ? ((unsigned)(tid0 / SW) * (unsigned)D.ntot + (unsigned)wrapx(x0 + (tid0 & (SW - 1)))) * 8u : 0u;
+      fthr ? ((unsigned)(tid / SW) * (unsigned)D.ntot + (unsigned)wrapx(x0 + (tid & (SW - 1)))) * 8u : 0u;
   const unsigned rowf = (unsigned)nx * 8u;
-  const double pk = velg[w];
-  const double pxi = pk * D.inv_dx;
-  // MFMA A operand of the raw-sum weights of this wavefront's k, for sums
-  // s < 8 over l < 8 in rows i = s and over l >= 8 in rows i = 8 + s: lane
-  // i + 16 c holds C[s][l = c + 4 b + 8 (i >> 3)] (p = p_k, q = p_l):
-  //   F: n: 1, j_x: p, j_y: q, P_xx: p^2, P_xy: p q, P_yy: q^2,
-  //      r_x: p (p^2 + q^2), r_y: q (p^2 + q^2);  G: g0: 1, h_x: p, h_y: q
-  double mop[2];
+  const double pk = velg[w], pr = velg[r];
+  // x faces, in the wavefront's orientation (uniform: in scalar registers)
+  const unsigned long long cpxb = __builtin_bit_cast(unsigned long long, A.c * D.inv_dx * fabs(pk));
+  const double cpx = __builtin_bit_cast(
+      double, (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)cpxb) |
+                  ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(cpxb >> 32)) << 32));
+  const double cpy = A.c * D.inv_dx * pr;        // y faces of l = r; of l = 15 - r with the other sign
+  // MFMA A operands: Dp along a mirror pair (mirror_dp), and the powers of
+  // p_l of the moments, for the indices of the lane's block and their mirrors
+  double dop[4], mop[2];
+  {
+    const int i = L & 3, par = (L >> 3) & 1, k = L >> 4;
+    const double* dp = dpmg + (2 * i + par) * Q;
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    const int i = L0 & 7;
-    const double q = velg[(L0 >> 4) + 4 * b + (L0 & 8)], pq2 = pk * pk + q * q;
-    double cw = 0.0;
-    if (i == 0) cw = 1.0;
-    else if (i == 1) cw = pk;
-    else if (i == 2) cw = q;
-    else if (d == 0 && i == 3) cw = pk * pk;
-    else if (d == 0 && i == 4) cw = pk * q;
-    else if (d == 0 && i == 5) cw = q * q;
-    else if (d == 0 && i == 6) cw = pk * pq2;
-    else if (d == 0 && i == 7) cw = q * pq2;
-    mop[b] = cw;
+    for (int s = 0; s < 2; ++s) {
+      const int j = 2 * k + (par ^ s);
+      dop[s] = fma(0.5, dp[15 - j], 0.5 * dp[j]);
+      dop[2 + s] = fma(-0.5, dp[15 - j], 0.5 * dp[j]);
+    }
+    const double p = velg[2 * k + par];
+    const double p2 = p * p;
+    mop[0] = i == 0 ? 1.0 : (i == 1 ? p : (i == 2 ? p2 : p * p2));
+    mop[1] = (i & 1) ? -mop[0] : mop[0];
   }
-  const bool PX = pk > 0.0;  // uniform per wavefront
-  const double bb = FIRST ? A.a + A.b : A.b;  // the first stage has f^n = f^(s-1)
 
-  // y within 4 rows of the domain (ny >= 8)
+  // y within 6 rows of the domain (ny >= 8)
   auto wrapy = [&](int y) { return (unsigned)(y < 0 ? y + ny : (y >= ny ? y - ny : y)); };
   auto rowso = [&](int y) { return wrapy(y) * rowb; };
   auto rowsf = [&](int y) { return wrapy(y) * rowf; };
@@ -669,299 +754,222 @@ __global__ __launch_bounds__(SNT) void fused_kernel(Dev D, FusedArgs A, const do
   // y + 3) for j = 0 (p_l < 0), so that the face between rows y and y + 1 is
   // weno5(R0 .. R4), resp. weno5(R4 .. R0), and the row dropped after the
   // face is always R0.
+  double fpre[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) fpre[i] = bload(rf, fvo, rowsf(ya + i));
   double R5[2][5];
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) R5[j][i] = bload(rs, vo, j * pso + rowso(ya - 1 - j + i));
+    R5[0][i] = bload(rs, vo0, rowso(ya - 1 + i));
+    R5[1][i] = bload(rs, vo1, rowso(ya - 2 + i));
   }
-  double fyl[2] = {0.0, 0.0};
-  if (ADV) {  // the face between rows ya - 1 and ya
-    const double e0 = bload(rs, vo, rowso(ya - 2)), e1 = bload(rs, vo, pso + rowso(ya - 3));
-    fyl[0] = weno5(R5[0][3], R5[0][2], R5[0][1], R5[0][0], e0, eps12);
-    fyl[1] = weno5(e1, R5[1][0], R5[1][1], R5[1][2], R5[1][3], eps12);
+  double e0 = 0.0, e1 = 0.0;
+  if (ADV) {
+    e0 = bload(rs, vo0, rowso(ya - 2));
+    e1 = bload(rs, vo1, rowso(ya - 3));
   }
-  // f^n and the halo of row ya, node fields of rows ya .. ya + 3
+  // f^n and the halo of row ya, node fields of row ya + 4
   double f0v[2] = {0.0, 0.0}, hv[2];
   if (!FIRST) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) f0v[j] = bload(r0, vo, j * pso + rowso(ya));
+    f0v[0] = bload(r0, vo0, rowso(ya));
+    f0v[1] = bload(r0, vo1, rowso(ya));
   }
   hv[0] = bload(rs, hvoA, rowso(ya));
   hv[1] = bload(rs, hvoB, rowso(ya));
-  double fq = bload(rf, fvo, rowsf(ya + 3));
-  const double fq2 = bload(rf, fvo, rowsf(ya + 2));
+  double fq = bload(rf, fvo, rowsf(ya + 4));
+  // node tables: fields of rows ya .. ya + 3, Hermite and collision
+  // coefficients of these, expansions of ya .. ya + 2, row tables of ya, ya + 1
   if (fthr) {
-    S.fl[ya & 1][tid0 / SW][tid0 & (SW - 1)] = bload(rf, fvo, rowsf(ya));
-    S.fl[(ya + 1) & 1][tid0 / SW][tid0 & (SW - 1)] = bload(rf, fvo, rowsf(ya + 1));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) S.fl[(ya + i) & 3][tid / SW][tid & (SW - 1)] = fpre[i];
   }
   __syncthreads();
-  // Hermite and collision coefficients of rows ya, ya + 1
-  if (w == 1 && L0 < 32) fused_hermite(S, (ya + (L0 >> 4)) & 1, L0 & 15);
-  if (w == 3 && L0 < 16) fused_coeffs(D, S, (ya + (L0 >> 3)) & 1, (ya + (L0 >> 3)) & 3, L0 & 7, d);
+  if (w == 1) fused_hermite(S, (ya + (L >> 4)) & 3, L & 15);
+  if (w == 3 && L < 32) fused_coeffs(D, S, (ya + (L >> 3)) & 3, L & 7, d, bb, A.c);
   __syncthreads();
-  // their expansions; the node fields of row ya + 2 replace those of row ya
-  if (w == 1) fused_expansions(S, ya & 1, L0);
-  if (w == 2) fused_expansions(S, (ya + 1) & 1, L0);
-  if (fthr) S.fl[ya & 1][tid0 / SW][tid0 & (SW - 1)] = fq2;
+  if (w < 3) fused_expansions(S, (ya + w) & 3, L);
   __syncthreads();
-  if (w == 1 && L0 < 16) fused_hermite(S, ya & 1, L0);
-  if (w == 3 && L0 < 8) fused_coeffs(D, S, ya & 1, (ya + 2) & 3, L0, d);
+  if (w < 4) fused_rowtab(S, (ya + (w >> 1)) & 3, S.tab[w >> 1], w & 1, L);
+  double fyl[2] = {0.0, 0.0};
+  if (ADV) {  // the face between rows ya - 1 and ya
+    fyl[0] = weno5(R5[0][3], R5[0][2], R5[0][1], R5[0][0], e0, K);
+    fyl[1] = weno5(e1, R5[1][0], R5[1][1], R5[1][2], R5[1][3], K);
+  }
   __syncthreads();
 
-  const int nsum = d == 0 ? 8 : 3;
   double accP[2] = {0.0, 0.0}, cfxP = 0.0;  // acc and c F_x of the row before
-  // Byte offsets in the shared block of this lane's writes of row y into FI
-  // (slot 0; l = r, r + 8) and of its halo values into T and FI, formed once
-  // and held opaque, so that the compiler keeps them in registers instead of
-  // deriving them again every row.
-  unsigned ofi[2], oh[4];
-  {
-    const int r0 = L0 >> 3, c0 = L0 & 7;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int l = r0 + 8 * j;
-      ofi[j] = (unsigned)offsetof(FusedSmem, FI) + 8u * (unsigned)(w * FIS + 8 * l + (c0 ^ ((l >> 1) & 7)));
-    }
-    const int lA = L0 >> 2, hA = L0 & 3, lB = (L0 & 31) >> 1, hB = 4 + (L0 & 1);
-    oh[0] = (unsigned)offsetof(FusedSmem, T) + 8u * (unsigned)((16 * w + lA) * TS + (hA < 3 ? hA : SW + hA));
-    oh[1] = (unsigned)offsetof(FusedSmem, FI) + 8u * (unsigned)(w * FIS + 16 * SW + 3 * lA);
-    oh[2] = (unsigned)offsetof(FusedSmem, T) + 8u * (unsigned)((16 * w + lB) * TS + SW + hB);
-    oh[3] = (unsigned)offsetof(FusedSmem, FI) + 8u * (unsigned)(w * FIS + 16 * SW + 3 * lB + hB - 3);
-  }
-  asm volatile("" : "+v"(ofi[0]), "+v"(ofi[1]), "+v"(oh[0]), "+v"(oh[1]), "+v"(oh[2]), "+v"(oh[3]));
+  // Byte offsets into the shared block, formed once and held opaque, so that
+  // the compiler keeps them in registers instead of deriving them again every
+  // row: the lane's columns of its two planes, its halo values, its parts of
+  // the row table, its moment, and two for the wavefront's own part of post:
+  // (Dp x I) f at (k, 15 - k, l) or the plane of its edge face.
   char* const Sb = (char*)&S;
-  auto lds = [&](unsigned o) -> double& { return *(double*)(Sb + o); };
+  unsigned b0 = 8u * (unsigned)(w * KS + r * PS + cl), b1 = 8u * (unsigned)(w * KS + (15 - r) * PS + cl);
+  unsigned hA = 8u * (unsigned)(w * KS + hlA * PS + hcA + 3), hB = 8u * (unsigned)(w * KS + hlB * PS + hcB + 3);
+  unsigned tP = (unsigned)(offsetof(FusedSmem, tab) + offsetof(RowTab, P)) + 32u * (unsigned)(w * SW + nc);
+  unsigned tE = (unsigned)(offsetof(FusedSmem, tab) + offsetof(RowTab, E)) + 48u * (unsigned)(r * SW + nc);
+  unsigned mw = (unsigned)offsetof(FusedSmem, mred) + 8u * (unsigned)(48 * w + 8 * (L >> 4) + nc);
+  unsigned s0 = 0, s1 = 0;
+  if (w >= 8) {
+    s0 = 8u * (unsigned)(r * KS + 2 * (w - 8) * PS + 3 + SW - 1 - cl);
+    s1 = 8u * (unsigned)((15 - r) * KS + 2 * (w - 8) * PS + 3 + cl);
+  } else if (w >= 4) {
+    s0 = 8u * (unsigned)((4 * (w - 4) + (L >> 4)) * KS + (L & 15) * PS);
+  }
+  asm volatile("" : "+v"(b0), "+v"(b1), "+v"(hA), "+v"(hB));
+  asm volatile("" : "+v"(tP), "+v"(tE), "+v"(mw), "+v"(s0), "+v"(s1));
+  auto lds = [&](unsigned o, int i) -> double& { return *((double*)(Sb + o) + i); };
+  auto lds2 = [&](unsigned o, int i) -> dbl2 { return *((const dbl2*)(Sb + o) + i); };
   // One row of the march.  The ring is not shifted: row y uses the slots
-  // rotated by ROT = (y - ya) mod 5 (slot (i + ROT) mod 5 holds ring entry
-  // i), and the march is unrolled five rows at a time so that every slot
-  // index is a constant.
+  // rotated by (y - ya) mod 5 (slot (i + ROT) mod 5 holds ring entry i), and
+  // row slot (y - ya) mod 2 of the shared block; the march is unrolled ten
+  // rows at a time, so that every slot index is a constant and every LDS
+  // address a held register plus an immediate.
   auto row = [&](auto rotc, const int y) {
     constexpr int ROT = decltype(rotc)::value;
+    constexpr int p = ROT & 1;                       // slots of rows y, y - 2
+    constexpr int U0 = p * USLOT, U1 = (1 - p) * USLOT;  // rows y and y - 1 in the shared block
+    constexpr int TAB = p * (int)sizeof(RowTab);
     auto R = [&](int j, int i) -> double& { return R5[j][(i + ROT) % 5]; };
-    // Opaque per-row copies of the thread indices: every LDS address and
-    // table value below is derived from them inside the row, so that the
-    // compiler does not hoist them out of the loop and hold (or spill) them
-    // across it.
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    const int L = tid & 63, col = L & (SW - 1), r = L >> 3;
-    const int yp = y & 1;
     double accN[2] = {0.0, 0.0}, cfxN = 0.0;
     // ---------------- pre(y) ----------------
-    double* Tw = &S.T[16 * w * TS];  // this wavefront's 16 velocities
-    const double* cf = &S.CF[y & 3][0][col];
-    double part[2] = {0.0, 0.0}, base[2] = {0.0, 0.0};
     if (y < yb) {
-      const unsigned fslot = (unsigned)yp * (unsigned)(Q * FIS * 8);  // FI[yp]
-      const double nu = cf[CF_NU * SW];
-      double cur[2];
-      cur[0] = R(0, 1);  // row y
-      cur[1] = R(1, 2);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        Tw[(r + 8 * j) * TS + 3 + col] = cur[j];
-        lds(ofi[j] + fslot) = cur[j];  // FI[yp][w][8 l + (col ^ ((l >> 1) & 7))]
-        base[j] = fma(A.a, f0v[j], bb * cur[j]);
-        part[j] = -nu * cur[j];
+      const double cur0 = R(0, 1), cur1 = R(1, 2);  // row y
+      lds(b0, U0 + 3) = cur0;
+      lds(b1, U0 + 3) = cur1;
+      lds(hA, U0) = hv[0];
+      lds(hB, U0) = hv[1];
+      if (fthr) S.fl[y & 3][tid / SW][tid & (SW - 1)] = fq;  // row y + 4
+      const dbl2 nA = lds2(tE + TAB, 0), nB = lds2(tE + TAB, 1);
+      if (FIRST) {
+        accN[0] = nA[1] * cur0;
+        accN[1] = nA[1] * cur1;
+      } else {
+        accN[0] = fma(A.a, f0v[0], nA[1] * cur0);
+        accN[1] = fma(A.a, f0v[1], nA[1] * cur1);
       }
-      // the halo: T of columns x0 - 3 .. x0 - 1, x0 + 8 .. x0 + 10, FI of
-      // columns x0 + 8 .. x0 + 10
-      lds(oh[0]) = hv[0];
-      if ((L & 3) == 3) lds(oh[1] + fslot) = hv[0];
-      lds(oh[2]) = hv[1];
-      lds(oh[3] + fslot) = hv[1];
-      if (tid < NF * SW) S.fl[(y + 3) & 1][tid / SW][tid & (SW - 1)] = fq;
       if (ADV) {
         // y faces: j = 0 upwind from above, j = 1 from below
-        const double fyr0 = weno5(R(0, 4), R(0, 3), R(0, 2), R(0, 1), R(0, 0), eps12);
-        const double fyr1 = weno5(R(1, 0), R(1, 1), R(1, 2), R(1, 3), R(1, 4), eps12);
-        part[0] = fma(D.inv_dx * S.vel[r], fyl[0] - fyr0, part[0]);
-        part[1] = fma(D.inv_dx * S.vel[r + 8], fyl[1] - fyr1, part[1]);
+        const double fyr0 = weno5(R(0, 4), R(0, 3), R(0, 2), R(0, 1), R(0, 0), K);
+        const double fyr1 = weno5(R(1, 0), R(1, 1), R(1, 2), R(1, 3), R(1, 4), K);
+        accN[0] = fma(cpy, fyl[0] - fyr0, accN[0]);
+        accN[1] = fma(cpy, fyr1 - fyl[1], accN[1]);
         fyl[0] = fyr0;
         fyl[1] = fyr1;
       }
+      if (FRC) {
+        double gy0, gy1;
+        mirror_dp(dop, cur0, cur1, gy0, gy1);
+        accN[0] = fma(-nB[1], gy0, accN[0]);
+        accN[1] = fma(-nB[1], gy1, accN[1]);
+        cfxN = nB[0];
+      }
+      // collision terms
+      const dbl2 PA = lds2(tP + TAB, 0), PB = lds2(tP + TAB, 1), el = lds2(tE + TAB, 2);
+      const double xy0 = pr - nA[0], xy1 = -pr - nA[0];
+      accN[0] = fma(el[0], fma(xy0, fma(xy0, fma(PB[1], xy0, PB[0]), PA[1]), PA[0]), accN[0]);
+      accN[1] = fma(el[1], fma(xy1, fma(xy1, fma(PB[1], xy1, PB[0]), PA[1]), PA[0]), accN[1]);
     }
-    // in flight across the rest of this iteration: node fields of row y + 4
+    // in flight across the rest of this iteration: node fields of row y + 5
     // (issued first: the wait for it in the next iteration then leaves the
     // later loads in flight), the ring's next row (into the slot just
     // dropped), f^n and the halo of row y + 1.  Outside the condition, and
     // past the segment too: a load under a condition would make the
     // compiler copy the register at the loop latch, which waits for every
     // load in flight.
-    fq = bload(rf, fvo, rowsf(y + 4));
-#pragma unroll
-    for (int j = 0; j < 2; ++j) R(j, 0) = bload(rs, vo, j * pso + rowso(y + 4 - j));  // row (y + 1) + 3 - j
+    fq = bload(rf, fvo, rowsf(y + 5));
+    R(0, 0) = bload(rs, vo0, rowso(y + 4));
+    R(1, 0) = bload(rs, vo1, rowso(y + 3));
     {
       const unsigned so1 = rowso(y + 1);
       if (!FIRST) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) f0v[j] = bload(r0, vo, j * pso + so1);
+        f0v[0] = bload(r0, vo0, so1);
+        f0v[1] = bload(r0, vo1, so1);
       }
       hv[0] = bload(rs, hvoA, so1);
       hv[1] = bload(rs, hvoB, so1);
     }
-    if (y < yb) {
-      if (ADV) {
-        // x faces from this wavefront's LDS row: each lane the face on its
-        // left, the face on its right from the next lane (the last column:
-        // the strip-edge face, added in post(y + 1))
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const double* t = &Tw[(r + 8 * j) * TS + col];
-          const double lf = PX ? weno5(t[0], t[1], t[2], t[3], t[4], eps12)
-                               : weno5(t[5], t[4], t[3], t[2], t[1], eps12);
-          // every lane runs the DPP move (a lane masked off would read as 0
-          // to its neighbour), then the last column drops what it read
-          const double nb = row_next(lf);
-          const double rf = col == SW - 1 ? 0.0 : nb;
-          part[j] = fma(pxi, lf - rf, part[j]);
-        }
-      }
-      double dy[2] = {0.0, 0.0};
-      const bool odd = ((y - ya) & 1) != 0;
-      if (FRC && (odd || y == yb - 1)) {
-        // (I x Dp) f for k = w of two rows at once: B[c][col16] = f(w, l =
-        // c + 4 b) at column col16 & 7 of row y - 1 (col16 < 8) or row y
-        // (col16 >= 8), both from this wavefront's interior of FI (the slot
-        // of row y - 1 is rewritten only in pre(y + 1)).  Row l' = 4 j + c of
-        // the result goes through columns 14 - 21 of T to the lanes that own
-        // it: row y's into this row's sum, row y - 1's (odd rows of the
-        // segment; the even rows before them ran no MFMA) into the sum of the
-        // row before.
-        const int c4 = L >> 4, c8 = L & 7;
-        const bool hi = (L & 8) != 0;
-        const double* fp = &S.FI[hi ? yp : 1 - yp][w][0];
-        const int x = c8 ^ (c4 >> 1);  // the swizzle of l = c4 + 4 b is x ^ 2 b
-        dbl4 dd = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-          dd = __builtin_amdgcn_mfma_f64_16x16x4f64(S.aop[b][L], fp[8 * (c4 + 4 * b) + (x ^ (2 * b))], dd, 0, 0, 0);
-        if (hi) {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) Tw[(4 * j + c4) * TS + 14 + c8] = dd[j];
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) dy[j] = Tw[(r + 8 * j) * TS + 14 + col];
-        if (odd) {
-          if (!hi) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) Tw[(4 * j + c4) * TS + 14 + c8] = dd[j];
-          }
-          // the lanes that wrote nothing still read what the others wrote:
-          // keep the compiler from reusing the values read above
-          asm volatile("" ::: "memory");
-          const double fyp = A.c * S.CF[(y - 1) & 3][CF_FY][col];
-#pragma unroll
-          for (int j = 0; j < 2; ++j) accP[j] = fma(-fyp, Tw[(r + 8 * j) * TS + 14 + col], accP[j]);
-        }
-      }
-      // collision terms: with xi_x = p_k - u_x fixed per wavefront, the row
-      // polynomial in xi_y = p_l - u_y
-      const double xx = pk - cf[CF_UX * SW];
-      const double c3 = cf[CF_C3 * SW], d2 = cf[CF_D2 * SW];
-      const double P0 = fma(xx, fma(xx, fma(c3, xx, cf[CF_C2 * SW]), cf[CF_C1 * SW]), cf[CF_C0 * SW]);
-      const double P1 = fma(xx, fma(d2, xx, cf[CF_D1 * SW]), cf[CF_D0 * SW]);
-      const double P2 = fma(c3, xx, cf[CF_E0 * SW]);
-      const double tfe = cf[CF_TFN * SW] * S.EK[yp][0][w][col];  // tf n e_k(u_x)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int l = r + 8 * j;
-        const double xy = S.vel[l] - cf[CF_UY * SW];
-        double Lc = tfe * S.EK[yp][1][l][col] * fma(xy, fma(xy, fma(d2, xy, P2), P1), P0);
-        if (FRC) Lc = fma(-cf[CF_FY * SW], dy[j], Lc);
-        accN[j] = fma(A.c, part[j] + Lc, base[j]);
-      }
-      if (FRC) cfxN = A.c * cf[CF_FX * SW];
+    if (ADV && y < yb) {
+      // x faces from this wavefront's LDS row: each lane the face on its
+      // left (in the wavefront's orientation), the face on its right from
+      // the next lane (the last column reads the zero column; its right face
+      // is the strip-edge face, added in post(y + 1)).  The fences keep the
+      // compiler from moving a lane's reads of other lanes' values.
+      asm volatile("" ::: "memory");
+      const double lf0 = weno5(lds(b0, U0), lds(b0, U0 + 1), lds(b0, U0 + 2), lds(b0, U0 + 3), lds(b0, U0 + 4), K);
+      const double lf1 = weno5(lds(b1, U0), lds(b1, U0 + 1), lds(b1, U0 + 2), lds(b1, U0 + 3), lds(b1, U0 + 4), K);
+      lds(b0, U0 + CDX) = lf0;
+      lds(b1, U0 + CDX) = lf1;
+      asm volatile("" ::: "memory");
+      accN[0] = fma(cpx, lf0 - lds(b0, U0 + CDX + 1), accN[0]);
+      accN[1] = fma(cpx, lf1 - lds(b1, U0 + CDX + 1), accN[1]);
     }
     __syncthreads();
     // ---------------- post(y) ----------------
     {
-      // f^(s) of row y - 1 (y > ya).  The stores run every iteration, those
-      // with nothing to store at an offset past the buffer, so that every
-      // iteration issues the same vector memory operations and the wait for
-      // a load issued before them never has to drain them.
-      const int pb = (y - 1) & 1;
+      // f^(s) of row y - 1 (y > ya).  The stores run every iteration, into
+      // an empty buffer where there is no row, so that every iteration
+      // issues the same vector memory operations and the wait for a load
+      // issued before them never has to drain them.
       const bool live = y > ya;
-      const unsigned so = live && x0 + col < nx ? vo + rowso(y - 1) : BUF_DROP;
-      double* Tw = &S.T[16 * w * TS];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int l = r + 8 * j;
-        double o = accP[j];
-        if (live) {
-          if (FRC) o = fma(-cfxP, S.DX[pb][w][8 * (l ^ (2 * (w & 1))) + col], o);
-          if (ADV && col == SW - 1) o = fma(-A.c * pxi, S.T[(16 * w + l) * TS + 22 + pb], o);
-        }
-        bstore(o, ro, so == BUF_DROP ? BUF_DROP : so + j * pso, 0);
-        Tw[l * TS + 14 + col] = o;  // free until pre(y + 1)
+      const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+          (void*)(A.out + dofs), (short)0, live ? (int)0x80000000u : 0, BUF_DWORD3);
+      const unsigned so = live ? rowso(y - 1) : 0u;
+      double o0 = accP[0], o1 = accP[1];
+      if (FRC) {
+        o0 = fma(-cfxP, lds(b0, U1 + CDX), o0);
+        o1 = fma(-cfxP, lds(b1, U1 + CDX), o1);
       }
-      if (live && A.want_mom) {
-        // this wavefront's terms of the raw sums, C f^(s) with C[s][l] the
-        // weights of sum s (mop), on the MFMA: B[c][col16] = f^(s)(w, l =
-        // c + 4 b + 8 h) at column col16 & 7, h = col16 >> 3.  Sum s = 4 j + c
-        // of a column is row s of the result at col16 < 8 (over l < 8) plus
-        // row 8 + s at col16 + 8 (over l >= 8), eight lanes further.
-        const int c4 = L >> 4, c8 = L & 7;
-        dbl4 dd = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          dd = __builtin_amdgcn_mfma_f64_16x16x4f64(mop[b], Tw[(c4 + 4 * b + (L & 8)) * TS + 14 + c8], dd, 0, 0, 0);
-        const double s0 = dd[0] + row_shl<8>(dd[2]), s1 = dd[1] + row_shl<8>(dd[3]);
-        if ((L & 8) == 0) {
-          S.mred[pb][w][c4][c8] = s0;
-          S.mred[pb][w][4 + c4][c8] = s1;
-        }
+      if (ADV && cl == SW - 1) {
+        o0 = fma(-cpx, lds(b0, U1 + CEDGE - (SW - 1)), o0);
+        o1 = fma(-cpx, lds(b1, U1 + CEDGE - (SW - 1)), o1);
+      }
+      bstore(o0, ro, vs0, so);
+      bstore(o1, ro, vs1, so);
+      if (A.want_mom) {
+        // moments of this wavefront's 16 velocities per column
+        const double m0 = mfma4(mop[1], o1, mfma4(mop[0], o0, 0.0));
+        lds(mw, (1 - p) * (SNW * 48)) = m0 + row_half(m0);
       }
     }
     // the serial chains on the oldest wavefront of each SIMD (the arbiter
-    // issues the oldest first), the strip-edge faces (VALU) on the next
-    // oldest, the MFMA work on the two youngest
+    // issues the oldest first), the strip-edge faces on the next oldest, the
+    // MFMA work on the two youngest.  Their addresses come from an opaque copy
+    // of the lane index, so that the compiler does not hoist them out of the
+    // march and hold (or spill) them across it.
+    int Lq = L;
+    asm volatile("" : "+v"(Lq));
     if (w == 0) {
-      if (A.want_mom && y - 2 >= ya && L < nsum * SW) fused_raw_sum(D, A, S, d, L, x0, y - 2);
+      if (A.want_mom && y - 2 >= ya) fused_raw_sum(D, A, S, d, p, Lq, x0, y - 2);
+      if (y + 2 < yb) fused_rowtab(S, (y + 2) & 3, S.tab[p], 0, Lq);
     } else if (w == 1) {
-      // Hermite coefficients of row y + 3
-      if (y + 3 < yb && L < 16) fused_hermite(S, (y + 3) & 1, L);
+      if (y + 4 < yb && Lq < 16) fused_hermite(S, y & 3, Lq);
     } else if (w == 2) {
-      if (y + 2 < yb) fused_expansions(S, (y + 2) & 1, L);
+      if (y + 3 < yb) fused_expansions(S, (y + 3) & 3, Lq);
     } else if (w == 3) {
-      // collision coefficients of row y + 3
-      if (y + 3 < yb && L < SW) fused_coeffs(D, S, (y + 3) & 1, (y + 3) & 3, L, d);
+      if (y + 2 < yb) fused_rowtab(S, (y + 2) & 3, S.tab[p], 1, Lq);
+      if (y + 4 < yb && Lq < SW) fused_coeffs(D, S, y & 3, Lq, d, bb, A.c);
     } else if (w >= 8) {
       if (FRC && y < yb) {
-        // (Dp x I) f for l = 2 (w - 8) + lh: B[c][col16] = f(k = c + 4 b, l),
-        // col16 = (column, lh)
-        const int c4 = L >> 4, lq = 2 * (w - 8) + ((L >> 3) & 1);
-        dbl4 dd = {0.0, 0.0, 0.0, 0.0};
+        // (Dp x I) f for l = 2 (w - 8) + lh, lane (k = r, column)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
-          dd = __builtin_amdgcn_mfma_f64_16x16x4f64(S.aop[b][L], S.FI[yp][c4 + 4 * b][8 * lq + (col ^ ((lq >> 1) & 7))],
-                                                    dd, 0, 0, 0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int k = 4 * j + c4;
-          S.DX[yp][k][8 * (lq ^ (2 * (k & 1))) + col] = dd[j];
+        for (int lh = 0; lh < 2; ++lh) {
+          double gx0, gx1;
+          mirror_dp(dop, lds(s0, U0 + lh * PS), lds(s1, U0 + lh * PS), gx0, gx1);
+          lds(s0, U0 + lh * PS + CDX - 3) = gx0;
+          lds(s1, U0 + lh * PS + CDX - 3) = gx1;
         }
       }
-    } else {  // wavefronts 4 - 7
-      if (ADV && y < yb) {
-        // the strip-edge face of velocity (k, l), q = 16 k + l, from the
-        // interior columns 5 - 7 and the right halo of FI, into the owner's T
-        const int q = 64 * (w - 4) + L, k = q >> 4, l = q & 15;
-        const double* fi = &S.FI[yp][k][8 * l];
-        const int sw = (l >> 1) & 7;
-        const double i5 = fi[5 ^ sw], i6 = fi[6 ^ sw], i7 = fi[7 ^ sw];
-        fi = &S.FI[yp][k][0];
-        const double h0 = fi[16 * SW + 3 * l], h1 = fi[16 * SW + 3 * l + 1], h2 = fi[16 * SW + 3 * l + 2];
-        const bool px = k >= 8;
-        S.T[q * TS + 22 + yp] = weno5(px ? i5 : h2, px ? i6 : h1, px ? i7 : h0, px ? h0 : i7, px ? h1 : i6, eps12);
-      }
+    } else if (ADV && y < yb) {
+      // wavefronts 4 - 7: the strip-edge face of one velocity per lane
+      lds(s0, U0 + CEDGE) = weno5(lds(s0, U0 + 8), lds(s0, U0 + 9), lds(s0, U0 + 10), lds(s0, U0 + 11),
+                                  lds(s0, U0 + 12), K);
     }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) accP[j] = accN[j];
+    accP[0] = accN[0];
+    accP[1] = accN[1];
     cfxP = cfxN;
   };
-  for (int y = ya; y <= yb; y += 5) {
+  for (int y = ya; y <= yb; y += 10) {
     row(RotC<0>(), y);
     if (y + 1 > yb) break;
     row(RotC<1>(), y + 1);
@@ -971,10 +979,20 @@ __global__ __launch_bounds__(SNT) void fused_kernel(Dev D, FusedArgs A, const do
     row(RotC<3>(), y + 3);
     if (y + 4 > yb) break;
     row(RotC<4>(), y + 4);
+    if (y + 5 > yb) break;
+    row(RotC<5>(), y + 5);
+    if (y + 6 > yb) break;
+    row(RotC<6>(), y + 6);
+    if (y + 7 > yb) break;
+    row(RotC<7>(), y + 7);
+    if (y + 8 > yb) break;
+    row(RotC<8>(), y + 8);
+    if (y + 9 > yb) break;
+    row(RotC<9>(), y + 9);
   }
   // velocity sums of the last row
   __syncthreads();
-  if (A.want_mom && w == 0 && L0 < nsum * SW) fused_raw_sum(D, A, S, d, L0, x0, yb - 1);
+  if (A.want_mom && w == 0) fused_raw_sum(D, A, S, d, (yb - 1 - ya) & 1, L, x0, yb - 1);
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1205,8 +1223,9 @@ int stage(Ctx* c, const double* fs, const double* f0, double* out, double a, dou
   if (rc) return rc;
   int nstrip, nseg, seglen;
   fused_shape(c, &nstrip, &nseg, &seglen);
-  FusedArgs A{fs, f0, out, (const double*)(c->ws + c->L.fld), (double*)(c->ws + c->L.raw), a, b, cc, first,
-              want_mom, nstrip, seglen};
+  const double eps = c->dev.weno_eps;
+  FusedArgs A{fs, f0, out, (const double*)(c->ws + c->L.fld), (double*)(c->ws + c->L.raw), a, b, cc, 0.3 * eps,
+              0.75 * eps, first, want_mom, nstrip, seglen};
   const dim3 grid((unsigned)(2 * nstrip * nseg));
   const bool adv = (c->dev.term_mask & EVLB_TERM_ADV) != 0, frc = (c->dev.term_mask & EVLB_TERM_FORCE) != 0;
   if (adv && frc)
