@@ -502,6 +502,14 @@ __device__ __forceinline__ double row_half(double v) {
   return __builtin_bit_cast(double, (unsigned long long)(unsigned)lo | ((unsigned long long)(unsigned)hi << 32));
 }
 
+// lanes 32 - 63 take the value of lanes 0 - 31
+__device__ __forceinline__ double half_lo(double v) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+  return __builtin_bit_cast(double, (unsigned long long)lo[0] | ((unsigned long long)hi[0] << 32));
+}
+
 typedef double dbl2 __attribute__((ext_vector_type(2)));
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
@@ -644,7 +652,7 @@ __device__ __forceinline__ void fused_raw_sum(const Dev& D, const FusedArgs& A, 
     u = mfma4(S.pw[t][L], mr[192 * t], u);
     if (d == 0) v = mfma4(S.pw[t][L], mr[192 * t + 16], v);
   }
-  const double w = __shfl_xor(v, 32);  // m ^ 2 of the second chain
+  const double w = half_lo(v);  // the second chain's m - 2 on the lanes of m >= 2
   if (x0 + c >= D.nx) return;
   double* raw = A.raw + (long long)y * D.nx + x0 + c;
   if (d == 0) {
