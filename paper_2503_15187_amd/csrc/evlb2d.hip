@@ -1040,6 +1040,34 @@ Layout make_layout(const evlb_params* p, const evlb::DiscTables& t) {
   return L;
 }
 
+// Split of the grid into workgroups of the fused stage: strips of SW columns,
+// two distributions, segments of rows.  A workgroup takes a CU's whole LDS, so
+// the launch runs in rounds of one workgroup per CU, and a segment costs its
+// rows and about FUSED_START rows' time for its prologue: the number of
+// segments that makes rounds x (rows + FUSED_START) smallest.  Measured per
+// stage against about one workgroup per CU in segments of at least 16 rows:
+// 64 x 48 nodes 16 segments 80, 3 segments 116 us; 333 x 270 (84 strips and
+// distributions on 256 CUs) 3 segments 353, 4 segments 512 us; 600 x 400 5
+// segments 896, 2 segments 1366 us; 1024 x 1024 one segment either way.  The
+// start's cost from 128 x 128 to 600 x 400 nodes: 12 to 15 us, a row's 2.6 to 3.5.
+constexpr int FUSED_START = 4;
+
+void fused_shape(int nx, int ny, int cus, int* nstrip, int* nseg, int* seglen) {
+  *nstrip = (nx + SW - 1) / SW;
+  long long best = -1;
+  for (int s = 1; s <= ny; ++s) {
+    const int len = (ny + s - 1) / s;
+    const int n = (ny + len - 1) / len;  // every segment non-empty
+    const long long wgs = 2ll * *nstrip * n;
+    const long long cost = (wgs + cus - 1) / cus * (len + FUSED_START);
+    if (best < 0 || cost < best) {
+      best = cost;
+      *nseg = n;
+      *seglen = len;
+    }
+  }
+}
+
 void disc_tables(const evlb_params* p, evlb::DiscTables& t) {
   evlb::build_disc_tables(p->dx, p->sigma, p->phi_sigma, p->r_cut, p->force_model == EVLB_FORCE_EV1, t);
 }
@@ -1053,6 +1081,7 @@ size_t fields_lds_bytes(int halo) {
 struct Ctx {
   evlb_params p;
   int nx, ny;
+  int nstrip, nseg, seglen;  // workgroups of the fused stage
   long long N;
   Layout L;
   Dev dev;
@@ -1116,6 +1145,13 @@ int init(const evlb_params* p, char* ws, size_t bytes, hipStream_t st, Ctx** out
   c->nx = p->nx[0];
   c->ny = p->ny;
   c->N = (long long)c->nx * c->ny;
+  int device = -1, cus = 0;
+  if (hipGetDevice(&device) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < 1) {
+    delete c;
+    return EVLB_EHIP;
+  }
+  fused_shape(c->nx, c->ny, cus, &c->nstrip, &c->nseg, &c->seglen);
   c->L = L;
   c->ws = ws;
   evlb::TableParams tp{Q, p->dx, p->sigma, p->phi_sigma, p->gamma, p->r_cut};
@@ -1202,19 +1238,6 @@ int launch_fields(Ctx* c, hipStream_t st) {
   return launched();
 }
 
-// Strips of SW columns, two distributions, and enough segments of rows for
-// about one workgroup per CU (at least 16 rows each: a segment re-reads the
-// six rows of its ring prologue).
-void fused_shape(const Ctx* c, int* nstrip, int* nseg, int* seglen) {
-  *nstrip = (c->nx + SW - 1) / SW;
-  int s = (256 + 2 * *nstrip - 1) / (2 * *nstrip);
-  const int smax = c->ny / 16 > 1 ? c->ny / 16 : 1;
-  if (s > smax) s = smax;
-  if (s < 1) s = 1;
-  *seglen = (c->ny + s - 1) / s;
-  *nseg = (c->ny + *seglen - 1) / *seglen;  // every segment non-empty
-}
-
 template <bool ADV, bool FRC>
 void launch_fused(Ctx* c, const FusedArgs& A, dim3 grid, int first, hipStream_t st) {
   if (first)
@@ -1229,12 +1252,10 @@ int stage(Ctx* c, const double* fs, const double* f0, double* out, double a, dou
           int want_mom, hipStream_t st) {
   int rc = launch_fields(c, st);
   if (rc) return rc;
-  int nstrip, nseg, seglen;
-  fused_shape(c, &nstrip, &nseg, &seglen);
   const double eps = c->dev.weno_eps;
   FusedArgs A{fs, f0, out, (const double*)(c->ws + c->L.fld), (double*)(c->ws + c->L.raw), a, b, cc, 0.3 * eps,
-              0.75 * eps, first, want_mom, nstrip, seglen};
-  const dim3 grid((unsigned)(2 * nstrip * nseg));
+              0.75 * eps, first, want_mom, c->nstrip, c->seglen};
+  const dim3 grid((unsigned)(2 * c->nstrip * c->nseg));
   const bool adv = (c->dev.term_mask & EVLB_TERM_ADV) != 0, frc = (c->dev.term_mask & EVLB_TERM_FORCE) != 0;
   if (adv && frc)
     launch_fused<true, true>(c, A, grid, first, st);
