@@ -10,7 +10,8 @@
 //
 // State d_f[2][16][16][ny][nx] (plane d*256 + k*16 + l, node fastest).  One
 // TVD-RK3 stage is two kernels:
-//   fields_kernel  32 x 8 nodes per workgroup, density tile with the force
+//   fields_kernel  32 x 16 (small grids: 16 x 8) nodes per workgroup, density
+//                  tile with the force
 //                  radius as halo in LDS: n, u, T, q from the raw velocity
 //                  sums, disc-averaged density, contact value (eq:carnstar),
 //                  force (antisymmetric cell pairs), transport
@@ -65,13 +66,14 @@ struct Dev {
   double weno_eps, g_ext;
   double T_iso;  // > 0: isothermal, the temperature the next stage sees
   int force_model, term_mask;
-  int navg, npair, halo;
+  int navg, npair, nrow, halo;  // cells of the averaging disc, pairs and rows of the force disc
   int* status;
 };
 
-__device__ __forceinline__ int wrap(int i, int n) {
-  const int r = i % n;
-  return r < 0 ? r + n : r;
+// i mod n for |i| < 2^22, inv = 1 / n: the quotient of i + 1/2 is at least
+// 1 / (2 n) away from an integer, the rounding of the product far less.
+__device__ __forceinline__ int wrap(int i, int n, float inv) {
+  return i - n * (int)floorf(((float)i + 0.5f) * inv);
 }
 
 // Raw velocity sums of one node -> n, u, T, q (Sec. II B moments with the
@@ -209,96 +211,257 @@ __global__ __launch_bounds__(256) void equilibrium_kernel(Dev D, const double* _
 // ---------------------------------------------------------------------------
 // node fields
 // ---------------------------------------------------------------------------
-constexpr int FTX = 32, FTY = 8, FNT = FTX * FTY;
-constexpr int GX = FTX + 4, GY = FTY + 4;  // tile +-2 (gradient stencil)
+typedef double dbl2 __attribute__((ext_vector_type(2)));
 
-// u_x, u_y and T from the raw sums of a node (3/2 n T = sum |xi|^2/2 F + G);
-// an isothermal run sees its fixed temperature
-__device__ __forceinline__ void flow_of(const double* __restrict__ raw, long long N, long long node, double T_iso,
-                                        double& ux, double& uy, double& T) {
-  const double n = raw[node];
-  ux = raw[N + node] / n;
-  uy = raw[2 * N + node] / n;
-  const double e = 0.5 * (raw[3 * N + node] + raw[5 * N + node]) + raw[8 * N + node];
+// Tile of a workgroup: TX x TY nodes, NT threads.  The force sums give a lane
+// XN nodes along x and each group of TX TY / XN lanes a share of the disc's
+// rows; the averaged density takes AV threads per node.
+template <int TX_, int TY_, int XN_, int NT_>
+struct FieldsShape {
+  static constexpr int TX = TX_, TY = TY_, XN = XN_, NT = NT_, NODES = TX * TY;
+  static constexpr int GX = TX + 4, GY = TY + 4;  // tile +-2 (gradient stencil)
+  static constexpr int LANES = NODES / XN;        // of a group
+  static constexpr int FG = NT / LANES;           // groups
+  static constexpr int AV = NT >= 2 * GX * GY ? 2 : 1;
+  static_assert(TX % XN == 0 && (LANES == 64 || LANES == 32) && FG % 2 == 0, "groups fill wavefronts");
+  static_assert(NT >= NODES, "a thread per node");
+  // Width of the density tile's rows in LDS: the tile and its halo, made 1
+  // (mod XN), so that lanes XN nodes apart in x and rows apart in y hit
+  // distinct banks.
+  __host__ __device__ static constexpr int px(int halo) { return (TX + 2 * halo + XN - 2) / XN * XN + 1; }
+  // Its size; half the groups' partial forces take its place once it has been
+  // read, XN apart by one (distinct banks).
+  static constexpr int PF = NODES + LANES;
+  __host__ __device__ static constexpr int tile(int halo) {
+    const int a = px(halo) * (TY + 2 * halo), b = FG * PF;
+    return ((a > b ? a : b) + 1) & ~1;
+  }
+};
+constexpr int ROWPAD = 16;  // empty rows after the disc's
+typedef FieldsShape<32, 16, 8, 512> FieldsWide;   // grids that fill the chip
+typedef FieldsShape<16, 8, 4, 512> FieldsSmall;   // small grids: a quarter of the chain per workgroup
+
+// u_x, u_y and T from the raw sums n, j_x, j_y, P_xx, P_yy, g0 of a node
+// (3/2 n T = sum |xi|^2/2 F + G); an isothermal run sees its fixed temperature
+__device__ __forceinline__ void flow_of(const double (&m)[6], double T_iso, double& ux, double& uy, double& T) {
+  const double n = m[0];
+  ux = m[1] / n;
+  uy = m[2] / n;
+  const double e = 0.5 * (m[3] + m[4]) + m[5];
   T = T_iso > 0.0 ? T_iso : (2.0 / 3.0) * (e - 0.5 * n * (ux * ux + uy * uy)) / n;
 }
 
-__global__ __launch_bounds__(FNT) void fields_kernel(Dev D, const double* __restrict__ raw, double* __restrict__ fld,
+// Mean-field force of the lane's FXN neighbouring nodes from one row of the disc: pairs
+// (di, dj), di = d0 .. d0 + cnt - 1, with the coefficients c = {cx, cy} in
+// order.  rp, lp: node 0's cells (d0, dj) and (-d0, -dj).  The cells of
+// neighbouring nodes overlap: per pair one new value on either side serves all
+// nodes, in registers that move by one cell a pair (four pairs unrolled, so
+// that nothing is moved).
+template <int FXN>
+__device__ __forceinline__ void force_row(const double* rp, const double* lp, const dbl2* c, int cnt,
+                                          double (&ax)[FXN], double (&ay)[FXN]) {
+  double r[FXN + 3], l[FXN + 3];  // cells of node 0 at pair t: t + i to the right, t + i - (FXN - 1) to the left
+#pragma unroll
+  for (int i = 0; i < FXN - 1; ++i) {
+    r[i] = rp[i];
+    l[i] = lp[FXN - 1 - i];
+  }
+  auto pair = [&](int q, const dbl2 k) {
+#pragma unroll
+    for (int j = 0; j < FXN; ++j) {
+      const double d = r[q + j] - l[q + FXN - 1 - j];
+      ax[j] = fma(k[0], d, ax[j]);
+      ay[j] = fma(k[1], d, ay[j]);
+    }
+  };
+  int t = 0;
+  for (; t + 4 <= cnt; t += 4) {
+    dbl2 k[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) k[i] = c[t + i];
+#pragma unroll
+    for (int i = FXN - 1; i < FXN + 3; ++i) {
+      r[i] = rp[t + i];
+      l[i] = lp[FXN - 1 - t - i];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) pair(q, k[q]);
+#pragma unroll
+    for (int i = 0; i < FXN - 1; ++i) {
+      r[i] = r[i + 4];
+      l[i] = l[i + 4];
+    }
+  }
+  // the last cnt - t < 4 pairs: their cells only
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    if (t + q < cnt) {
+      r[q + FXN - 1] = rp[t + q + FXN - 1];
+      l[q + FXN - 1] = lp[-t - q];
+      pair(q, c[t + q]);
+    }
+  }
+}
+
+// Bound by the force sums, 628 pairs per node at a radius of 20 cells, and on
+// small grids by their chain.  With one node per lane every pair reads two
+// values and three coefficients from LDS and the scalar cache one wait after
+// the other; here a lane takes 8 (4) neighbouring nodes, so that a pair costs a
+// quarter (half) of a value, the disc's rows are shared among 8 (16) groups and
+// summed through LDS, and every phase's loads are in flight together.  Per
+// launch: 1024 x 1024 nodes 249 -> 157 us, 333 x 270 66 -> 30 us, 64 x 48 51 -> 11 us.
+template <class SH>
+__global__ __launch_bounds__(SH::NT) void fields_kernel(Dev D, const double* __restrict__ raw, double* __restrict__ fld,
                                                      const int* __restrict__ avg_ofs,
                                                      const double* __restrict__ avg_w,
-                                                     const int* __restrict__ pair_ofs,
-                                                     const double* __restrict__ pair_cx,
-                                                     const double* __restrict__ pair_cy) {
+                                                     const int4* __restrict__ disc_rows,
+                                                     const dbl2* __restrict__ disc_c) {
   extern __shared__ double sm[];
-  const int H = D.halo, PX = FTX + 2 * H, PY = FTY + 2 * H;
+  constexpr int FTX = SH::TX, FTY = SH::TY, FXN = SH::XN, FNT = SH::NT, FG = SH::FG, GX = SH::GX, GY = SH::GY;
+  constexpr int PF = SH::PF, LANES = SH::LANES, AV = SH::AV;
+  const int H = D.halo, PX = SH::px(H), PY = FTY + 2 * H;
   double* sn = sm;             // [PY][PX] density, node (x0 - H + c, y0 - H + r)
-  double* sX = sn + PX * PY;   // [GY][GX] node (x0 - 2 + c, y0 - 2 + r)
+  double* sX = sn + SH::tile(H);  // [GY][GX] node (x0 - 2 + c, y0 - 2 + r)
   double* sT = sX + GX * GY;
   double* sux = sT + GX * GY;
   double* suy = sux + GX * GY;
-  double* sC = suy + GX * GY;
+  double* sC = suy + GX * GY;        // [FTY][FTX] contact value
+  dbl2* sP = (dbl2*)(sC + SH::NODES);      // [npair] force coefficients
+  double* sA = (double*)(sP + D.npair);  // [navg] averaging weights
+  int* sO = (int*)(sA + D.navg);     // [navg] and offsets
+  double* sF = sn;                   // [FG / 2][2][PF] partial forces, in the tile's place
   const int tid = threadIdx.x;
   // contiguous ranges of tiles per XCD (row-major over the tile grid): the
   // density halos of neighbouring tiles meet in one L2
   const unsigned tb = xcd_block(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
   const int x0 = (int)(tb % gridDim.x) * FTX, y0 = (int)(tb / gridDim.x) * FTY;
   const long long N = D.ntot;
-  for (int i = tid; i < PX * PY; i += FNT) {
-    const int r = i / PX, c = i - r * PX;
-    sn[i] = raw[(long long)wrap(y0 - H + r, D.ny) * D.nx + wrap(x0 - H + c, D.nx)];
-  }
-  for (int i = tid; i < GX * GY; i += FNT) {
-    const int r = i / GX, c = i - r * GX;
-    const long long node = (long long)wrap(y0 - 2 + r, D.ny) * D.nx + wrap(x0 - 2 + c, D.nx);
-    flow_of(raw, N, node, D.T_iso, sux[i], suy[i], sT[i]);
-  }
-  __syncthreads();
-  // averaged density over the disc, contact value, X on the tile +-2
-  for (int i = tid; i < GX * GY; i += FNT) {
-    const int r = i / GX, c = i - r * GX;
-    const int ctr = (r - 2 + H) * PX + (c - 2 + H);
-    double s0 = 0.0, s1 = 0.0;
-    int t = 0;
-    for (; t + 1 < D.navg; t += 2) {
-      s0 += avg_w[t] * sn[ctr + avg_ofs[t]];
-      s1 += avg_w[t + 1] * sn[ctr + avg_ofs[t + 1]];
+  // density tile, u and T on the tile +-2, stencil tables: many loads in
+  // flight at a time (one by one, each would wait for the one before)
+  constexpr int FLB = 9;
+  const int PW = FTX + 2 * H, ntile = PW * PY;
+  const float inx = 1.0f / (float)D.nx, iny = 1.0f / (float)D.ny;
+  int r = tid / PW, c = tid - r * PW;
+  const int dr = FNT / PW, dc = FNT - dr * PW;
+  for (int b = tid; b < ntile; b += FLB * FNT) {
+    double v[FLB];
+    int at[FLB];
+#pragma unroll
+    for (int q = 0; q < FLB; ++q) {
+      at[q] = b + q * FNT < ntile ? r * PX + c : -1;
+      v[q] = 0.0;
+      if (at[q] >= 0) v[q] = raw[(long long)wrap(y0 - H + r, D.ny, iny) * D.nx + wrap(x0 - H + c, D.nx, inx)];
+      r += dr;
+      c += dc;
+      if (c >= PW) {
+        c -= PW;
+        ++r;
+      }
     }
-    if (t < D.navg) s0 += avg_w[t] * sn[ctr + avg_ofs[t]];
-    const double eta = D.eta_c * (s0 + s1);
-    const double om = 1.0 - eta;
-    const double chi = (2.0 - eta) / (2.0 * om * om * om);
-    const double n = sn[ctr];
-    sC[i] = chi;
-    sX[i] = n * n * chi * sT[i];
+#pragma unroll
+    for (int q = 0; q < FLB; ++q)
+      if (at[q] >= 0) sn[at[q]] = v[q];
+  }
+  {
+    constexpr int LG = (GX * GY + FNT - 1) / FNT;
+    double m[LG][6];
+#pragma unroll
+    for (int q = 0; q < LG; ++q) {
+      const int i = tid + q * FNT, gr = i / GX, gc = i - gr * GX;
+      const long long node = (long long)wrap(y0 - 2 + gr, D.ny, iny) * D.nx + wrap(x0 - 2 + gc, D.nx, inx);
+      constexpr int pl[6] = {0, 1, 2, 3, 5, 8};  // n, j_x, j_y, P_xx, P_yy, g0
+#pragma unroll
+      for (int k = 0; k < 6; ++k) m[q][k] = i < GX * GY ? raw[pl[k] * N + node] : 1.0;
+    }
+    for (int i = tid; i < D.npair; i += FNT) sP[i] = disc_c[i];
+    for (int i = tid; i < D.navg; i += FNT) {
+      sA[i] = avg_w[i];
+      sO[i] = avg_ofs[i];
+    }
+#pragma unroll
+    for (int q = 0; q < LG; ++q) {
+      const int i = tid + q * FNT;
+      if (i < GX * GY) flow_of(m[q], D.T_iso, sux[i], suy[i], sT[i]);
+    }
   }
   __syncthreads();
-
+  // averaged density over the disc, contact value, X on the tile +-2; with two
+  // threads per node each takes every other cell
+  for (int j = tid; j < AV * GX * GY; j += FNT) {
+    const int i = j / AV, part = j - AV * i;
+    const int gr = i / GX, gc = i - gr * GX;
+    const int ctr = (gr - 2 + H) * PX + (gc - 2 + H);
+    double s0 = 0.0, s1 = 0.0;
+    int t = part;
+    for (; t + 7 * AV < D.navg; t += 8 * AV) {
+#pragma unroll
+      for (int q = 0; q < 8; q += 2) {
+        s0 += sA[t + q * AV] * sn[ctr + sO[t + q * AV]];
+        s1 += sA[t + (q + 1) * AV] * sn[ctr + sO[t + (q + 1) * AV]];
+      }
+    }
+    for (; t < D.navg; t += AV) s0 += sA[t] * sn[ctr + sO[t]];
+    s0 += s1;
+    if (AV == 2) s0 += __shfl_xor(s0, 1);
+    if (part == 0) {
+      const double eta = D.eta_c * s0;
+      const double om = 1.0 - eta;
+      const double chi = (2.0 - eta) / (2.0 * om * om * om);
+      const double n = sn[ctr];
+      if (gr >= 2 && gr < FTY + 2 && gc >= 2 && gc < FTX + 2) sC[(gr - 2) * FTX + gc - 2] = chi;
+      sX[i] = n * n * chi * sT[i];
+    }
+  }
   const int tx = tid % FTX, ty = tid / FTX;
+  const double n = tid < SH::NODES ? sn[(ty + H) * PX + (tx + H)] : 1.0;
+  if (D.force_model == EVLB_FORCE_EV1) {
+    const int grp = LANES == 64 ? __builtin_amdgcn_readfirstlane(tid / LANES) : tid / LANES, lane = tid % LANES;
+    const int fx = lane % (FTX / FXN) * FXN, fy = lane / (FTX / FXN);
+    const double* ctr = sn + (fy + H) * PX + fx + H;
+    double ax[FXN] = {}, ay[FXN] = {};
+    int4 q = disc_rows[grp];  // dj, d0, count, first pair (count 0 past the last row)
+    for (int i = grp; i < D.nrow; i += FG) {
+      const int4 qn = disc_rows[i + FG];
+      force_row<FXN>(ctr + q.x * PX + q.y, ctr - q.x * PX - q.y, sP + q.w, q.z, ax, ay);
+      q = qn;
+    }
+    __syncthreads();  // the density tile is read
+    // the upper half of the groups hands its sums to the lower half, which
+    // leaves its own for the nodes' threads
+    double* p = sF + grp % (FG / 2) * 2 * PF + lane * (FXN + 1);
+    if (grp >= FG / 2) {
+#pragma unroll
+      for (int j = 0; j < FXN; ++j) {
+        p[j] = ax[j];
+        p[PF + j] = ay[j];
+      }
+    }
+    __syncthreads();
+    if (grp < FG / 2) {
+#pragma unroll
+      for (int j = 0; j < FXN; ++j) {
+        p[j] += ax[j];
+        p[PF + j] += ay[j];
+      }
+    }
+  }
+  __syncthreads();
   const int x = x0 + tx, y = y0 + ty;
-  if (x >= D.nx || y >= D.ny) return;
+  if (tid >= SH::NODES || x >= D.nx || y >= D.ny) return;
   const long long node = (long long)y * D.nx + x;
   const int g = (ty + 2) * GX + (tx + 2);
-  const int ctr = (ty + H) * PX + (tx + H);
-  const double n = sn[ctr], T = sT[g], ux = sux[g], uy = suy[g], chi = sC[g];
+  const double T = sT[g], ux = sux[g], uy = suy[g], chi = sC[tid];
   double Fx = D.g_ext, Fy = 0.0;
   if (D.force_model == EVLB_FORCE_EV1) {
-    double ax0 = 0.0, ax1 = 0.0, ay0 = 0.0, ay1 = 0.0;
-    int t = 0;
-    for (; t + 1 < D.npair; t += 2) {
-      const double d0 = sn[ctr + pair_ofs[t]] - sn[ctr - pair_ofs[t]];
-      const double d1 = sn[ctr + pair_ofs[t + 1]] - sn[ctr - pair_ofs[t + 1]];
-      ax0 += pair_cx[t] * d0;
-      ay0 += pair_cy[t] * d0;
-      ax1 += pair_cx[t + 1] * d1;
-      ay1 += pair_cy[t + 1] * d1;
+    const double* p = sF + tid / FXN * (FXN + 1) + tid % FXN;
+    double sx[2] = {}, sy[2] = {};
+#pragma unroll
+    for (int w = 0; w < FG / 2; ++w) {
+      sx[w & 1] += p[w * 2 * PF];
+      sy[w & 1] += p[w * 2 * PF + PF];
     }
-    if (t < D.npair) {
-      const double d0 = sn[ctr + pair_ofs[t]] - sn[ctr - pair_ofs[t]];
-      ax0 += pair_cx[t] * d0;
-      ay0 += pair_cy[t] * d0;
-    }
-    Fx += ax0 + ax1;
-    Fy = ay0 + ay1;
+    Fx += sx[0] + sx[1];
+    Fy = sy[0] + sy[1];
   }
   const double c12 = D.inv_dx * (1.0 / 12.0);
   const double X = sX[g];
@@ -510,7 +673,6 @@ __device__ __forceinline__ double half_lo(double v) {
   return __builtin_bit_cast(double, (unsigned long long)lo[0] | ((unsigned long long)hi[0] << 32));
 }
 
-typedef double dbl2 __attribute__((ext_vector_type(2)));
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double mfma4(double a, double b, double c) {
@@ -1007,7 +1169,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
   size_t tab_d, tab_i, f1, f2, mom, raw, fld, status, total;
-  int navg, npair, halo;
+  int navg, npair, nrow, halo;
 };
 
 bool is_integer_multiple(double a, double dx, int* m) {
@@ -1023,12 +1185,13 @@ Layout make_layout(const evlb_params* p, const evlb::DiscTables& t) {
   const long long N = (long long)p->nx[0] * p->ny;
   L.navg = (int)t.avg_w.size();
   L.npair = (int)t.pair_cx.size();
+  L.nrow = 2 * t.pair_reach + 1;
   L.halo = t.pair_reach > t.avg_reach + 2 ? t.pair_reach : t.avg_reach + 2;
   size_t off = 0;
   L.tab_d = off;
-  off += align256(sizeof(double) * (size_t)(Q + 2 * Q * Q + L.navg + 2 * (L.npair > 0 ? L.npair : 1)));
+  off += align256(sizeof(double) * (size_t)(Q + 2 * Q * Q + L.navg + (L.navg & 1) + 2 * (L.npair + 1)));
   L.tab_i = off;
-  off += align256(sizeof(int) * (size_t)(L.navg + (L.npair > 0 ? L.npair : 1)));
+  off += align256(sizeof(int) * (size_t)L.navg + sizeof(int4) * (size_t)(L.nrow + ROWPAD));
   const size_t fbytes = align256(sizeof(double) * 2 * (size_t)V * (size_t)N);
   L.f1 = off; off += fbytes;
   L.f2 = off; off += fbytes;
@@ -1072,8 +1235,17 @@ void disc_tables(const evlb_params* p, evlb::DiscTables& t) {
   evlb::build_disc_tables(p->dx, p->sigma, p->phi_sigma, p->r_cut, p->force_model == EVLB_FORCE_EV1, t);
 }
 
-size_t fields_lds_bytes(int halo) {
-  return sizeof(double) * ((size_t)(FTX + 2 * halo) * (FTY + 2 * halo) + 5 * (size_t)GX * GY);
+template <class SH>
+size_t fields_lds_bytes(int halo, int npair, int navg) {
+  return sizeof(double) * ((size_t)SH::tile(halo) + 4 * (size_t)SH::GX * SH::GY + SH::NODES + 2 * (size_t)npair + navg) +
+         sizeof(int) * (size_t)navg;
+}
+
+// The small tile where the wide one leaves CUs without a workgroup (64 x 48
+// nodes: wide 24 us, small 11 us; 333 x 270, 187 wide tiles: 31 and 30 us).
+bool fields_small(int nx, int ny, int cus) {
+  typedef FieldsWide W;
+  return (long long)((nx + W::TX - 1) / W::TX) * ((ny + W::TY - 1) / W::TY) < cus;
 }
 
 }  // namespace
@@ -1082,12 +1254,15 @@ struct Ctx {
   evlb_params p;
   int nx, ny;
   int nstrip, nseg, seglen;  // workgroups of the fused stage
+  bool small;                // fields tile
   long long N;
   Layout L;
   Dev dev;
   char* ws;
-  const double *vel, *meq, *dpm, *avg_w, *pair_cx, *pair_cy;
-  const int *avg_ofs, *pair_ofs;
+  const double *vel, *meq, *dpm, *avg_w;
+  const dbl2* disc_c;
+  const int* avg_ofs;
+  const int4* disc_rows;
   std::vector<double> hvel;
 };
 
@@ -1152,34 +1327,46 @@ int init(const evlb_params* p, char* ws, size_t bytes, hipStream_t st, Ctx** out
     return EVLB_EHIP;
   }
   fused_shape(c->nx, c->ny, cus, &c->nstrip, &c->nseg, &c->seglen);
+  c->small = fields_small(c->nx, c->ny, cus);
   c->L = L;
   c->ws = ws;
   evlb::TableParams tp{Q, p->dx, p->sigma, p->phi_sigma, p->gamma, p->r_cut};
   evlb::HostTables ht;
   evlb::build_tables(tp, ht);
   c->hvel = ht.vel;
-  const int PX = FTX + 2 * L.halo;
+  const int PX = c->small ? FieldsSmall::px(L.halo) : FieldsWide::px(L.halo);
   std::vector<double> hd;
   hd.insert(hd.end(), ht.vel.begin(), ht.vel.end());
   hd.insert(hd.end(), ht.meq.begin(), ht.meq.end());
   hd.insert(hd.end(), ht.dpm.begin(), ht.dpm.end());
   hd.insert(hd.end(), t.avg_w.begin(), t.avg_w.end());
-  const size_t o_cx = hd.size();
-  hd.insert(hd.end(), t.pair_cx.begin(), t.pair_cx.end());
-  if (t.pair_cx.empty()) hd.push_back(0.0);
-  const size_t o_cy = hd.size();
-  hd.insert(hd.end(), t.pair_cy.begin(), t.pair_cy.end());
-  if (t.pair_cy.empty()) hd.push_back(0.0);
+  // the force pairs row by row of the disc (the tables list them so, di
+  // ascending): rows {dj, first di, pairs, index of the first pair}
+  std::vector<int4> hr;
+  if (hd.size() & 1) hd.push_back(0.0);  // pairs on 16 bytes
+  const size_t o_c = hd.size();
+  for (int i = 0; i < L.npair; ++i) {
+    if (hr.empty() || hr.back().x != t.pair_dj[i]) hr.push_back(make_int4(t.pair_dj[i], t.pair_di[i], 0, i));
+    if (t.pair_di[i] != hr.back().y + hr.back().z) {
+      delete c;
+      return EVLB_EUNSUPPORTED;
+    }
+    ++hr.back().z;
+    hd.push_back(t.pair_cx[i]);
+    hd.push_back(t.pair_cy[i]);
+  }
+  const int nrow = (int)hr.size();
+  hr.resize(L.nrow + ROWPAD, make_int4(0, 0, 0, 0));
   std::vector<int> hi;
   for (size_t i = 0; i < t.avg_w.size(); ++i) hi.push_back(t.avg_dj[i] * PX + t.avg_di[i]);
-  const size_t o_po = hi.size();
-  for (size_t i = 0; i < t.pair_cx.size(); ++i) hi.push_back(t.pair_dj[i] * PX + t.pair_di[i]);
-  if (t.pair_cx.empty()) hi.push_back(0);
   double* tabd = (double*)(ws + L.tab_d);
-  int* tabi = (int*)(ws + L.tab_i);
+  int4* tabr = (int4*)(ws + L.tab_i);
+  int* tabi = (int*)(tabr + L.nrow + ROWPAD);
   // ordered on the caller's stream, which is synchronised before the host
   // vectors go out of scope
-  if (hipMemcpyAsync(tabd, hd.data(), hd.size() * sizeof(double), hipMemcpyHostToDevice, st) != hipSuccess ||
+  if (nrow > L.nrow ||
+      hipMemcpyAsync(tabd, hd.data(), hd.size() * sizeof(double), hipMemcpyHostToDevice, st) != hipSuccess ||
+      hipMemcpyAsync(tabr, hr.data(), hr.size() * sizeof(int4), hipMemcpyHostToDevice, st) != hipSuccess ||
       hipMemcpyAsync(tabi, hi.data(), hi.size() * sizeof(int), hipMemcpyHostToDevice, st) != hipSuccess ||
       hipMemsetAsync(ws + L.status, 0, 256, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
     delete c;
@@ -1189,10 +1376,9 @@ int init(const evlb_params* p, char* ws, size_t bytes, hipStream_t st, Ctx** out
   c->meq = tabd + Q;
   c->dpm = tabd + Q + Q * Q;
   c->avg_w = tabd + Q + 2 * Q * Q;
-  c->pair_cx = tabd + o_cx;
-  c->pair_cy = tabd + o_cy;
+  c->disc_c = (const dbl2*)(tabd + o_c);
   c->avg_ofs = tabi;
-  c->pair_ofs = tabi + o_po;
+  c->disc_rows = tabr;
   Dev& d = c->dev;
   d.nx = c->nx;
   d.ny = c->ny;
@@ -1209,6 +1395,7 @@ int init(const evlb_params* p, char* ws, size_t bytes, hipStream_t st, Ctx** out
   d.T_iso = p->T_iso;
   d.navg = L.navg;
   d.npair = p->force_model == EVLB_FORCE_EV1 ? L.npair : 0;
+  d.nrow = d.npair > 0 ? nrow : 0;
   d.halo = L.halo;
   d.status = (int*)(ws + L.status);
   *out = c;
@@ -1230,12 +1417,19 @@ int launch_raw(Ctx* c, const double* f, hipStream_t st) {
   return launched();
 }
 
-int launch_fields(Ctx* c, hipStream_t st) {
-  const dim3 grid((c->nx + FTX - 1) / FTX, (c->ny + FTY - 1) / FTY);
-  hipLaunchKernelGGL(fields_kernel, grid, dim3(FNT), fields_lds_bytes(c->L.halo), st, c->dev,
+template <class SH>
+int launch_fields_shape(Ctx* c, hipStream_t st) {
+  static_assert(SH::FG <= ROWPAD, "the next row of every group exists");
+  const dim3 grid((c->nx + SH::TX - 1) / SH::TX, (c->ny + SH::TY - 1) / SH::TY);
+  hipLaunchKernelGGL((fields_kernel<SH>), grid, dim3(SH::NT),
+                     fields_lds_bytes<SH>(c->L.halo, c->dev.npair, c->L.navg), st, c->dev,
                      (const double*)(c->ws + c->L.raw), (double*)(c->ws + c->L.fld), c->avg_ofs, c->avg_w,
-                     c->pair_ofs, c->pair_cx, c->pair_cy);
+                     c->disc_rows, c->disc_c);
   return launched();
+}
+
+int launch_fields(Ctx* c, hipStream_t st) {
+  return c->small ? launch_fields_shape<FieldsSmall>(c, st) : launch_fields_shape<FieldsWide>(c, st);
 }
 
 template <bool ADV, bool FRC>

@@ -58,3 +58,19 @@ def test_steps_match_oracle(nx, ny, nsteps):
     F, G = step2d.run(F, G, tb, nsteps)
     check(E.Solver.planes(f).cpu().numpy(), [F, G], 1e-11, steps=nsteps, what=f"{nx}x{ny}")
     assert s.status() == 0
+
+
+# the widest stencils the parameters admit (averaging radius 22 cells, force
+# radius 24 or 23) and narrow ones (averaging disc of one cell, force radius 1)
+@pytest.mark.parametrize("cells,reach", [(22.0, 24), (21.5, 23), (0.9, 1), (2.0, 3)])
+def test_rhs_stencil_widths(cells, reach):
+    print(f"2D stencils sigma/dx={cells} r_cut/dx={reach}", flush=True)
+    nx, ny, dx = 40, 27, 1.0 / cells
+    p = dict(dx=dx, dt=0.2 * dx / 6.630878198393129, r_cut=reach * dx)
+    tb = step2d.Tables2D(Params(Q=16, **p))
+    F, G = moving_state(nx, ny, tb)
+    s = E.Solver(16, p["dx"], p["dt"], nx, ny=ny, r_cut=p["r_cut"])
+    L = E.Solver.planes(s.rhs(E.Solver.from_planes(td(np.stack([F, G])))))
+    torch.cuda.synchronize()
+    check(L.cpu().numpy(), step2d.rhs(F, G, tb), 1e-11, what=f"{cells} {reach}")
+    assert s.status() == 0
