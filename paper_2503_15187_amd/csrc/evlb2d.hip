@@ -83,136 +83,202 @@ struct Raw {
   double n, jx, jy, pxx, pxy, pyy, rx, ry, g0, hx, hy;
 };
 
-__device__ __forceinline__ void finish_moments(const Raw& m, double* out6, long long N, long long node,
-                                               int* status, double T_iso) {
-  const double n = m.n;
-  const double ux = m.jx / n, uy = m.jy / n;
-  const double u2 = ux * ux + uy * uy;
+struct Moments {
+  double n, ux, uy, T, qx, qy;
+};
+
+__device__ __forceinline__ Moments finish_moments(const Raw& m, int* status, double T_iso) {
+  Moments o;
+  o.n = m.n;
+  o.ux = m.jx / o.n;
+  o.uy = m.jy / o.n;
+  const double u2 = o.ux * o.ux + o.uy * o.uy;
   const double tr = m.pxx + m.pyy;
-  const double T = (2.0 / 3.0) * (0.5 * tr + m.g0 - 0.5 * n * u2) / n;
-  const double qx = 0.5 * (m.rx - 2.0 * (ux * m.pxx + uy * m.pxy) - ux * tr + 2.0 * n * ux * u2) + (m.hx - ux * m.g0);
-  const double qy = 0.5 * (m.ry - 2.0 * (ux * m.pxy + uy * m.pyy) - uy * tr + 2.0 * n * uy * u2) + (m.hy - uy * m.g0);
-  out6[node] = n;
-  out6[N + node] = ux;
-  out6[2 * N + node] = uy;
-  out6[3 * N + node] = T_iso > 0.0 ? T_iso : T;
-  out6[4 * N + node] = qx;
-  out6[5 * N + node] = qy;
-  if (!(n > 0.0) || !(T > 0.0) || !isfinite(n) || !isfinite(T) || !isfinite(ux) || !isfinite(uy) ||
-      !isfinite(qx) || !isfinite(qy))
+  const double T = (2.0 / 3.0) * (0.5 * tr + m.g0 - 0.5 * o.n * u2) / o.n;
+  o.qx = 0.5 * (m.rx - 2.0 * (o.ux * m.pxx + o.uy * m.pxy) - o.ux * tr + 2.0 * o.n * o.ux * u2) + (m.hx - o.ux * m.g0);
+  o.qy = 0.5 * (m.ry - 2.0 * (o.ux * m.pxy + o.uy * m.pyy) - o.uy * tr + 2.0 * o.n * o.uy * u2) + (m.hy - o.uy * m.g0);
+  o.T = T_iso > 0.0 ? T_iso : T;
+  if (!(o.n > 0.0) || !(T > 0.0) || !isfinite(o.n) || !isfinite(T) || !isfinite(o.ux) || !isfinite(o.uy) ||
+      !isfinite(o.qx) || !isfinite(o.qy))
     status[0] = 1;
+  return o;
 }
 
-// ---------------------------------------------------------------------------
-// moments of a state (first stage of a step, evlb_moments).  State layout:
-// distribution d, node i, velocity (k, l) at ((d ntot + i) V + Q k + l): the
-// 2 KiB of a node's distribution are contiguous, so one wavefront reads a
-// node with lane L taking the velocities L + 64 m.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
+typedef double dbl2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ Raw velocity_sums(const Dev& D, const double* __restrict__ f,
-                                             const double* __restrict__ vel, long long node, int lane) {
-  const double* F = f + node * V;
-  const double* G = f + (D.ntot + node) * V;
-  double a[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  const double pl = vel[lane & 15];
+// ---------------------------------------------------------------------------
+// raw velocity sums of a state (first stage of a step, evlb_moments).  State
+// layout: distribution d, node i, velocity (k, l) at ((d ntot + i) V + Q k + l):
+// the 2 KiB of a node's distribution are contiguous.  Eight lanes a node, lane
+// q the velocities l = 2 q, 2 q + 1 of every k as 16-byte loads (a wavefront's
+// load covers eight whole lines): per l the moments over k, sum_k p_k^m F for
+// m < 4 and sum_k p_k^m G for m < 2, which the powers of p_l then weigh, and
+// three exchanges among the eight lanes.  Bound by the read of the state; one
+// wavefront a node with 66 shuffles took 1.40 ms at 1024 x 1024 nodes, this
+// 0.90 ms (moments 1.43 and four copies, 0.82 ms: 5.3 TB/s).
+// ---------------------------------------------------------------------------
+constexpr int MNODES = 32;  // nodes per workgroup of 256 threads
+
+// sum over the eight lanes 8 i .. 8 i + 7 (every lane gets it): DPP quad_perm
+// xor 1 and 2, then row_half_mirror
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
+  return v + __builtin_bit_cast(double, (unsigned long long)(unsigned)lo | ((unsigned long long)(unsigned)hi << 32));
+}
+__device__ __forceinline__ double sum8(double v) { return dpp_add<0x141>(dpp_add<0x4e>(dpp_add<0xb1>(v))); }
+
+// raw sums [11][MNODES] of the workgroup's nodes into LDS (nodes past the
+// domain repeat the last one)
+__device__ __forceinline__ void velocity_sums(const Dev& D, const double* __restrict__ f,
+                                              const double* __restrict__ vel, double (*S)[MNODES]) {
+  const int slot = threadIdx.x >> 3, q = threadIdx.x & 7;
+  const long long node = min((long long)blockIdx.x * MNODES + slot, D.ntot - 1);
+  const dbl2* F = (const dbl2*)(f + node * V) + q;
+  const dbl2* G = (const dbl2*)(f + (D.ntot + node) * V) + q;
+  dbl2 Fv[Q], Gv[Q];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const int v = lane + 64 * m;
-    const double pk = vel[v >> 4];
-    const double Fv = F[v], Gv = G[v];
-    const double p2 = pk * pk + pl * pl;
-    a[0] += Fv;
-    a[1] += pk * Fv;
-    a[2] += pl * Fv;
-    a[3] += pk * pk * Fv;
-    a[4] += pk * pl * Fv;
-    a[5] += pl * pl * Fv;
-    a[6] += pk * p2 * Fv;
-    a[7] += pl * p2 * Fv;
-    a[8] += Gv;
-    a[9] += pk * Gv;
-    a[10] += pl * Gv;
+  for (int k = 0; k < Q; ++k) Fv[k] = F[k * (Q / 2)];
+#pragma unroll
+  for (int k = 0; k < Q; ++k) Gv[k] = G[k * (Q / 2)];
+  double a[11] = {};
+  dbl2 s0 = {}, s1 = {}, s2 = {}, s3 = {}, t0 = {}, t1 = {};
+#pragma unroll
+  for (int k = 0; k < Q; ++k) {
+    const double p = vel[k], p2 = p * p, p3 = p2 * p;
+    s0 += Fv[k];
+    s1 += p * Fv[k];
+    s2 += p2 * Fv[k];
+    s3 += p3 * Fv[k];
+    t0 += Gv[k];
+    t1 += p * Gv[k];
   }
 #pragma unroll
-  for (int i = 0; i < 11; ++i) a[i] = wave_sum(a[i]);
-  return Raw{a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10]};
+  for (int j = 0; j < 2; ++j) {
+    const double p = vel[2 * q + j], p2 = p * p;
+    a[0] += s0[j];
+    a[1] += s1[j];
+    a[2] += p * s0[j];
+    a[3] += s2[j];
+    a[4] += p * s1[j];
+    a[5] += p2 * s0[j];
+    a[6] += s3[j] + p2 * s1[j];
+    a[7] += p * s2[j] + p2 * p * s0[j];
+    a[8] += t0[j];
+    a[9] += t1[j];
+    a[10] += p * t0[j];
+  }
+#pragma unroll
+  for (int i = 0; i < 11; ++i) {
+    a[i] = sum8(a[i]);
+    if (q == (i & 7)) S[i][slot] = a[i];
+  }
+  __syncthreads();
 }
 
-// n, u, T, q of a state (evlb_moments): T is the moment temperature; one
-// wavefront per node
-__global__ __launch_bounds__(256) void moments_kernel(Dev D, const double* __restrict__ f, double* __restrict__ out6,
-                                                      const double* __restrict__ vel) {
-  const long long node = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (node >= D.ntot) return;
-  const Raw m = velocity_sums(D, f, vel, node, threadIdx.x & 63);
-  if ((threadIdx.x & 63) == 0) finish_moments(m, out6, D.ntot, node, D.status, 0.0);
+// n, u, T, q of a state (evlb_moments): T is the moment temperature
+__global__ __launch_bounds__(256) void moments_kernel(Dev D, const double* __restrict__ f, double* __restrict__ n,
+                                                      double* __restrict__ u, double* __restrict__ T,
+                                                      double* __restrict__ q, const double* __restrict__ vel) {
+  __shared__ double S[11][MNODES];
+  velocity_sums(D, f, vel, S);
+  const int t = threadIdx.x;
+  const long long node = (long long)blockIdx.x * MNODES + t, N = D.ntot;
+  if (t >= MNODES || node >= N) return;
+  const Raw m{S[0][t], S[1][t], S[2][t], S[3][t], S[4][t], S[5][t], S[6][t], S[7][t], S[8][t], S[9][t], S[10][t]};
+  const Moments o = finish_moments(m, D.status, 0.0);
+  n[node] = o.n;
+  u[node] = o.ux;
+  u[N + node] = o.uy;
+  T[node] = o.T;
+  if (q) {
+    q[node] = o.qx;
+    q[N + node] = o.qy;
+  }
 }
 
 // raw velocity sums [11][ntot] of a state, the input of a stage's fields
 __global__ __launch_bounds__(256) void raw_sums_kernel(Dev D, const double* __restrict__ f, double* __restrict__ raw,
                                                        const double* __restrict__ vel) {
-  const long long node = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (node >= D.ntot) return;
-  const Raw m = velocity_sums(D, f, vel, node, threadIdx.x & 63);
-  const long long N = D.ntot;
-  const double v[11] = {m.n, m.jx, m.jy, m.pxx, m.pxy, m.pyy, m.rx, m.ry, m.g0, m.hx, m.hy};
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int i = 0; i < 11; ++i)
-    if (lane == i) raw[i * N + node] = v[i];
+  __shared__ double S[11][MNODES];
+  velocity_sums(D, f, vel, S);
+  for (int i = threadIdx.x; i < 11 * MNODES; i += 256) {
+    const long long node = (long long)blockIdx.x * MNODES + i % MNODES;
+    if (node < D.ntot) raw[i / MNODES * D.ntot + node] = S[i / MNODES][i % MNODES];
+  }
 }
 
-// Hermite equilibrium of one velocity component at unit density:
-// a_0 = 1, a_1 = u, a_{m+1} = u a_m + m (T - 1) a_{m-1};  e_k = sum_m meq[k][m] a_m.
-__device__ __forceinline__ void hermite_coeffs(double u, double T, double* a) {
-  a[0] = 1.0;
-  a[1] = u;
-#pragma unroll
-  for (int m = 1; m < Q - 1; ++m) a[m + 1] = u * a[m] + (double)m * (T - 1.0) * a[m - 1];
-}
+// Reduced Maxwellian of given fields.  A workgroup takes ENODES nodes: the
+// Hermite coefficients of one velocity component at unit density, a_0 = 1,
+// a_1 = u, a_{m+1} = u a_m + m (T - 1) a_{m-1}, once per (node, axis); the
+// expansions e_k = sum_m meq[k][m] a_m once per (node, axis, k); then the
+// products, as 16-byte stores over the nodes' contiguous 2 KiB.  Bound by the
+// write of the state; with all 64 lanes of a node's wavefront forming the
+// coefficients and their own expansions it took 2.07 ms at 1024 x 1024 nodes,
+// this 0.80 ms (5.4 TB/s).
+constexpr int ENODES = 16;
 
-// one wavefront per node: lane L writes the velocities L + 64 m, i.e. the
-// rows k = L / 16 + 4 m of column l = L % 16
 __global__ __launch_bounds__(256) void equilibrium_kernel(Dev D, const double* __restrict__ n_in,
                                                           const double* __restrict__ u_in,
                                                           const double* __restrict__ T_in, double* __restrict__ f,
                                                           const double* __restrict__ meq) {
-  const long long node = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (node >= D.ntot) return;
-  const int lane = threadIdx.x & 63, l = lane & 15;
-  const long long N = D.ntot;
-  const double n = n_in[node], ux = u_in[node], uy = u_in[N + node], T = T_in[node];
-  double ax[Q], ay[Q];
-  hermite_coeffs(ux, T, ax);
-  hermite_coeffs(uy, T, ay);
-  double ey = 0.0;
+  __shared__ double sa[Q][2 * ENODES];            // a_m of column (axis, node)
+  __shared__ __align__(16) double se[2][ENODES][Q];  // n e_k(u_x), e_l(u_y)
+  __shared__ double sT[ENODES];
+  const int t = threadIdx.x;
+  const long long N = D.ntot, i0 = (long long)blockIdx.x * ENODES;
+  // meq row of this thread's expansions, fetched beside the fields
+  const int k = t & 15, col = t >> 4;  // column col (x) and ENODES + col (y)
+  double mrow[Q];
 #pragma unroll
-  for (int m = 0; m < Q; ++m) ey += meq[l * Q + m] * ay[m];
-  double* F = f + node * V;
-  double* G = f + (N + node) * V;
+  for (int m = 0; m < Q; ++m) mrow[m] = meq[k * Q + m];
+  const long long inode = min(i0 + col, N - 1);
+  const double n = n_in[inode];
+  if (t < 2 * ENODES) {
+    const long long node = min(i0 + (t & (ENODES - 1)), N - 1);
+    const double u = u_in[t < ENODES ? node : N + node], T = T_in[node];
+    double a0 = 1.0, a1 = u;
+    sa[0][t] = a0;
+    sa[1][t] = a1;
 #pragma unroll
-  for (int mm = 0; mm < 4; ++mm) {
-    const int k = (lane >> 4) + 4 * mm;
-    double ex = 0.0;
+    for (int m = 1; m < Q - 1; ++m) {
+      const double an = u * a1 + (double)m * (T - 1.0) * a0;
+      a0 = a1;
+      a1 = an;
+      sa[m + 1][t] = an;
+    }
+    if (t < ENODES) sT[t] = T;
+  }
+  __syncthreads();
+  double ex = 0.0, ey = 0.0;
 #pragma unroll
-    for (int m = 0; m < Q; ++m) ex += meq[k * Q + m] * ax[m];
-    const double E = n * ex * ey;
-    F[lane + 64 * mm] = E;
-    G[lane + 64 * mm] = 0.5 * T * E;
+  for (int m = 0; m < Q; ++m) {
+    ex += mrow[m] * sa[m][col];
+    ey += mrow[m] * sa[m][ENODES + col];
+  }
+  se[0][col][k] = n * ex;
+  se[1][col][k] = ey;
+  __syncthreads();
+  // thread (h, kk, lp): velocities (kk, 2 lp), (kk, 2 lp + 1) of nodes h, h + 2, ..
+  const int lp = t & 7, kk = (t >> 3) & 15, h = t >> 7;
+#pragma unroll
+  for (int i = 0; i < ENODES; i += 2) {
+    const long long node = i0 + i + h;
+    if (node >= N) break;
+    const double e = se[0][i + h][kk];
+    const dbl2 y = *(const dbl2*)&se[1][i + h][2 * lp];
+    const dbl2 E = {e * y[0], e * y[1]};
+    const double g = 0.5 * sT[i + h];
+    *(dbl2*)(f + node * V + Q * kk + 2 * lp) = E;
+    *(dbl2*)(f + (N + node) * V + Q * kk + 2 * lp) = dbl2{g * E[0], g * E[1]};
   }
 }
 
 // ---------------------------------------------------------------------------
 // node fields
 // ---------------------------------------------------------------------------
-typedef double dbl2 __attribute__((ext_vector_type(2)));
-
 // Tile of a workgroup: TX x TY nodes, NT threads.  The force sums give a lane
 // XN nodes along x and each group of TX TY / XN lanes a share of the disc's
 // rows; the averaged density takes AV threads per node.
@@ -495,9 +561,8 @@ __global__ __launch_bounds__(SH::NT) void fields_kernel(Dev D, const double* __r
   m.g0 = raw[8 * N + node];
   m.hx = raw[9 * N + node];
   m.hy = raw[10 * N + node];
-  double q6[6];
-  finish_moments(m, q6, 1, 0, D.status, D.T_iso);
-  const double vals[NF] = {n, ux, uy, T, s * q6[4], s * q6[5], nu, -bn * chi, Fx, Fy,
+  const Moments o = finish_moments(m, D.status, D.T_iso);
+  const double vals[NF] = {n, ux, uy, T, s * o.qx, s * o.qy, nu, -bn * chi, Fx, Fy,
                            Ax, Ay, Bx, By, Uxx, Uxy, Uyx, Uyy};
 #pragma unroll
   for (int i = 0; i < NF; ++i) fld[i * N + node] = vals[i];
@@ -1168,7 +1233,7 @@ __global__ __launch_bounds__(SNT) void fused_kernel(Dev D, FusedArgs A, const do
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-  size_t tab_d, tab_i, f1, f2, mom, raw, fld, status, total;
+  size_t tab_d, tab_i, f1, f2, raw, fld, status, total;
   int navg, npair, nrow, halo;
 };
 
@@ -1195,7 +1260,6 @@ Layout make_layout(const evlb_params* p, const evlb::DiscTables& t) {
   const size_t fbytes = align256(sizeof(double) * 2 * (size_t)V * (size_t)N);
   L.f1 = off; off += fbytes;
   L.f2 = off; off += fbytes;
-  L.mom = off; off += align256(sizeof(double) * 6 * (size_t)N);
   L.raw = off; off += align256(sizeof(double) * NRAW * (size_t)N);
   L.fld = off; off += align256(sizeof(double) * NF * (size_t)N);
   L.status = off; off += 256;
@@ -1412,7 +1476,7 @@ namespace {
 int launched() { return hipGetLastError() == hipSuccess ? EVLB_OK : EVLB_EHIP; }
 
 int launch_raw(Ctx* c, const double* f, hipStream_t st) {
-  const unsigned nb = (unsigned)((c->N + 3) / 4);  // one wavefront per node
+  const unsigned nb = (unsigned)((c->N + MNODES - 1) / MNODES);
   hipLaunchKernelGGL(raw_sums_kernel, dim3(nb), dim3(256), 0, st, c->dev, f, (double*)(c->ws + c->L.raw), c->vel);
   return launched();
 }
@@ -1465,7 +1529,7 @@ int stage(Ctx* c, const double* fs, const double* f0, double* out, double a, dou
 }  // namespace
 
 int set_equilibrium(Ctx* c, const double* n, const double* u, const double* T, double* f, hipStream_t st) {
-  const unsigned nb = (unsigned)((c->N + 3) / 4);  // one wavefront per node
+  const unsigned nb = (unsigned)((c->N + ENODES - 1) / ENODES);
   hipLaunchKernelGGL(equilibrium_kernel, dim3(nb), dim3(256), 0, st, c->dev, n, u, T, f, c->meq);
   return launched();
 }
@@ -1496,17 +1560,9 @@ int rhs(Ctx* c, const double* f, double* L, hipStream_t st) {
 }
 
 int moments(Ctx* c, const double* f, double* n, double* u, double* T, double* q, hipStream_t st) {
-  double* m = (double*)(c->ws + c->L.mom);
-  const unsigned nb = (unsigned)((c->N + 3) / 4);  // one wavefront per node
-  hipLaunchKernelGGL(moments_kernel, dim3(nb), dim3(256), 0, st, c->dev, f, m, c->vel);
-  if (launched()) return EVLB_EHIP;
-  const size_t bytes = sizeof(double) * (size_t)c->N;
-  if (hipMemcpyAsync(n, m, bytes, hipMemcpyDeviceToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(u, m + c->N, 2 * bytes, hipMemcpyDeviceToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(T, m + 3 * c->N, bytes, hipMemcpyDeviceToDevice, st) != hipSuccess)
-    return EVLB_EHIP;
-  if (q && hipMemcpyAsync(q, m + 4 * c->N, 2 * bytes, hipMemcpyDeviceToDevice, st) != hipSuccess) return EVLB_EHIP;
-  return EVLB_OK;
+  const unsigned nb = (unsigned)((c->N + MNODES - 1) / MNODES);
+  hipLaunchKernelGGL(moments_kernel, dim3(nb), dim3(256), 0, st, c->dev, f, n, u, T, q, c->vel);
+  return launched();
 }
 
 }  // namespace evlb2d

@@ -74,3 +74,31 @@ def test_rhs_stencil_widths(cells, reach):
     torch.cuda.synchronize()
     check(L.cpu().numpy(), step2d.rhs(F, G, tb), 1e-11, what=f"{cells} {reach}")
     assert s.status() == 0
+
+
+# node counts around the 16 and 32 nodes a workgroup takes, and one past both
+@pytest.mark.parametrize("nx,ny", [(8, 8), (9, 11), (33, 31), (8, 9)])
+@pytest.mark.parametrize("heat", [True, False])
+def test_equilibrium_and_moments_match_oracle(nx, ny, heat):
+    print(f"2D observe nx={nx} ny={ny} heat={heat}", flush=True)
+    c = workloads.constants()["phase_separation_2d"]
+    tb = step2d.Tables2D(Params(Q=16, dx=c["dx"], dt=c["dt"]))
+    rng = np.random.default_rng(nx * ny)
+    n, T = (b * (1 + 0.1 * rng.standard_normal((ny, nx))) for b in (0.3, 0.6))
+    u = 0.1 * rng.standard_normal((2, ny, nx))
+    s = E.Solver(16, c["dx"], c["dt"], nx, ny=ny)
+    f = s.equilibrium(td(n), td(u), td(T))
+    ref = step2d.initial_state(n, u[0], u[1], T, tb)
+    check(E.Solver.planes(f).cpu().numpy(), ref, 1e-11, what="equilibrium")
+    F, G = moving_state(nx, ny, tb)
+    g = E.Solver.from_planes(td(np.stack([F, G])))
+    m = np.stack(step2d.moments(F, G, tb)).reshape(6, -1)
+    out = torch.full((6, nx * ny), 7.0, dtype=torch.float64, device="cuda")
+    E.evlb_moments(s.ctx, g, out[0], out[1:3], out[3], out[4:6] if heat else None)
+    got = out.cpu().numpy()
+    # sums of 512 terms with weights up to 6.7^3: a few hundred roundings of the largest moment
+    assert np.max(np.abs(got[:4] - m[:4])) < 1e-12
+    if heat:
+        assert np.max(np.abs(got[4:] - m[4:])) < 1e-12
+    else:
+        assert np.all(got[4:] == 7.0)
