@@ -19,13 +19,15 @@
 // row load and store of a wavefront is one contiguous 512-byte segment.
 //
 // Tile shapes: wide tiles (64 nodes, groups of velocities per wavefront,
-// tables through the scalar cache), narrow tiles (16 nodes, one update per
-// thread, the velocity-space contractions on the f64 MFMA) for grids too
-// small to fill the chip, and column tiles (one wavefront of 63 nodes, a
-// node's whole velocity column in registers) for large grids.
+// tables through the scalar cache), narrow and broad tiles (16 and 32 nodes, a
+// mirror pair of velocities per lane, the velocity-space contractions on the
+// f64 MFMA) for grids too small to fill the chip, and column tiles (one
+// wavefront of 63 nodes, a node's whole velocity column in registers) for
+// large grids.
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -49,9 +51,14 @@ constexpr int NFIELD = 10;
 
 enum { NF_N, NF_U, NF_T, NF_NU, NF_S, NF_PRE, NF_A, NF_B, NF_U1, NF_FX };
 
+// Averaging weights at 0, force taps at TAB_CF, zeros elsewhere.
+constexpr int TAB_CF = 2 * MS_MAX + 1, NTAB = TAB_CF + MF_MAX;
+
 struct DevParams {
   const double* vel;   // [q]
   const double* meq;   // [q][q]
+  const double* ntab;  // [NTAB] averaging weights and force taps
+  const double* mx;    // [operands][64] MFMA operands of the mirror shape
   const double* dpm;   // [q][q]
   const double* savg;  // [2 ms + 1]
   const double* cfor;  // [mf]
@@ -68,7 +75,7 @@ struct DevParams {
   double eta_c;    // pi sigma^3 / 6
   double mu0c;     // 5 / (16 sigma^2 sqrt(pi)):  mu0 = mu0c sqrt(T)
   double sigma;
-  double weno_eps, g_ext, two_a, kappa;
+  double weno_eps, weno_e3, weno_e75, g_ext, two_a, kappa;
   double T_iso;    // > 0: isothermal, the temperature the next stage sees
   const double* tiso;  // per node: the isothermal temperature of its system (0 = thermal), or null
   int force_model, term_mask;
@@ -87,13 +94,12 @@ struct StageArgs {
   int rhs_mode;          // write L(f_prev) instead of a stage
 };
 
-// 1/x from the hardware reciprocal and two Newton steps r <- r (2 - x r):
-// within an ulp or two of the quotient, with a shorter dependency chain
-// than the correctly rounded division
+// 1/x from the hardware reciprocal (within 2^-24.4) and one third-order step r
+// <- r (1 + d + d^2), d = 1 - x r: within an ulp or two of the quotient, with
+// a shorter dependency chain than the correctly rounded division
 __device__ __forceinline__ double rcpn(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(r, fma(-x, r, 1.0), r);
-  return fma(r, fma(-x, r, 1.0), r);
+  const double r = __builtin_amdgcn_rcp(x), d = fma(-x, r, 1.0);
+  return fma(r, fma(d, d, d), r);
 }
 
 // Lane i takes lane i + 1's value across the whole wavefront (DPP wave_shl:1;
@@ -106,77 +112,55 @@ __device__ __forceinline__ double wave_next(double v) {
   return __builtin_bit_cast(double, (unsigned long long)(unsigned)lo | ((unsigned long long)(unsigned)hi << 32));
 }
 
+// Constants of the faces; the plain numbers in scalar registers, for as
+// literals the compiler puts them into two-operand fused multiply-adds, each
+// behind a register copy.
+struct WenoK {
+  double e3, e75, m275, m125, p25;
+};
+__device__ __forceinline__ WenoK weno_k(const DevParams& P) {
+  WenoK K{P.weno_e3, P.weno_e75, -2.75, -1.25, 2.5};
+  asm volatile("" : "+s"(K.m275), "+s"(K.m125), "+s"(K.p25));
+  return K;
+}
+
 // Classical WENO-5 (Jiang & Shu) face value from the five upwind-ordered
 // values v0..v4 = f_{i-2}..f_{i+2}; alpha_r = d_r/(eps+beta_r)^2 combined
-// over a common denominator (one reciprocal).
-//
-// Two arithmetic forms of the same function.  LEAN works in the first
-// differences e_m = v_(m+1) - v_m: the candidates less v2 are g0 = (5 e1 -
-// 2 e0) / 6, 6 g1 = e1 + 2 e2, 3 g2 = 2 e2 - e3 / 2; the smoothness
-// indicators 12 beta_r (against 12 eps) expand in the squares and neighbour
-// products of the differences to 16 e0^2 - 44 e0 e1 + 40 e1^2, 16 e1^2 -
-// 20 e1 e2 + 16 e2^2 and 40 e2^2 - 44 e2 e3 + 16 e3^2; with the linear
-// weights as 10 d_r = (1, 6, 3) the value is v2 plus the normalised
-// weighted corrections -- about fifteen fewer operations per face: the
-// column and wide tiles, whose faces are throughput work, use it.  The
-// narrow tile's faces sit on its critical path, and there the textbook form
-// measures slightly faster.
-template <bool LEAN>
+// over a common denominator (one reciprocal), in the first differences
+// e_m = v_(m+1) - v_m: the candidates less v2 are g0 = (5 e1 -
+// 2 e0) / 6, 6 g1 = e1 + 2 e2, 3 g2 = 2 e2 - e3 / 2; three quarters of the
+// smoothness indicators are the quadratic forms e0 (e0 - 11/4 e1) + 5/2 e1^2,
+// e1 (e1 - 5/4 e2) + e2^2 and e3 (e3 - 11/4 e2) + 5/2 e2^2 (eps enters them
+// with 3/4, under the factor 5/2 with 3/10); with the linear weights as 10 d_r
+// = (1, 6, 3) the value is v2 plus the normalised weighted corrections.  The
+// reciprocal is the hardware's, within 2^-24.4 on this part, and one
+// third-order step.  36 instructions.
 __device__ __forceinline__ double weno5(double v0, double v1, double v2, double v3, double v4,
-                                        double eps) {
-  if constexpr (LEAN) {
-    const double eps12 = 12.0 * eps;
-    const double d0 = v1 - v0, d1 = v2 - v1, d2 = v3 - v2, d3 = v4 - v3;
-    // eps12 enters through the squares: -eps12 / 64 on the outer two, eps12 / 32
-    // on the inner two sum to eps12 in every indicator (no accumulator copy)
-    const double lo = -eps12 * (1.0 / 64.0), hi = eps12 * (1.0 / 32.0);
-    const double s0 = fma(d0, d0, lo), s1 = fma(d1, d1, hi), s2 = fma(d2, d2, hi), s3 = fma(d3, d3, lo);
-    const double x01 = d0 * d1, x12 = d1 * d2, x23 = d2 * d3;
-    double t0 = fma(16.0, s0, fma(-44.0, x01, 40.0 * s1));
-    double t1 = fma(16.0, s1, fma(-20.0, x12, 16.0 * s2));
-    double t2 = fma(40.0, s2, fma(-44.0, x23, 16.0 * s3));
-    t0 *= t0;
-    t1 *= t1;
-    t2 *= t2;
-    const double u0 = t1 * t2, u1 = t0 * t2, u2 = t0 * t1;
-    const double g0 = fma(5.0 / 6.0, d1, (-1.0 / 3.0) * d0);
-    const double g1x6 = fma(2.0, d2, d1);
-    const double g2x3 = fma(2.0, d2, -0.5 * d3);
-    const double num = fma(u2, g2x3, fma(u1, g1x6, u0 * g0));
-    const double den = fma(3.0, u2, fma(6.0, u1, u0));
-    double r = __builtin_amdgcn_rcp(den);
-    r = fma(r, fma(-den, r, 1.0), r);
-    r = fma(r, fma(-den, r, 1.0), r);
-    return fma(num, r, v2);
-  }
-  const double c0 = v0 - 2.0 * v1 + v2, e0 = v0 - 4.0 * v1 + 3.0 * v2;
-  const double c1 = v1 - 2.0 * v2 + v3, e1 = v1 - v3;
-  const double c2 = v2 - 2.0 * v3 + v4, e2 = 3.0 * v2 - 4.0 * v3 + v4;
-  const double q0 = (2.0 * v0 - 7.0 * v1 + 11.0 * v2) * (1.0 / 6.0);
-  const double q1 = (-v1 + 5.0 * v2 + 2.0 * v3) * (1.0 / 6.0);
-  const double q2 = (2.0 * v2 + 5.0 * v3 - v4) * (1.0 / 6.0);
-  const double b0 = (13.0 / 12.0) * c0 * c0 + 0.25 * e0 * e0;
-  const double b1 = (13.0 / 12.0) * c1 * c1 + 0.25 * e1 * e1;
-  const double b2 = (13.0 / 12.0) * c2 * c2 + 0.25 * e2 * e2;
-  double t0 = eps + b0; t0 *= t0;
-  double t1 = eps + b1; t1 *= t1;
-  double t2 = eps + b2; t2 *= t2;
-  const double w0 = 0.1 * t1 * t2;
-  const double w1 = 0.6 * t0 * t2;
-  const double w2 = 0.3 * t0 * t1;
-  // divide through the hardware reciprocal and two Newton steps r <- r (2 - d r)
-  const double den = w0 + w1 + w2;
-  double r = __builtin_amdgcn_rcp(den);
-  r = fma(r, fma(-den, r, 1.0), r);
-  r = fma(r, fma(-den, r, 1.0), r);
-  return (w0 * q0 + w1 * q1 + w2 * q2) * r;
+                                        const WenoK& K) {
+  const double e0 = v1 - v0, e1 = v2 - v1, e2 = v3 - v2, e3 = v4 - v3;
+  const double q1 = fma(e1, e1, K.e3), q2 = fma(e2, e2, K.e3);
+  double t0 = fma(e0, fma(K.m275, e1, e0), K.p25 * q1);
+  double t1 = fma(e1, fma(K.m125, e2, e1), fma(e2, e2, K.e75));
+  double t2 = fma(e3, fma(K.m275, e2, e3), K.p25 * q2);
+  t0 *= t0;
+  t1 *= t1;
+  t2 *= t2;
+  const double u0 = t1 * t2, u1 = t0 * t2, u2 = t0 * t1;
+  const double g0 = fma(5.0 / 6.0, e1, (-1.0 / 3.0) * e0);
+  const double g1x6 = fma(2.0, e2, e1);
+  const double g2x3 = fma(2.0, e2, -0.5 * e3);
+  const double num = fma(u2, g2x3, fma(u1, g1x6, u0 * g0));
+  const double den = fma(3.0, u2, fma(6.0, u1, u0));
+  const double r = __builtin_amdgcn_rcp(den);
+  const double d = fma(-den, r, 1.0);
+  return fma(num, fma(r, fma(d, d, d), r), v2);
 }
 
 // Launch shape of the wide stage kernel: tiles of W = 64 nodes, NG groups of
 // velocities (thread = node j x group g, NT = W * NG threads).  A velocity
 // group is uniform over a wavefront, so the constant tables are read through
-// the scalar cache.  (The 16-node shape has its own tile function,
-// stage_tile_narrow.)
+// the scalar cache.  (The mirror shapes of 16 and 32 nodes have their
+// own tile function.)
 template <int Q, int W, int NG>
 struct Shape {
   static constexpr int NT = W * NG;
@@ -380,6 +364,7 @@ __device__ void stage_tile(const DevParams& P, const StageArgs& A, int tile, Sme
       S.fpart[g][j] = s0 + s1;
     }
     if (P.term_mask & EVLB_TERM_ADV) {
+      const WenoK K = weno_k(P);
       for (int idx = tid; idx < 2 * Q * (W + 1); idx += NT) {
         const int r = idx / (W + 1);
         const int jf = idx - r * (W + 1);      // face i0 + jf - 1/2
@@ -388,8 +373,7 @@ __device__ void stage_tile(const DevParams& P, const StageArgs& A, int tile, Sme
         const double* fr = &S.f[r][0];
         const int b0 = pos ? jf : jf + 5;
         const int st = pos ? 1 : -1;
-        S.flux[r][jf] = weno5<true>(fr[b0], fr[b0 + st], fr[b0 + 2 * st], fr[b0 + 3 * st], fr[b0 + 4 * st],
-                              P.weno_eps);
+        S.flux[r][jf] = weno5(fr[b0], fr[b0 + st], fr[b0 + 2 * st], fr[b0 + 3 * st], fr[b0 + 4 * st], K);
       }
     }
   }
@@ -565,21 +549,7 @@ __device__ void stage_tile(const DevParams& P, const StageArgs& A, int tile, Sme
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
-// ---------------------------------------------------------------------------
-// Narrow shape: WN = 16 nodes x Q velocities, one update per thread
-// (tid = k * 16 + j), Q / 4 wavefronts.  Built for grids too small to fill
-// the chip, where a stage is a chain of latencies: every global load of a
-// tile goes out in one batch, and the velocity-space contractions
-//   E_k = sum_l meq[k][l] a_l,  (Dp F)_k = sum_k' dpm[k][k'] F_k'  (and G)
-// run on v_mfma_f64_16x16x4 as (Q x Q) x (Q x 16 nodes) products (A operand
-// [i][c] from lane i + 16 c, B operand [c][col] from lane col + 16 c, result
-// [4 r + c][col] in register r of lane col + 16 c), so an update reads three
-// LDS values instead of 3 Q.  The Dp chains need only the tile and run with
-// the contact values and faces; the equilibrium chains wait for the Hermite
-// moments and run with the node fields, on wavefronts other than the one
-// that computes the fields.
-// ---------------------------------------------------------------------------
-constexpr int WN = 16;
+constexpr int WN = 16;  // nodes per narrow tile
 
 // Sum of v over the four lanes j, j + 16, j + 32, j + 48 (every lane gets
 // it): the cross-row swaps of gfx950 exchange 16-lane rows (pairs 0-1, 2-3)
@@ -601,32 +571,121 @@ __device__ __forceinline__ double row4_sum(double v) {
   return x + y;
 }
 
-template <int Q>
-struct SmemN {
-  double f[2 * Q][WN + 2 * HF];  // F rows then G rows, tile + WENO halo
-  double flux[2 * Q][WN + 1];    // WENO-5 face values
-  double n[WN + 2 * HN_MAX];     // density window
-  double u[WN + 4], T[WN + 4], X[WN + 4], chi[WN + 4];
-  double a[Q][WN];               // Hermite moments of the local Maxwellian
-  double fpart[Q][WN];           // EV1 partial force sums
-  double ctr[3][Q][WN];          // E, Dp F, Dp G
-  double nf[NFIELD][WN];
-  double red[Q / 4][6][WN];      // per-wavefront velocity moments
-  double sav[2 * MS_MAX + 1];
-  double cf[MF_MAX];
+// ---------------------------------------------------------------------------
+// Mirror shape: a tile of W nodes, wavefronts of column groups and four node
+// wavefronts.  A column wavefront takes NC = 128 / Q neighbouring nodes (Q = 24:
+// 4) of one distribution; its lane holds a mirror pair of velocities (r, Q - 1 -
+// r) of one node, p_(Q-1-r) = -p_r, in the layout of v_mfma_f64_4x4x4 (four
+// blocks b = L >> 2 & 3 of four columns L & 3 by four contraction indices or
+// rows k = L >> 4; an A operand has its row in L & 3): r = KT k + kt with KT = Q /
+// 8 and kt the block's part of r (Q = 8: the blocks are four column groups; Q =
+// 16: two column groups by kt; Q = 24: kt = b, the fourth block idle).  Both
+// contractions split into even and odd halves over mirror pairs, (Q / 2) x (Q /
+// 2) each, straight from the registers:
+//   (Dp f)_r, (Dp f)_(Q-1-r) = o +- e,  e = S (f_j + f_(Q-1-j)), o = A (f_j - f_(Q-1-j)),
+//   E_r, E_(Q-1-r) = e +- o,            e, o = sums over the even and odd Hermite moments,
+// and the velocity sums of the new state are the moments sum p^i f, i < 4, of
+// each distribution, a 4 x Q product.  Four node wavefronts work beside the
+// columns.  Phases (a barrier between):
+//   load      f with a 3-node halo, density window, u, T, tables to LDS
+//   faces     columns: the upwind face of each value, Dp f; nodes: 0 contact
+//             value, 1 Hermite moments, 2 force, 3 the tile's edge faces
+//   node      columns: equilibrium, the other face from LDS; nodes: 0 gradients
+//             and J1, 1 force, 2 transport and J0
+//   update    new values, their store, their moments
+//   moments   n, u, T, q of the new state
+// A stage is a chain of latencies at small grids and bound by vector
+// instructions and occupancy at large ones.  The node wavefronts' chains are
+// the longest of the two middle phases, so they issue first (s_setprio: 1 to
+// 4%).  A stage of 16-node tiles in a captured graph, where an empty launch is
+// 1.6 us, against one value per thread, full 16x16x4 products and the partial
+// velocity moments through LDS:
+//   256 nodes   q 8 5.93 -> 3.79   q 16 5.85 -> 4.06   q 24 6.24 -> 4.65 us
+// ---------------------------------------------------------------------------
+template <int Q, int W>
+struct Mirror {
+  static constexpr int KT = Q / 8;                         // parts of r
+  static constexpr int NC = Q == 24 ? 4 : 128 / Q;         // nodes per column wavefront
+  static constexpr int NR = Q == 8 ? 1 : (Q == 16 ? 2 : 4);  // blocks that hold parts of r
+  static constexpr int NCW = 2 * (W / NC);                 // column wavefronts
+  static constexpr int NT = 64 * (NCW + 4);
+  static constexpr int NOP = 4 * NR + 2;                   // MFMA operands per lane
+  // row stride in LDS: the lanes of a half wavefront, NC columns of 32 / NC
+  // consecutive r, on distinct banks: NC (mod 2 NC) or its negative, at least W + 7
+  static constexpr int stride() {
+    int s = W + 2 * HF + 1;
+    while (s % (Q == 24 ? 8 : 32) != (Q == 24 ? 4 : (Q == 8 ? 16 : 8)) && (Q != 16 || s % 32 != 24)) ++s;
+    return s;
+  }
+  static constexpr int FS = stride();
+  static_assert(W % NC == 0 && 64 % W == 0 && W + 4 <= 64 && NT <= 1024, "tile shape");
 };
 
+// Per-node quantities of the update, scaled by the stage's factor of L: u, the
+// factor of f, force, then per distribution the J1 part of the cubic (4) and
+// the J0 part of its coefficients 0, 1 and 3.
+enum { MC_U, MC_NUB, MC_FX, MC_F, MC_G = MC_F + 7, NMC = MC_G + 7 };
+
+template <int Q, int W>
+struct SmemM {
+  double f[2 * Q][Mirror<Q, W>::FS];     // F rows then G rows: node i at i + 3
+  double flux[2 * Q][Mirror<Q, W>::FS];  // faces: left of node i at i
+  double n[W + 2 * HN_MAX];              // density window
+  double u[W + 4], T[W + 4], X[W + 4], chi[W + 4];
+  double a[Q][W];                        // Hermite moments of the local Maxwellian
+  double fp[64 / W][W];                 // parts of the force
+  double co[NMC][W];                     // node coefficients of the update
+  double mom[2][4][W];                   // moments of the new F and G
+  double tab[NTAB];                      // averaging weights and force taps
+  double op[Mirror<Q, W>::NOP][64];      // MFMA operands
+};
+
+// lane i takes the value of lane i - 4 S of its 16-lane row (cyclic)
+template <int S>
+__device__ __forceinline__ double row_rot(double v) {
+  if constexpr (S == 0) {
+    return v;
+  } else {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, 0x120 + 4 * S, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), 0x120 + 4 * S, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (unsigned long long)(unsigned)lo | ((unsigned long long)(unsigned)hi << 32));
+  }
+}
+
+__device__ __forceinline__ double mfma4(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+
+// sum over the blocks that hold parts of r of (operand s) x (value of the
+// block s away)
 template <int Q>
-__device__ void stage_tile_narrow(const DevParams& P, const StageArgs& A, int tile, SmemN<Q>& S) {
-  constexpr int W = WN, NT = W * Q, NW = Q / 4;
-  constexpr int RB = (Q + 15) / 16;  // row blocks of 16 output rows
-  constexpr int KC = Q / 4;          // contraction steps of 4
-  static_assert(2 * RB <= NW, "one Dp chain per wavefront");
-  static_assert(NT >= 2 * MS_MAX + 1 + MF_MAX, "one thread per table entry");
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
+__device__ __forceinline__ double mirror_dot(const double* op, double v) {  // op: 64 apart
+  double x = mfma4(op[0], v, 0.0);
+  if constexpr (Q == 16) {
+    x = mfma4(op[64], row_rot<2>(v), x);
+  } else if constexpr (Q == 24) {
+    x = mfma4(op[64], row_rot<1>(v), x);
+    x = mfma4(op[128], row_rot<2>(v), x);
+    x = mfma4(op[192], row_rot<3>(v), x);
+  }
+  return x;
+}
+
+template <int Q>
+__device__ __forceinline__ double mirror_blocks(double v) {  // sum over the blocks' parts
+  if constexpr (Q == 8) return v;
+  v += row_rot<2>(v);
+  if constexpr (Q == 24) v += row_rot<1>(v);
+  return v;
+}
+
+template <int Q, int W>
+__device__ void stage_tile_mirror(const DevParams& P, const StageArgs& A, int tile, SmemM<Q, W>& S) {
+  using M = Mirror<Q, W>;
+  constexpr int NT = M::NT, KT = M::KT, NC = M::NC, NR = M::NR, NCW = M::NCW, FS = M::FS;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int j = tid % W, k = tid / W;
   int off, nsys, i0;
   if (P.single) {
     off = 0;
@@ -640,50 +699,25 @@ __device__ void stage_tile_narrow(const DevParams& P, const StageArgs& A, int ti
   }
   const long long ntot = P.ntot;
   const int hn = P.hn;
-  const bool valid = (i0 + j) < nsys;
-  const long long gnode = off + i0 + j;
+  const bool adv = P.term_mask & EVLB_TERM_ADV, frc = P.term_mask & EVLB_TERM_FORCE;
+  // out = ca f_n + bb f + cc L(f)
+  const double cc = A.rhs_mode ? 1.0 : A.beta * P.dt;
+  const double ca = A.rhs_mode || A.first ? 0.0 : A.alpha;
+  const double bb = A.rhs_mode ? 0.0 : (A.first ? A.alpha + A.beta : A.beta);
 
-  // MFMA chains of this wavefront: Dp chain i < 2 RB (F then G, row block
-  // i mod RB) and equilibrium chain rb < RB run on wavefront (1 + i) mod NW
-  // and (1 + rb) mod NW (wavefront 0 computes the node fields)
-  int chD = -1, chE = -1;
-#pragma unroll
-  for (int i = 0; i < 2 * RB; ++i)
-    if ((1 + i) % NW == wave) chD = i;
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-    if ((1 + rb) % NW == wave) chE = rb;
-  const bool dchain = chD >= 0 && (P.term_mask & EVLB_TERM_FORCE);
+  const WenoK K = weno_k(P);
 
-  // ---- 1. load: one batch of global loads, then the LDS writes ----------
-  double aD[KC], aE[KC];  // MFMA A operands: table rows 16 rb + (lane & 15)
-  {
-    const int rowD = 16 * (chD % RB) + (lane & 15), rowE = 16 * chE + (lane & 15);
-#pragma unroll
-    for (int b = 0; b < KC; ++b) {
-      const int col = 4 * b + (lane >> 4);
-      aD[b] = dchain && rowD < Q ? P.dpm[rowD * Q + col] : 0.0;
-      aE[b] = chE >= 0 && rowE < Q ? P.meq[rowE * Q + col] : 0.0;
-    }
-  }
-  const double pk = P.vel[k];
-  double Fn = 0.0, Gn = 0.0;
-  if (!A.first && !A.rhs_mode && valid) {
-    Fn = A.f_n[(long long)k * ntot + gnode];
-    Gn = A.f_n[(long long)(Q + k) * ntot + gnode];
-  }
-  constexpr int FW = W + 2 * HF;
-  constexpr int NFV = 2 * Q * FW;
-  constexpr int LF = (NFV + NT - 1) / NT;
+  // ---- load: one batch of global loads, then the LDS writes ----------------
+  // rows of f: LPR lanes a row, NT / LPR rows at a time
+  constexpr int FW = W + 2 * HF, LPR = FW <= 32 ? 32 : 64, RPB = NT / LPR, LF = (2 * Q + RPB - 1) / RPB;
+  static_assert(FW <= LPR && NT % LPR == 0, "a row's columns fit its lanes");
+  const int fcol = tid % LPR, frow = tid / LPR;
+  const double* fsrc = A.f_prev + (long long)frow * ntot + off + wrapi(i0 - HF + fcol, nsys);
   double fv[LF];
 #pragma unroll
   for (int i = 0; i < LF; ++i) {
-    const int idx = tid + i * NT;
     fv[i] = 0.0;
-    if (idx < NFV) {
-      const int r = idx / FW;
-      fv[i] = A.f_prev[(long long)r * ntot + off + wrapi(i0 - HF + idx - r * FW, nsys)];
-    }
+    if (fcol < FW && frow + i * RPB < 2 * Q) fv[i] = fsrc[(long long)(i * RPB) * ntot];
   }
   const double* mn = A.mom_in;
   constexpr int LN = (W + 2 * HN_MAX + NT - 1) / NT;
@@ -692,321 +726,284 @@ __device__ void stage_tile_narrow(const DevParams& P, const StageArgs& A, int ti
 #pragma unroll
   for (int i = 0; i < LN; ++i) {
     const int c = tid + i * NT;
-    nv[i] = c < nwin ? mn[off + wrapi(i0 - hn + c, nsys)] : 0.0;
+    nv[i] = 0.0;
+    if (c < nwin) nv[i] = mn[off + wrapi(i0 - hn + c, nsys)];
   }
-  // thread c < W + 4 owns node i0 - 2 + c: u, T, q
-  double uv = 0.0, Tv = 0.0, qv = 0.0;
-  if (tid < W + 4) {
-    const int node = off + wrapi(i0 - 2 + tid, nsys);
-    uv = mn[ntot + node];
-    Tv = mn[2 * ntot + node];
-    qv = mn[3 * ntot + node];
+  constexpr int LO = (64 * M::NOP + NT - 1) / NT;
+  double ov[LO];
+#pragma unroll
+  for (int i = 0; i < LO; ++i) {
+    ov[i] = 0.0;
+    if (tid + i * NT < 64 * M::NOP) ov[i] = P.mx[tid + i * NT];
+  }
+  // node wavefront 0: the tables; 1: u and T of the tile +-2; 2: q of its nodes
+  constexpr int LT = (NTAB + 63) / 64;
+  double uv, Tv, qv, tv[LT];
+  if (wave == NCW) {
+#pragma unroll
+    for (int i = 0; i < LT; ++i)
+      if (lane + 64 * i < NTAB) tv[i] = P.ntab[lane + 64 * i];
+  } else if (wave == NCW + 1) {
+    if (lane < W + 4) {
+      const int node = off + wrapi(i0 - 2 + lane, nsys);
+      uv = mn[ntot + node];
+      Tv = mn[2 * ntot + node];
+    }
+  } else if (wave == NCW + 2 && lane < W) {
+    qv = mn[3 * ntot + off + wrapi(i0 + lane, nsys)];
+  }
+  // a column wavefront's f_n
+  const int d = wave & 1;
+  const int kt = Q == 8 ? 0 : (Q == 16 ? (lane >> 3) & 1 : (lane >> 2) & 3);
+  const bool live = kt < KT;  // Q = 24: the fourth block has no velocities
+  const int r = KT * (lane >> 4) + (live ? kt : 0);
+  const int cw = lane & (NC - 1), c = (wave >> 1) * NC + cw;  // node of a column lane
+  const int row0 = d * Q + r, row1 = d * Q + Q - 1 - r;
+  const bool valid = live && i0 + c < nsys;
+  const long long gnode = off + i0 + c;
+  double Fn0, Fn1, pr;
+  if (wave < NCW) {
+    Fn0 = 0.0;
+    Fn1 = 0.0;
+    pr = P.vel[r];
+    if (!A.first && !A.rhs_mode && valid) {
+      Fn0 = A.f_n[(long long)row0 * ntot + gnode];
+      Fn1 = A.f_n[(long long)row1 * ntot + gnode];
+    }
   }
   // isothermal temperature of the own node's system (moment threads)
   double tiso = P.T_iso;
-  if (P.tiso && tid < W && valid) tiso = P.tiso[gnode];
-  // averaging weights and force taps: threads NT - 97 .. NT - 1
-  constexpr int NSAV = 2 * MS_MAX + 1;
-  const int e = tid - (NT - NSAV - MF_MAX);
-  const double* src = nullptr;
-  int si = 0;
-  if (e >= 0 && e < 2 * P.ms + 1) { src = P.savg; si = e; }
-  else if (e >= NSAV && e < NSAV + P.mf) { src = P.cfor; si = e - NSAV; }
-  const double tv = src ? src[si] : 0.0;
+  if (P.tiso && tid < W && i0 + tid < nsys) tiso = P.tiso[off + i0 + tid];
 #pragma unroll
-  for (int i = 0; i < LF; ++i) {
-    const int idx = tid + i * NT;
-    if (idx < NFV) {
-      const int r = idx / FW;
-      S.f[r][idx - r * FW] = fv[i];
-    }
-  }
+  for (int i = 0; i < LF; ++i)
+    if (fcol < FW && frow + i * RPB < 2 * Q) S.f[frow + i * RPB][fcol] = fv[i];
 #pragma unroll
   for (int i = 0; i < LN; ++i) {
-    const int c = tid + i * NT;
-    if (c < nwin) S.n[c] = nv[i];
+    const int w = tid + i * NT;
+    if (w < nwin) S.n[w] = nv[i];
   }
-  if (tid < W + 4) {
-    S.u[tid] = uv;
-    S.T[tid] = Tv;
+#pragma unroll
+  for (int i = 0; i < LO; ++i)
+    if (tid + i * NT < 64 * M::NOP) (&S.op[0][0])[tid + i * NT] = ov[i];
+  if (wave == NCW) {
+#pragma unroll
+    for (int i = 0; i < LT; ++i)
+      if (lane + 64 * i < NTAB) S.tab[lane + 64 * i] = tv[i];
+  } else if (wave == NCW + 1 && lane < W + 4) {
+    S.u[lane] = uv;
+    S.T[lane] = Tv;
   }
-  if (e >= 0 && e < NSAV) S.sav[e] = tv;
-  else if (e >= NSAV) S.cf[e - NSAV] = tv;
   __syncthreads();
 
-  // ---- 2. contact value, transport, Hermite moments, force sums, faces ----
-  // B operands of this wavefront's Dp chain, read before the faces
-  double bD[KC];
-#pragma unroll
-  for (int b = 0; b < KC; ++b) bD[b] = 0.0;
-  if (dchain) {
-    const int brow = chD / RB == 1 ? Q : 0;
-#pragma unroll
-    for (int b = 0; b < KC; ++b) bD[b] = S.f[brow + 4 * b + (lane >> 4)][(lane & 15) + HF];
-  }
-  if (tid < W + 4) {
-    // chi(nbar) and X = n^2 chi T on the tile +-2 (eq:carnstar)
-    const int c = tid, cn = c + hn - 2;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int jj = -P.ms;
-    for (; jj + 3 <= P.ms; jj += 4) {
-      s0 += S.sav[jj + P.ms] * S.n[cn + jj];
-      s1 += S.sav[jj + 1 + P.ms] * S.n[cn + jj + 1];
-      s2 += S.sav[jj + 2 + P.ms] * S.n[cn + jj + 2];
-      s3 += S.sav[jj + 3 + P.ms] * S.n[cn + jj + 3];
+  // ---- faces, Dp f; contact value and transport; Hermite moments; force ----
+  double f0, f1, lf0, lf1, g0, g1;  // column wavefronts
+  double nn, chi;                         // node wavefront 0, node lane - 2
+  const double* op = &S.op[0][lane];
+  // force of node lane % W, share `part` of 64 / W of the paired taps
+  auto force_part = [&](int part) {
+    constexpr int NP = 64 / W;
+    const int j = lane % W;
+    const double* nc = &S.n[j + hn];
+    double s0 = 0.0, s1 = 0.0;
+    if (P.force_model == EVLB_FORCE_EV1) {
+      const double* cf = &S.tab[TAB_CF - 1];
+      int m = 1 + part;
+      for (; m + 4 * NP <= P.mf; m += 5 * NP) {
+        s0 += cf[m] * (nc[m] - nc[-m]);
+        s1 += cf[m + NP] * (nc[m + NP] - nc[-m - NP]);
+        s0 += cf[m + 2 * NP] * (nc[m + 2 * NP] - nc[-m - 2 * NP]);
+        s1 += cf[m + 3 * NP] * (nc[m + 3 * NP] - nc[-m - 3 * NP]);
+        s0 += cf[m + 4 * NP] * (nc[m + 4 * NP] - nc[-m - 4 * NP]);
+      }
+      for (; m <= P.mf; m += NP) s0 += cf[m] * (nc[m] - nc[-m]);
+    } else if (P.force_model == EVLB_FORCE_EV2 && part == 0) {
+      const double idx12 = P.inv_dx * (1.0 / 12.0);
+      const double d1 = (nc[-2] - 8.0 * nc[-1] + 8.0 * nc[1] - nc[2]) * idx12;
+      const double d3 = (-nc[-2] + 2.0 * nc[-1] - 2.0 * nc[1] + nc[2]) * (0.5 * P.inv_dx * P.inv_dx * P.inv_dx);
+      s0 = P.two_a * d1 + P.kappa * d3;
     }
-    for (; jj <= P.ms; ++jj) s0 += S.sav[jj + P.ms] * S.n[cn + jj];
-    const double eta = P.eta_c * ((s0 + s1) + (s2 + s3));
-    const double om = 1.0 - eta;
-    const double chi = (2.0 - eta) * rcpn(2.0 * om * om * om);
-    const double nn = S.n[cn];
-    S.chi[c] = chi;
-    S.X[c] = nn * nn * chi * Tv;
-    if (c >= 2 && c < W + 2) {
-      // transport of the own node: mu (eq:viscosity), tau (eq:tau), Pr (eq:prandtl)
-      const double bn = P.b * nn;
+    S.fp[part][j] = s0 + s1;
+  };
+  if (wave >= NCW) __builtin_amdgcn_s_setprio(2);
+  if (wave < NCW) {
+    // p_r < 0: the face on the right, upwind from the right; Q - 1 - r: on the left
+    const double* x0 = &S.f[row0][c + 2];
+    const double* x1 = &S.f[row1][c];
+    f0 = x0[1];
+    f1 = x1[3];
+    g0 = 0.0;
+    g1 = 0.0;
+    if (adv) {
+      lf0 = weno5(x0[4], x0[3], x0[2], x0[1], x0[0], K);
+      lf1 = weno5(x1[0], x1[1], x1[2], x1[3], x1[4], K);
+      S.flux[row0][c + 1] = lf0;
+      S.flux[row1][c] = lf1;
+    }
+    if (frc) {
+      const double e = mirror_dot<Q>(op, f0 + f1), o = mirror_dot<Q>(op + 64 * NR, f0 - f1);
+      g0 = o + e;
+      g1 = o - e;
+    }
+  } else if (wave == NCW) {
+    if (lane < W + 4) {
+      // chi(nbar) and X = n^2 chi T (eq:carnstar); the averaging weights are
+      // even: pairs, four in flight
+      const double* nc = &S.n[lane + hn - 2];
+      const double* sw = &S.tab[P.ms];
+      nn = nc[0];
+      double s0 = sw[0] * nn, s1 = 0.0;
+      int j = 1;
+      for (; j + 3 <= P.ms; j += 4) {
+        s0 += sw[j] * (nc[j] + nc[-j]);
+        s1 += sw[j + 1] * (nc[j + 1] + nc[-j - 1]);
+        s0 += sw[j + 2] * (nc[j + 2] + nc[-j - 2]);
+        s1 += sw[j + 3] * (nc[j + 3] + nc[-j - 3]);
+      }
+      for (; j <= P.ms; ++j) s0 += sw[j] * (nc[j] + nc[-j]);
+      const double eta = P.eta_c * (s0 + s1);
+      const double om = 1.0 - eta;
+      chi = (2.0 - eta) * rcpn(2.0 * om * om * om);
+      S.chi[lane] = chi;
+      S.X[lane] = nn * nn * chi * S.T[lane];
+    }
+  } else if (wave == NCW + 1) {
+    if (lane < W) {
+      // Hermite moments a_0 = n, a_1 = n u, a_{l+1} = u a_l + l (T - 1) a_{l-1}
+      const double n = S.n[lane + hn], u = S.u[lane + 2], tm1 = S.T[lane + 2] - 1.0;
+      double am = n, a = n * u;
+      S.a[0][lane] = am;
+      S.a[1][lane] = a;
+#pragma unroll
+      for (int l = 1; l < Q - 1; ++l) {
+        const double an = fma(u, a, (double)l * tm1 * am);
+        am = a;
+        a = an;
+        S.a[l + 1][lane] = a;
+      }
+    }
+  } else if (wave == NCW + 2) {
+    force_part(lane / W);
+  } else if (adv && lane < 2 * Q) {
+    // the face of each row that no node's lane forms: right of the last
+    // node (p_k > 0) or left of the first
+    const bool pos = lane % Q >= Q / 2;
+    const double* x = &S.f[lane][pos ? W : 1];
+    const double v[5] = {x[0], x[1], x[2], x[3], x[4]};
+    S.flux[lane][pos ? W : 0] = weno5(pos ? v[0] : v[4], pos ? v[1] : v[3], v[2], pos ? v[3] : v[1],
+                                            pos ? v[4] : v[0], K);
+  }
+  __syncthreads();
+
+  // ---- equilibrium and the other faces; coefficients per node --------------
+  double E0, E1, acc0, acc1;
+  if (wave < NCW) {
+    acc0 = 0.0;
+    acc1 = 0.0;
+    const double ev = S.a[2 * r][c], od = S.a[2 * r + 1][c];
+    if (adv) {
+      const double cpx = cc * P.inv_dx * fabs(pr);
+      acc0 = cpx * (lf0 - S.flux[row0][c]);
+      acc1 = cpx * (lf1 - S.flux[row1][c + 1]);
+    }
+    acc0 = fma(ca, Fn0, acc0);
+    acc1 = fma(ca, Fn1, acc1);
+    const double e = mirror_dot<Q>(op + 128 * NR, ev), o = mirror_dot<Q>(op + 192 * NR, od);
+    E0 = e + o;
+    E1 = e - o;
+  } else if (wave == NCW) {
+    // gradients and J1.  Shakhov relaxation and J1 of a value: -nu f + E c(xi)
+    // with a cubic c per node and distribution (see the column shape)
+    const double idx12 = P.inv_dx * (1.0 / 12.0);
+    const int w = lane, j = w - 2;
+    if (j >= 0 && j < W) {
+      const double T = S.T[w], iT = rcpn(T);
+      const double Ag = (S.X[w - 2] - 8.0 * S.X[w - 1] + 8.0 * S.X[w + 1] - S.X[w + 2]) * idx12 * rcpn(S.X[w]);
+      const double Bg = (S.T[w - 2] - 8.0 * S.T[w - 1] + 8.0 * S.T[w + 1] - S.T[w + 2]) * idx12 * iT;
+      const double Ug = (S.u[w - 2] - 8.0 * S.u[w - 1] + 8.0 * S.u[w + 1] - S.u[w + 2]) * idx12;
+      const double pre = P.term_mask & EVLB_TERM_J1 ? -P.b * nn * chi * cc : 0.0;
+      const double pA = pre * Ag, pB = pre * Bg, pU = pre * Ug;
+      S.co[MC_F][j] = -0.6 * pU;
+      S.co[MC_F + 1][j] = pA - 0.9 * pB;
+      S.co[MC_F + 2][j] = 0.6 * pU * iT;
+      S.co[MC_F + 3][j] = 0.3 * pB * iT;
+      S.co[MC_G][j] = -0.2 * T * pU;
+      S.co[MC_G + 1][j] = T * (pA - 0.3 * pB);
+      S.co[MC_G + 2][j] = 0.6 * pU;
+      S.co[MC_G + 3][j] = 0.3 * pB;
+    }
+  } else if (wave == NCW + 1) {
+    if (lane < W) {
+      double Fx = S.fp[0][lane];
+#pragma unroll
+      for (int q = 1; q < 64 / W; ++q) Fx += S.fp[q][lane];
+      S.co[MC_FX][lane] = frc ? cc * (P.g_ext + Fx) : 0.0;
+      S.co[MC_U][lane] = S.u[lane + 2];
+    }
+  } else if (wave == NCW + 2) {
+    // transport: mu (eq:viscosity), tau (eq:tau), Pr (eq:prandtl); J0
+    if (lane < W) {
+      const double T = S.T[lane + 2], n = S.n[lane + hn], chi = S.chi[lane + 2];
+      const double bn = P.b * n;
       const double y = bn * chi;
-      const double mu0 = P.mu0c * sqrt(Tv);
       const double c12 = 0.16 * (1.0 + 12.0 / M_PI);
       const double c32 = 0.36 * (1.0 + 32.0 / (9.0 * M_PI));
+      const double mu0 = P.mu0c * sqrt(T);
       const double mu = mu0 * (rcpn(chi) + 0.8 * bn + c12 * bn * bn * chi);
-      S.nf[NF_NU][c - 2] = chi * nn * Tv * (1.0 + 0.4 * y) * rcpn(mu);
       const double Pr = (2.0 / 3.0) * (1.0 + 0.6 * y) * (1.0 + 0.8 * y + c12 * y * y) *
                         rcpn((1.0 + 0.4 * y) * (1.0 + 1.2 * y + c32 * y * y));
-      const double iT = rcpn(Tv);
-      S.nf[NF_S][c - 2] = (1.0 - Pr) * qv * (0.2 * iT * iT) * rcpn(nn);
-      S.nf[NF_PRE][c - 2] = -bn * chi;
-    }
-  }
-  if (tid >= NT - W) {
-    // Hermite moments a_0 = n, a_1 = n u, a_{l+1} = u a_l + l (T - 1) a_{l-1}
-    const int jn = tid - (NT - W);
-    const double n = S.n[jn + hn], u = S.u[jn + 2], tm1 = S.T[jn + 2] - 1.0;
-    double am = n, a = n * u;
-    S.a[0][jn] = am;
-    S.a[1][jn] = a;
-#pragma unroll
-    for (int l = 1; l < Q - 1; ++l) {
-      const double an = u * a + (double)l * tm1 * am;
-      am = a;
-      a = an;
-      S.a[l + 1][jn] = a;
-    }
-  }
-  if (P.force_model == EVLB_FORCE_EV1) {
-    // node j, chunk k of the paired taps
-    const int ch = (P.mf + Q - 1) / Q;
-    const int m0 = 1 + k * ch;
-    const int m1 = min(P.mf, m0 + ch - 1);
-    const int cn = j + hn;
-    double s0 = 0.0, s1 = 0.0;
-    int m = m0;
-    for (; m + 1 <= m1; m += 2) {
-      s0 += S.cf[m - 1] * (S.n[cn + m] - S.n[cn - m]);
-      s1 += S.cf[m] * (S.n[cn + m + 1] - S.n[cn - m - 1]);
-    }
-    if (m <= m1) s0 += S.cf[m - 1] * (S.n[cn + m] - S.n[cn - m]);
-    S.fpart[k][j] = s0 + s1;
-  }
-  // WENO faces on the threads without contact-value or Hermite work.  With
-  // six or more wavefronts the contact-value wavefront takes none, wavefronts
-  // 1 .. NW-2 take FM faces per thread and the Hermite wavefront's other lanes
-  // the rest, so that no wavefront runs many faces and the recurrence too.
-  // Each face index is clamped into range and only the store is guarded, so
-  // the faces of a thread are independent straight-line code.
-  if (P.term_mask & EVLB_TERM_ADV) {
-    constexpr int NFACE = 2 * Q * (W + 1);
-    constexpr bool SPLIT = NT >= 384;
-    constexpr int WS = SPLIT ? 64 : W + 4;            // first face thread
-    constexpr int NMAIN = SPLIT ? 64 * (NW - 2) : NT - W - WS;
-    constexpr int FM = SPLIT ? NFACE / NMAIN : (NFACE + NMAIN - 1) / NMAIN;
-    constexpr int NREST = SPLIT ? NFACE - FM * NMAIN : 0;  // faces for the last wavefront
-    static_assert(!SPLIT || NREST <= 64 - W, "the remaining faces fit the last wavefront");
-    int base = -1, nf = 0, stride = 0;
-    if (tid >= WS && tid < WS + NMAIN) {
-      base = tid - WS;
-      nf = FM;
-      stride = NMAIN;
-    } else if (SPLIT && tid >= 64 * (NW - 1) && tid < 64 * (NW - 1) + NREST) {
-      base = FM * NMAIN + tid - 64 * (NW - 1);
-      nf = 1;
-      stride = 0;
-    }
-    // face idx of row r = idx / (W + 1): face i0 + jf - 1/2, upwind by the sign of p_k
-    auto face = [&](int idx, bool keep) {
-      const int r = idx / (W + 1);
-      const int jf = idx - r * (W + 1);
-      const int kr = r < Q ? r : r - Q;
-      const bool pos = kr >= Q / 2;  // p_k > 0: upwind from the left
-      const double* fr = &S.f[r][0];
-      const int b0 = pos ? jf : jf + 5;
-      const int st = pos ? 1 : -1;
-      const double h = weno5<false>(fr[b0], fr[b0 + st], fr[b0 + 2 * st], fr[b0 + 3 * st], fr[b0 + 4 * st], P.weno_eps);
-      if (keep) S.flux[r][jf] = h;
-    };
-    if (nf == FM) {  // whole wavefronts take this branch or the next
-#pragma unroll
-      for (int i = 0; i < FM; ++i) {
-        const int want = base + i * stride;
-        const bool keep = want < NFACE;
-        face(keep ? want : base, keep);
-      }
-    } else if (nf == 1) {
-      face(base, true);
-    }
-  }
-  if (dchain) {
-    // (Dp F) or (Dp G) for one row block on the MFMA, as two independent
-    // accumulation chains (even and odd contraction steps)
-    const int p = 1 + chD / RB, rb = chD % RB;
-    const int col = lane & 15, c = lane >> 4;
-    dbl4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int b = 0; b < KC; b += 2) {
-      acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(aD[b], bD[b], acc0, 0, 0, 0);
-      if (b + 1 < KC) acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(aD[b + 1], bD[b + 1], acc1, 0, 0, 0);
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = 16 * rb + 4 * r + c;
-      if (row < Q) S.ctr[p][row][col] = acc0[r] + acc1[r];
+      const double iT = rcpn(T);
+      const double nu = P.term_mask & EVLB_TERM_J0 ? cc * chi * n * T * (1.0 + 0.4 * y) * rcpn(mu) : 0.0;
+      const double sv = nu * ((1.0 - Pr) * qv * (0.2 * iT * iT) * rcpn(n));
+      S.co[MC_NUB][lane] = bb - nu;
+      S.co[MC_F + 4][lane] = nu;
+      S.co[MC_F + 5][lane] = -3.0 * sv;
+      S.co[MC_F + 6][lane] = sv * iT;
+      S.co[MC_G + 4][lane] = T * nu;
+      S.co[MC_G + 5][lane] = -T * sv;
+      S.co[MC_G + 6][lane] = sv;
     }
   }
   __syncthreads();
 
-  // ---- 3. force and gradients (threads < 16); equilibrium (MFMA) ----------
-  if (tid < W) {
-    const int c = j + 2, cn = j + hn;
-    const double idx12 = P.inv_dx * (1.0 / 12.0);
-    double Fx = P.g_ext;
-    if (P.force_model == EVLB_FORCE_EV1) {
-      double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-      for (int g = 0; g + 1 < Q; g += 2) {
-        s0 += S.fpart[g][j];
-        s1 += S.fpart[g + 1][j];
-      }
-      Fx += s0 + s1;
-    } else if (P.force_model == EVLB_FORCE_EV2) {
-      const double d1 = (S.n[cn - 2] - 8.0 * S.n[cn - 1] + 8.0 * S.n[cn + 1] - S.n[cn + 2]) * idx12;
-      const double d3 = (-S.n[cn - 2] + 2.0 * S.n[cn - 1] - 2.0 * S.n[cn + 1] + S.n[cn + 2]) *
-                        (0.5 * P.inv_dx * P.inv_dx * P.inv_dx);
-      Fx += P.two_a * d1 + P.kappa * d3;
-    }
-    const double T = S.T[c];
-    S.nf[NF_A][j] = (S.X[c - 2] - 8.0 * S.X[c - 1] + 8.0 * S.X[c + 1] - S.X[c + 2]) * idx12 * rcpn(S.X[c]);
-    S.nf[NF_B][j] = (S.T[c - 2] - 8.0 * S.T[c - 1] + 8.0 * S.T[c + 1] - S.T[c + 2]) * idx12 * rcpn(T);
-    S.nf[NF_U1][j] = (S.u[c - 2] - 8.0 * S.u[c - 1] + 8.0 * S.u[c + 1] - S.u[c + 2]) * idx12;
-    S.nf[NF_FX][j] = Fx;
-    S.nf[NF_N][j] = S.n[cn];
-    S.nf[NF_U][j] = S.u[c];
-    S.nf[NF_T][j] = T;
-  }
-  if (chE >= 0) {
-    const int col = lane & 15, c = lane >> 4;
-    dbl4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int b = 0; b < KC; ++b)
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(aE[b], S.a[4 * b + c][col], acc, 0, 0, 0);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = 16 * chE + 4 * r + c;
-      if (row < Q) S.ctr[0][row][col] = acc[r];
-    }
-  }
-  __syncthreads();
-
-  // ---- 4. update -----------------------------------------------------------
-  double pm[6];
-  {
-    const double u = S.nf[NF_U][j], T = S.nf[NF_T][j];
-    const double nu = S.nf[NF_NU][j], sS = S.nf[NF_S][j], pre = S.nf[NF_PRE][j];
-    const double Ag = S.nf[NF_A][j], Bg = S.nf[NF_B][j], Ug = S.nf[NF_U1][j];
-    const double Fx = S.nf[NF_FX][j];
-    const double invT = rcpn(T);
-    const double E = S.ctr[0][k][j];
-    const double F = S.f[k][j + HF];
-    const double G = S.f[Q + k][j + HF];
-    const double xi = pk - u;
-    const double th = xi * xi * invT;
-    double LF = 0.0, LG = 0.0;
-    if (P.term_mask & EVLB_TERM_ADV) {
-      LF = -pk * (S.flux[k][j + 1] - S.flux[k][j]) * P.inv_dx;
-      LG = -pk * (S.flux[Q + k][j + 1] - S.flux[Q + k][j]) * P.inv_dx;
-    }
-    if (P.term_mask & EVLB_TERM_FORCE) {
-      LF -= Fx * S.ctr[1][k][j];
-      LG -= Fx * S.ctr[2][k][j];
-    }
-    if (P.term_mask & EVLB_TERM_J0) {
-      const double FS = E * (1.0 + sS * xi * (th - 3.0));
-      const double GS = T * E * (1.0 + sS * xi * (th - 1.0));
-      LF -= nu * (F - FS);
-      LG -= nu * (G - GS);
-    }
-    if (P.term_mask & EVLB_TERM_J1) {
-      LF += pre * E * (xi * (Ag + 0.3 * (th - 3.0) * Bg) + 0.6 * (th - 1.0) * Ug);
-      LG += pre * T * E * (xi * (Ag + 0.3 * (th - 1.0) * Bg) + 0.2 * (3.0 * th - 1.0) * Ug);
-    }
-    double Fo, Go;
-    if (A.rhs_mode) {
-      Fo = LF;
-      Go = LG;
-    } else {
-      const double Fb = A.first ? F : Fn;
-      const double Gb = A.first ? G : Gn;
-      Fo = A.alpha * Fb + A.beta * (F + P.dt * LF);
-      Go = A.alpha * Gb + A.beta * (G + P.dt * LG);
-    }
+  // ---- update ---------------------------------------------------------------
+  if (wave < NCW) {
+    const double* co = &S.co[d == 0 ? MC_F : MC_G][c];
+    const double u = S.co[MC_U][c], nub = S.co[MC_NUB][c], fx = S.co[MC_FX][c];
+    const double x0 = pr - u, x1 = -pr - u;
+    acc0 = fma(nub, f0, fma(-fx, g0, acc0));
+    acc1 = fma(nub, f1, fma(-fx, g1, acc1));
+    const double k0 = co[0] + co[4 * W], k1 = co[W] + co[5 * W], k2 = co[2 * W], k3 = co[3 * W] + co[6 * W];
+    const double o0 = fma(E0, fma(fma(fma(k3, x0, k2), x0, k1), x0, k0), acc0);
+    const double o1 = fma(E1, fma(fma(fma(k3, x1, k2), x1, k1), x1, k0), acc1);
     if (valid) {
-      A.f_out[(long long)k * ntot + gnode] = Fo;
-      A.f_out[(long long)(Q + k) * ntot + gnode] = Go;
+      A.f_out[(long long)row0 * ntot + gnode] = o0;
+      A.f_out[(long long)row1 * ntot + gnode] = o1;
     }
-    const double p2 = pk * pk;
-    pm[0] = Fo;
-    pm[1] = pk * Fo;
-    pm[2] = p2 * Fo;
-    pm[3] = p2 * pk * Fo;
-    pm[4] = Go;
-    pm[5] = pk * Go;
+    if (!A.rhs_mode) {
+      const double m = mirror_blocks<Q>(mfma4(op[256 * NR + 64], o1, mfma4(op[256 * NR], o0, 0.0)));
+      S.mom[d][lane >> 4][c] = m;
+    }
   }
   if (A.rhs_mode) {
     __syncthreads();  // LDS is reused by the next tile
     return;
   }
-  // the four velocities of a node within a wavefront: lanes j, j + 16, j + 32, j + 48
-#pragma unroll
-  for (int m = 0; m < 6; ++m) pm[m] = row4_sum(pm[m]);
-  if (lane < W) {
-#pragma unroll
-    for (int m = 0; m < 6; ++m) S.red[wave][m][j] = pm[m];
-  }
   __syncthreads();
 
-  // ---- 5. moments of the new state --------------------------------------
-  if (tid < W && valid) {
-    double ms[6];
-#pragma unroll
-    for (int m = 0; m < 6; ++m) {
-      double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-      for (int w = 0; w + 1 < NW; w += 2) {
-        s0 += S.red[w][m][tid];
-        s1 += S.red[w + 1][m][tid];
-      }
-      if (NW & 1) s0 += S.red[NW - 1][m][tid];
-      ms[m] = s0 + s1;
-    }
-    const double n = ms[0];
+  // ---- moments of the new state ----------------------------------------------
+  if (tid < W && i0 + tid < nsys) {
+    const long long g = off + i0 + tid;
+    const double n = S.mom[0][0][tid], m1 = S.mom[0][1][tid], m2 = S.mom[0][2][tid], m3 = S.mom[0][3][tid];
+    const double e0 = S.mom[1][0][tid], e1 = S.mom[1][1][tid];
     const double in = rcpn(n);
-    const double u = ms[1] * in;
-    const double T = (2.0 / 3.0) * (0.5 * ms[2] + ms[4] - 0.5 * n * u * u) * in;
-    const double x3 = ms[3] - 3.0 * u * ms[2] + 3.0 * u * u * ms[1] - u * u * u * n;
-    const double q = 0.5 * x3 + ms[5] - u * ms[4];
-    A.mom_out[gnode] = n;
-    A.mom_out[ntot + gnode] = u;
-    A.mom_out[2 * ntot + gnode] = tiso > 0.0 ? tiso : T;
-    A.mom_out[3 * ntot + gnode] = q;
+    const double u = m1 * in;
+    const double T = (2.0 / 3.0) * (0.5 * m2 + e0 - 0.5 * n * u * u) * in;
+    const double x3 = m3 - 3.0 * u * m2 + 3.0 * u * u * m1 - u * u * u * n;
+    const double q = 0.5 * x3 + e1 - u * e0;
+    A.mom_out[g] = n;
+    A.mom_out[ntot + g] = u;
+    A.mom_out[2 * ntot + g] = tiso > 0.0 ? tiso : T;
+    A.mom_out[3 * ntot + g] = q;
     if (!(n > 0.0) || !(T > 0.0) || !isfinite(n) || !isfinite(T) || !isfinite(q) || !isfinite(u))
       P.status[0] = 1;
   }
@@ -1024,28 +1021,26 @@ __device__ __forceinline__ int xcd_tile(int b, int ntiles) {
   return x * q + min(x, r) + i;
 }
 
+template <int Q, int W>
+__global__ __launch_bounds__((Mirror<Q, W>::NT)) void stage_kernel_mirror(DevParams P, StageArgs A) {
+  __shared__ SmemM<Q, W> S;
+  // every kernel argument into SGPRs before the first branch: one scalar
+  // round trip at entry instead of one at each first use
+  asm volatile("" ::"s"(P.mx), "s"(P.vel), "s"(P.ntab), "s"(P.tiles), "s"(P.status), "s"(P.ntiles), "s"(P.single),
+               "s"(P.ms), "s"(P.mf), "s"(P.hn), "s"(P.ntot), "s"(P.force_model), "s"(P.term_mask));
+  asm volatile("" ::"s"(P.inv_dx), "s"(P.dt), "s"(P.b), "s"(P.eta_c), "s"(P.mu0c), "s"(P.weno_e3), "s"(P.weno_e75),
+               "s"(P.g_ext), "s"(P.two_a), "s"(P.kappa), "s"(P.T_iso), "s"(P.tiso));
+  asm volatile("" ::"s"(A.f_prev), "s"(A.f_n), "s"(A.f_out), "s"(A.mom_in), "s"(A.mom_out), "s"(A.alpha),
+               "s"(A.beta), "s"(A.first), "s"(A.rhs_mode));
+  // one tile per workgroup (the grid is the tile count)
+  if ((int)blockIdx.x < P.ntiles) stage_tile_mirror<Q, W>(P, A, xcd_tile(blockIdx.x, P.ntiles), S);
+}
+
 template <int Q, int W, int NG>
 __global__ __launch_bounds__(W * NG) void stage_kernel(DevParams P, StageArgs A) {
-  if constexpr (W == WN) {
-    static_assert(NG == Q, "narrow tiles take one velocity per thread");
-    __shared__ SmemN<Q> S;
-    // every kernel argument into SGPRs before the first branch: one scalar
-    // round trip at entry instead of one at each first use
-    asm volatile("" ::"s"(P.meq), "s"(P.dpm), "s"(P.vel), "s"(P.savg), "s"(P.cfor), "s"(P.tiles), "s"(P.status),
-                 "s"(P.ntiles), "s"(P.single), "s"(P.ms), "s"(P.mf), "s"(P.hn), "s"(P.ntot), "s"(P.force_model),
-                 "s"(P.term_mask));
-    asm volatile("" ::"s"(P.inv_dx), "s"(P.dt), "s"(P.b), "s"(P.eta_c), "s"(P.mu0c), "s"(P.weno_eps), "s"(P.g_ext),
-                 "s"(P.two_a), "s"(P.kappa), "s"(P.T_iso), "s"(P.tiso));
-    asm volatile("" ::"s"(A.f_prev), "s"(A.f_n), "s"(A.f_out), "s"(A.mom_in), "s"(A.mom_out), "s"(A.alpha),
-                 "s"(A.beta), "s"(A.first), "s"(A.rhs_mode));
-    // one tile per workgroup (the grid is the tile count): no loop, so no
-    // wait at a loop head for loads still in flight
-    if ((int)blockIdx.x < P.ntiles) stage_tile_narrow<Q>(P, A, xcd_tile(blockIdx.x, P.ntiles), S);
-  } else {
-    __shared__ Smem<Q, W, NG> S;
-    load_tables<Q, W, NG>(P, S);
-    if ((int)blockIdx.x < P.ntiles) stage_tile<Q, W, NG>(P, A, xcd_tile(blockIdx.x, P.ntiles), S);
-  }
+  __shared__ Smem<Q, W, NG> S;
+  load_tables<Q, W, NG>(P, S);
+  if ((int)blockIdx.x < P.ntiles) stage_tile<Q, W, NG>(P, A, xcd_tile(blockIdx.x, P.ntiles), S);
 }
 
 // ---------------------------------------------------------------------------
@@ -1264,6 +1259,7 @@ __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile,
 
   // ---- 4. update, velocity by velocity -----------------------------------
   double pm[6] = {0, 0, 0, 0, 0, 0};
+  const WenoK K = weno_k(P);
   const bool adv = P.term_mask & EVLB_TERM_ADV;
   const bool frc = P.term_mask & EVLB_TERM_FORCE;
   const bool j0 = P.term_mask & EVLB_TERM_J0;
@@ -1296,8 +1292,8 @@ __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile,
       const int st = pos ? 1 : -1;
       const double* fr = &S.f[k][0];
       const double* gr = &S.f[Q + k][0];
-      const double hF = weno5<true>(fr[b0], fr[b0 + st], fr[b0 + 2 * st], fr[b0 + 3 * st], fr[b0 + 4 * st], P.weno_eps);
-      const double hG = weno5<true>(gr[b0], gr[b0 + st], gr[b0 + 2 * st], gr[b0 + 3 * st], gr[b0 + 4 * st], P.weno_eps);
+      const double hF = weno5(fr[b0], fr[b0 + st], fr[b0 + 2 * st], fr[b0 + 3 * st], fr[b0 + 4 * st], K);
+      const double hG = weno5(gr[b0], gr[b0 + st], gr[b0 + 2 * st], gr[b0 + 3 * st], gr[b0 + 4 * st], K);
       const double hFr = wave_next(hF);  // lane 63's faces are not used
       const double hGr = wave_next(hG);
       LF = -pk * (hFr - hF) * P.inv_dx;
@@ -1441,14 +1437,22 @@ struct PersistArgs {
 template <int Q, int W, int NG>
 struct GroupShape {
   static constexpr int NT = W * NG;
-  typedef std::conditional_t<W == WN, SmemN<Q>, Smem<Q, W, NG>> Shared;
-  __device__ static void prologue(const DevParams& P, Shared& S) {
-    if constexpr (W != WN) load_tables<Q, W, NG>(P, S);
-  }
+  typedef Smem<Q, W, NG> Shared;
+  __device__ static void prologue(const DevParams& P, Shared& S) { load_tables<Q, W, NG>(P, S); }
   __device__ static void tile(const DevParams& P, const StageArgs& A, int t, Shared& S, const double*,
                               const double*, const double*) {
-    if constexpr (W == WN) stage_tile_narrow<Q>(P, A, t, S);
-    else stage_tile<Q, W, NG>(P, A, t, S);
+    stage_tile<Q, W, NG>(P, A, t, S);
+  }
+};
+
+template <int Q, int W>
+struct MirrorShape {
+  static constexpr int NT = Mirror<Q, W>::NT;
+  typedef SmemM<Q, W> Shared;
+  __device__ static void prologue(const DevParams&, Shared&) {}
+  __device__ static void tile(const DevParams& P, const StageArgs& A, int t, Shared& S, const double*,
+                              const double*, const double*) {
+    stage_tile_mirror<Q, W>(P, A, t, S);
   }
 };
 
@@ -1565,11 +1569,14 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr int WIDE = 64;    // tile width for large grids
 constexpr int NARROW = WN;  // tile width for grids too small to fill the chip
 
+constexpr int WB = 32;    // nodes per broad mirror tile (q 8 and 16)
+constexpr int BROAD = 1;  // launch shape code: broad mirror tiles
+
 struct Layout {
-  size_t tables, tiles_wide, tiles_narrow, tiles_col, tiles_adj, f1, f2, momA, momB, status, tiso;
+  size_t tables, mx, tiles_broad, tiles_wide, tiles_narrow, tiles_col, tiles_adj, f1, f2, momA, momB, status, tiso;
   size_t adj_g, adj_mu2, adj_mu1, adj_fa, adj_fb, adj_mom, adj_part, adj_lam, total;
   long long ntot;
-  int ntiles_wide, ntiles_narrow, ntiles_col, ntiles_adj, ms, mf;
+  int ntiles_broad, ntiles_wide, ntiles_narrow, ntiles_col, ntiles_adj, ms, mf;
   size_t ntables;
 };
 
@@ -1635,10 +1642,41 @@ int validate(const evlb_params* p) {
   return EVLB_OK;
 }
 
+// MFMA operands per lane of the mirror shape, and their values: lane L of
+// operand i at 64 i + L, in the order Dp even, Dp odd, meq even, meq odd (one
+// for each block that holds parts of r, by distance), then p_r^i and p_(q-1-r)^i.
+int mirror_operands(int q) { return q == 8 ? Mirror<8, WN>::NOP : (q == 16 ? Mirror<16, WN>::NOP : Mirror<24, WN>::NOP); }
+
+std::vector<double> mirror_table(int q, const evlb::HostTables& t) {
+  const int KT = q / 8, NR = (mirror_operands(q) - 2) / 4;
+  auto part = [&](int b) { return q == 8 ? 0 : (q == 16 ? b >> 1 : b); };  // kt of a block
+  std::vector<double> x((size_t)64 * (4 * NR + 2), 0.0);
+  for (int L = 0; L < 64; ++L) {
+    const int i = L & 3, b = (L >> 2) & 3, k = L >> 4;
+    if (part(b) >= KT) continue;
+    const int row = KT * i + part(b);
+    for (int s = 0; s < NR; ++s) {
+      const int src = part((b - (q == 16 ? 2 * s : s)) & 3);
+      if (src >= KT) continue;
+      const int j = KT * k + src;
+      const double dj = t.dpm[(size_t)row * q + j], dm = t.dpm[(size_t)row * q + q - 1 - j];
+      x[64 * s + L] = 0.5 * (dj + dm);
+      x[64 * (NR + s) + L] = 0.5 * (dj - dm);
+      x[64 * (2 * NR + s) + L] = t.meq[(size_t)row * q + 2 * j];
+      x[64 * (3 * NR + s) + L] = t.meq[(size_t)row * q + 2 * j + 1];
+    }
+    const double p = t.vel[KT * k + part(b)], m = i == 0 ? 1.0 : (i == 1 ? p : (i == 2 ? p * p : p * p * p));
+    x[64 * (4 * NR) + L] = m;
+    x[64 * (4 * NR + 1) + L] = i & 1 ? -m : m;
+  }
+  return x;
+}
+
 Layout make_layout(const evlb_params* p) {
   Layout L{};
   L.ntot = 0;
   for (int s = 0; s < p->n_sys; ++s) L.ntot += p->nx[s];
+  L.ntiles_broad = count_tiles(p, WB);
   L.ntiles_wide = count_tiles(p, WIDE);
   L.ntiles_narrow = count_tiles(p, NARROW);
   L.ntiles_col = count_tiles(p, WC);
@@ -1651,6 +1689,10 @@ Layout make_layout(const evlb_params* p) {
   const int mfa = L.mf > 0 ? L.mf : 1;
   L.ntables = (size_t)(q + 2 * q * q + 2 * (2 * L.ms + 1) + 3 * mfa);
   off += align256(sizeof(double) * L.ntables);
+  L.mx = off;
+  off += align256(sizeof(double) * (64 * (size_t)mirror_operands(q) + NTAB));
+  L.tiles_broad = off;
+  off += align256(sizeof(int4) * (size_t)L.ntiles_broad);
   L.tiles_wide = off;
   off += align256(sizeof(int4) * (size_t)L.ntiles_wide);
   L.tiles_narrow = off;
@@ -1709,8 +1751,7 @@ namespace {
     if ((call) != hipSuccess) return EVLB_EHIP; \
   } while (0)
 
-// launch shapes per quadrature order: wide tiles (64 nodes, NG groups) and
-// narrow tiles (16 nodes, one velocity per thread)
+// launch shapes per quadrature order: wide tiles of 64 nodes, NG groups
 template <int Q> struct WideNG;
 template <> struct WideNG<8> { static constexpr int v = 4; };
 template <> struct WideNG<16> { static constexpr int v = 8; };
@@ -1721,6 +1762,9 @@ DevParams params_for(const evlb_ctx* c, int w) {
   if (w == NARROW) {
     P.tiles = (const int4*)(c->ws + c->L.tiles_narrow);
     P.ntiles = c->L.ntiles_narrow;
+  } else if (w == BROAD) {
+    P.tiles = (const int4*)(c->ws + c->L.tiles_broad);
+    P.ntiles = c->L.ntiles_broad;
   } else if (w == WC) {
     P.tiles = (const int4*)(c->ws + c->L.tiles_col);
     P.ntiles = c->L.ntiles_col;
@@ -1735,6 +1779,13 @@ template <int Q, int W, int NG>
 int launch_stage(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
   const DevParams P = params_for(c, W);
   hipLaunchKernelGGL((stage_kernel<Q, W, NG>), dim3(P.ntiles), dim3(W * NG), 0, st, P, A);
+  return hipGetLastError() == hipSuccess ? EVLB_OK : EVLB_EHIP;
+}
+
+template <int Q, int W>
+int launch_stage_mirror(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
+  const DevParams P = params_for(c, W == NARROW ? NARROW : BROAD);
+  hipLaunchKernelGGL((stage_kernel_mirror<Q, W>), dim3(P.ntiles), dim3(Mirror<Q, W>::NT), 0, st, P, A);
   return hipGetLastError() == hipSuccess ? EVLB_OK : EVLB_EHIP;
 }
 
@@ -1779,9 +1830,25 @@ int run_moments(evlb_ctx* c, const double* f, double* n, double* u, double* T, d
   return hipGetLastError() == hipSuccess ? EVLB_OK : EVLB_EHIP;
 }
 
-// tile shape: explicit, or the column shape when it yields at least four
-// wavefronts per CU, else the narrow shape (small grids, latency bound)
+// Tile shape of the per-stage launches: explicit, or by the number of tiles.
+// A stage in us on 256 CUs, narrow / broad / column:
+//   q 8    4096 nodes 4.7 / 5.0 / 11   5120 5.2 / 4.8 / 11   49152 17 / 12 / 13   65536 21 / 14.6 / 17
+//   q 16   4096 nodes 5.0 / 5.6 / 18   5120 5.7 / 5.5 / 18   49152 21 / 18 / 23   65536 26 / 23 / 28
+//   q 24   4096 nodes 5.7 / - / 30     8192 7.5 / - / 31     49152 35 / - / 44    65536 45 / - / 46
+// Narrow tiles while they fill the CUs once: the stage is one tile's latency,
+// and a broad one's is longer.  Beyond that broad tiles for q 8 and 16, which
+// hold fewer halos and node fields formed twice (q 24 would need two
+// workgroups' lanes).  The column shape once it has four wavefronts per CU to
+// hide its chain of a node's work behind.
 int pick_width(const evlb_ctx* c) {
+  if (c->p.tile_nodes) return c->p.tile_nodes;
+  if (c->L.ntiles_col >= 4 * c->cus) return WC;
+  return c->p.q < 24 && c->L.ntiles_narrow > c->cus ? BROAD : NARROW;
+}
+
+// of the persistent launch, whose grid barrier waits for every workgroup: the
+// broad shape is not built for it
+int pick_width_persistent(const evlb_ctx* c) {
   if (c->p.tile_nodes) return c->p.tile_nodes;
   return c->L.ntiles_col >= 4 * c->cus ? WC : NARROW;
 }
@@ -1805,8 +1872,11 @@ StageArgs stage_args(double* f, double* f1, double* f2, double* momA, double* mo
 
 template <int Q>
 int launch_stage_w(evlb_ctx* c, int w, const StageArgs& A, hipStream_t st) {
-  if (w == NARROW) return launch_stage<Q, NARROW, Q>(c, A, st);
+  if (w == NARROW) return launch_stage_mirror<Q, NARROW>(c, A, st);
   if (w == WC) return launch_stage_col<Q>(c, A, st);
+  if constexpr (Q < 24) {
+    if (w == BROAD) return launch_stage_mirror<Q, WB>(c, A, st);
+  }
   return launch_stage<Q, WIDE, WideNG<Q>::v>(c, A, st);
 }
 
@@ -1817,11 +1887,11 @@ int run_step(evlb_ctx* c, double* f, int nsteps, hipStream_t st) {
   double* momB = (double*)(c->ws + c->L.momB);
   int rc = run_moments<Q>(c, f, momA, momA + nt, momA + 2 * nt, momA + 3 * nt, st);
   if (rc) return rc;
-  const int w = pick_width(c);
   int mode = c->p.exec_mode;
   if (mode == EVLB_EXEC_AUTO) mode = EVLB_EXEC_PER_STAGE;
+  const int w = mode == EVLB_EXEC_PERSISTENT ? pick_width_persistent(c) : pick_width(c);
   if (mode == EVLB_EXEC_PERSISTENT) {
-    if (w == NARROW) return launch_persistent<GroupShape<Q, NARROW, Q>>(c, w, f, nsteps, st);
+    if (w == NARROW) return launch_persistent<MirrorShape<Q, NARROW>>(c, w, f, nsteps, st);
     if (w == WC) return launch_persistent<ColumnShape<Q>>(c, w, f, nsteps, st);
     return launch_persistent<GroupShape<Q, WIDE, WideNG<Q>::v>>(c, w, f, nsteps, st);
   }
@@ -2169,9 +2239,15 @@ int evlb_init(const evlb_params* params, void* d_workspace, size_t ws_bytes, voi
   host.insert(host.end(), t.cphi.begin(), t.cphi.end());
   host.insert(host.end(), t.csig.begin(), t.csig.end());
   host.insert(host.end(), t.ssig.begin(), t.ssig.end());
-  std::vector<int4> tw, tn, tc, ta;
+  std::vector<double> mx = mirror_table(q, t);
+  const size_t ntab = mx.size();
+  mx.resize(ntab + NTAB, 0.0);
+  std::copy(t.savg.begin(), t.savg.end(), mx.begin() + ntab);
+  if (L.mf > 0) std::copy(t.cfor.begin(), t.cfor.end(), mx.begin() + ntab + TAB_CF);
+  std::vector<int4> tb, tw, tn, tc, ta;
   int off = 0;
   for (int s = 0; s < params->n_sys; ++s) {
+    for (int i0 = 0; i0 < params->nx[s]; i0 += WB) tb.push_back(make_int4(off, params->nx[s], i0, 0));
     for (int i0 = 0; i0 < params->nx[s]; i0 += WIDE) tw.push_back(make_int4(off, params->nx[s], i0, 0));
     for (int i0 = 0; i0 < params->nx[s]; i0 += NARROW) tn.push_back(make_int4(off, params->nx[s], i0, 0));
     for (int i0 = 0; i0 < params->nx[s]; i0 += WC) tc.push_back(make_int4(off, params->nx[s], i0, 0));
@@ -2190,7 +2266,10 @@ int evlb_init(const evlb_params* params, void* d_workspace, size_t ws_bytes, voi
   }
   // copies ordered on the caller's stream; the stream is synchronised before
   // returning because the host vectors die with this call
-  if (hipMemcpyAsync(tab, host.data(), host.size() * sizeof(double), hipMemcpyHostToDevice, st) != hipSuccess ||
+  if (hipMemcpyAsync(c->ws + L.mx, mx.data(), mx.size() * sizeof(double), hipMemcpyHostToDevice, st) != hipSuccess ||
+      hipMemcpyAsync(tab, host.data(), host.size() * sizeof(double), hipMemcpyHostToDevice, st) != hipSuccess ||
+      hipMemcpyAsync(c->ws + L.tiles_broad, tb.data(), tb.size() * sizeof(int4), hipMemcpyHostToDevice, st) !=
+          hipSuccess ||
       hipMemcpyAsync(c->ws + L.tiles_wide, tw.data(), tw.size() * sizeof(int4), hipMemcpyHostToDevice, st) !=
           hipSuccess ||
       hipMemcpyAsync(c->ws + L.tiles_narrow, tn.data(), tn.size() * sizeof(int4), hipMemcpyHostToDevice, st) !=
@@ -2209,6 +2288,8 @@ int evlb_init(const evlb_params* params, void* d_workspace, size_t ws_bytes, voi
   DevParams& d = c->dp;
   d.vel = tab;
   d.meq = tab + q;
+  d.mx = (const double*)(c->ws + L.mx);
+  d.ntab = d.mx + ntab;
   d.dpm = tab + q + q * q;
   d.savg = tab + q + 2 * q * q;
   const int nc = (int)t.cfor.size();
@@ -2232,6 +2313,8 @@ int evlb_init(const evlb_params* params, void* d_workspace, size_t ws_bytes, voi
   d.mu0c = 5.0 / (16.0 * sg * sg * std::sqrt(M_PI));
   d.sigma = sg;
   d.weno_eps = params->weno_eps;
+  d.weno_e3 = 0.3 * params->weno_eps;
+  d.weno_e75 = 0.75 * params->weno_eps;
   d.g_ext = params->g_ext;
   const double g = params->gamma;
   d.two_a = 2.0 * (2.0 * M_PI * sg * sg * sg / 3.0) * params->phi_sigma * g / (g - 3.0);
