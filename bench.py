@@ -37,7 +37,8 @@ HBM_PEAK_GBS = 8000.0
 # stage 1 reads f^n and writes f^(1) (16 + 16 B), stages 2 and 3 each read
 # f^(s-1) and f^n and write f^(s) (48 B); node fields and halo re-reads excluded
 BYTES_PER_UPDATE_STEP = 128.0
-KERNEL_NAMES = {16: "stage_kernel_mirror<{q},16>", 63: "stage_kernel_col<{q}>", 64: "stage_kernel<{q},64,8>"}
+KERNEL_NAMES = {0: "stage_kernel_mirror<{q},32>", 16: "stage_kernel_mirror<{q},16>",
+                63: "stage_kernel_col<{q}>", 64: "stage_kernel<{q},64,8>"}
 
 
 def cpu_baseline(c, n, u, T, target_s=8.0):
@@ -271,11 +272,14 @@ def copy_bandwidth(torch, dev, mib=1024, reps=10):
             "what": f"torch copy_ of {mib} MiB FP64, device to device"}
 
 
-def default_tile(nx, cus=256):
-    """The library's automatic tile choice: column tiles when they give at
-    least four wavefronts per CU, else narrow 16-node tiles."""
+def default_tile(nx, q, cus=256):
+    """The library's automatic tile choice: column tiles when they give more
+    than two and a half wavefronts per CU (q 24: one and a half), else narrow
+    16-node tiles while these fit one per CU; 0, the broad tiles, between."""
     nxs = [nx] if isinstance(nx, int) else list(nx)
-    return 63 if sum((v + 62) // 63 for v in nxs) >= 4 * cus else 16
+    if 2 * sum((v + 62) // 63 for v in nxs) > (5 if q < 24 else 3) * cus:
+        return 63
+    return 0 if q < 24 and sum((v + 15) // 16 for v in nxs) > cus else 16
 
 
 def measure(E, torch, dev, q, dx, dt, nx, n, u, T, steps, warmup, mode=None, tile=None, graph=True):
@@ -557,7 +561,7 @@ def main():
         c, n, u, T = workloads.slab_1d()
         mode, tile = args.exec_mode, args.tile
         if args.no_autotune:
-            mode, tile = E.EVLB_EXEC_PER_STAGE, default_tile(c["nx"])
+            mode, tile = E.EVLB_EXEC_PER_STAGE, default_tile(c["nx"], c["Q"])
         m = measure(E, torch, dev, c["Q"], c["dx"], c["dt"], c["nx"], n, u, T, args.slab_steps, args.slab_warmup,
                     mode, tile, graph=not args.no_graph)
         ent = {"config": {"workload": "slab_evaporation_1d", "nx": c["nx"], "q": c["Q"], "dx": c["dx"],
@@ -575,7 +579,7 @@ def main():
         Tb = np.concatenate([x[2] for x in systems])
         bmode = btile = None
         if args.no_autotune:
-            bmode, btile = E.EVLB_EXEC_PER_STAGE, default_tile(cb["nx_list"])
+            bmode, btile = E.EVLB_EXEC_PER_STAGE, default_tile(cb["nx_list"], cb["Q"])
         mb = measure(E, torch, dev, cb["Q"], cb["dx"], cb["dt"], cb["nx_list"], nb, ub, Tb,
                      args.batch_steps, 5, bmode, btile, graph=not args.no_graph)
         out["secondary"].append({

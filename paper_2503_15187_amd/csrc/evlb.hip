@@ -58,6 +58,7 @@ struct DevParams {
   const double* vel;   // [q]
   const double* meq;   // [q][q]
   const double* ntab;  // [NTAB] averaging weights and force taps
+  const double* pairs; // [q/2][2q] coefficients of a mirror pair (pair_table)
   const double* mx;    // [operands][64] MFMA operands of the mirror shape
   const double* dpm;   // [q][q]
   const double* savg;  // [2 ms + 1]
@@ -107,8 +108,8 @@ __device__ __forceinline__ double rcpn(double x) {
 // trip.
 __device__ __forceinline__ double wave_next(double v) {
   const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, 0x130, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), 0x130, 0xf, 0xf, false);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, 0x130, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), 0x130, 0xf, 0xf, true);
   return __builtin_bit_cast(double, (unsigned long long)(unsigned)lo | ((unsigned long long)(unsigned)hi << 32));
 }
 
@@ -1045,11 +1046,22 @@ __global__ __launch_bounds__(W * NG) void stage_kernel(DevParams P, StageArgs A)
 
 // ---------------------------------------------------------------------------
 // Column shape: one wavefront per tile of WC = 63 nodes, thread = node.  Each
-// thread keeps its node's F, G columns and Hermite moments in registers, so
-// the q x q contractions (equilibrium, momentum derivative) need no LDS
-// traffic and the velocity moments of the new state are a per-thread sum.
-// The 64 lanes compute the 64 WENO-5 faces of a row (face j between nodes
-// j-1 and j); a node's right face comes from the next lane by a shuffle.
+// thread keeps its node's F, G columns (as sums and differences over mirror
+// pairs of velocities) and Hermite moments in registers, so the contractions
+// (equilibrium, momentum derivative) need no LDS traffic and the velocity
+// moments of the new state are a per-thread sum.  The 64 lanes compute the 64
+// WENO-5 faces of a row (face j between nodes j-1 and j); a node's right face
+// comes from the next lane.
+//
+// An iteration forms the four values of a mirror pair (p_k, p_(Q-1-k)) of F and
+// G: both contractions split into even and odd halves, half the multiplies
+// and half the coefficients through the scalar cache, whose latency hides
+// behind two faces each.  Bound by vector issue at two wavefronts per SIMD
+// (the columns fill the registers, the tile a fifth or less of the LDS) and by
+// the latency of the state's loads, which no other wavefront covers at small
+// grids.  Requesting f_n an iteration ahead changed nothing.  A stage of 1.18 M
+// nodes, value by value with full contractions -> by mirror pairs:
+//   q 16  270 -> 224 us (4.0 TB/s of the state)   q 24  511 -> 350 us
 // ---------------------------------------------------------------------------
 constexpr int WC = 63;
 
@@ -1069,10 +1081,9 @@ struct SmemCol {
   double cf[MF_MAX];                 // EV1 force taps
 };
 
-template <int Q>
+template <int Q, bool FULL>
 __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile, SmemCol<Q>& S,
-                               const double* __restrict__ vel, const double* __restrict__ meq,
-                               const double* __restrict__ dpm) {
+                               const double* __restrict__ vel, const double* __restrict__ pairs) {
   const int lane = threadIdx.x;  // 0..63
   const int4 td = P.tiles[tile];
   const int off = td.x, nsys = td.y, i0 = td.z;
@@ -1178,18 +1189,22 @@ __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile,
     chv[i] = 1.0;
     Xv[i] = 1.0;
     if (cc < WC + 4) {
-      const int cn = cc + hn - 2;
-      double s0 = 0.0, s1 = 0.0;
-      int jj = -P.ms;
-      for (; jj + 1 <= P.ms; jj += 2) {
-        s0 += S.sav[jj + P.ms] * S.w.n[cn + jj];
-        s1 += S.sav[jj + 1 + P.ms] * S.w.n[cn + jj + 1];
+      // the averaging weights are even: pairs
+      const double* nc = &S.w.n[cc + hn - 2];
+      const double* sw = &S.sav[P.ms];
+      const double nn = nc[0];
+      double s0 = sw[0] * nn, s1 = 0.0;
+      int j = 1;
+      for (; j + 3 <= P.ms; j += 4) {
+        s0 += sw[j] * (nc[j] + nc[-j]);
+        s1 += sw[j + 1] * (nc[j + 1] + nc[-j - 1]);
+        s0 += sw[j + 2] * (nc[j + 2] + nc[-j - 2]);
+        s1 += sw[j + 3] * (nc[j + 3] + nc[-j - 3]);
       }
-      if (jj <= P.ms) s0 += S.sav[jj + P.ms] * S.w.n[cn + jj];
+      for (; j <= P.ms; ++j) s0 += sw[j] * (nc[j] + nc[-j]);
       const double eta = P.eta_c * (s0 + s1);
       const double om = 1.0 - eta;
       chv[i] = (2.0 - eta) * rcpn(2.0 * om * om * om);
-      const double nn = S.w.n[cn];
       Xv[i] = nn * nn * chv[i] * Tv[i];
     }
   }
@@ -1255,13 +1270,27 @@ __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile,
   a[0] = n;
   a[1] = n * u;
 #pragma unroll
-  for (int l = 1; l < Q - 1; ++l) a[l + 1] = u * a[l] + (double)l * (T - 1.0) * a[l - 1];
+  for (int l = 1; l < Q - 1; ++l) a[l + 1] = fma(u, a[l], (double)l * (T - 1.0) * a[l - 1]);
+  // even and odd parts of the columns over mirror pairs, f_j +- f_(Q-1-j)
+#pragma unroll
+  for (int j = 0; j < Q / 2; ++j) {
+    const double f0 = Fc[j], f1 = Fc[Q - 1 - j], g0 = Gc[j], g1 = Gc[Q - 1 - j];
+    Fc[j] = f0 + f1;
+    Fc[Q - 1 - j] = f0 - f1;
+    Gc[j] = g0 + g1;
+    Gc[Q - 1 - j] = g0 - g1;
+  }
 
-  // ---- 4. update, velocity by velocity -----------------------------------
-  double pm[6] = {0, 0, 0, 0, 0, 0};
+  // ---- 4. update, mirror pair by mirror pair ------------------------------
+  // out = ca f_n + bb f + cc L(f)
+  const double cc = A.rhs_mode ? 1.0 : A.beta * P.dt;
+  const double ca = A.rhs_mode || A.first ? 0.0 : A.alpha;
+  const double bb = A.rhs_mode ? 0.0 : (A.first ? A.alpha + A.beta : A.beta);
+  const bool base = !A.first && !A.rhs_mode && valid;
   const WenoK K = weno_k(P);
-  const bool adv = P.term_mask & EVLB_TERM_ADV;
-  const bool frc = P.term_mask & EVLB_TERM_FORCE;
+  // FULL: advection and force known to be on
+  const bool adv = FULL || (P.term_mask & EVLB_TERM_ADV);
+  const bool frc = FULL || (P.term_mask & EVLB_TERM_FORCE);
   const bool j0 = P.term_mask & EVLB_TERM_J0;
   const bool j1 = P.term_mask & EVLB_TERM_J1;
   // Shakhov relaxation and J1 of velocity k: -nu f_k + E_k c(xi) with
@@ -1269,87 +1298,115 @@ __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile,
   //   nu (1 + sS xi (xi^2/T - 3)) + pre (xi (A + 0.3 (xi^2/T - 3) B) + 0.6 (xi^2/T - 1) U),
   // for G,
   //   nu T (1 + sS xi (xi^2/T - 1)) + pre T (xi (A + 0.3 (xi^2/T - 1) B) + 0.2 (3 xi^2/T - 1) U),
-  // expanded in powers of xi.
-  const double nu0 = j0 ? nu : 0.0, sv = j0 ? nu * sS : 0.0;
-  const double pA = j1 ? pre * Ag : 0.0, pB = j1 ? pre * Bg : 0.0, pU = j1 ? pre * Ug : 0.0;
+  // expanded in powers of xi and scaled by cc.
+  const double nu0 = j0 ? cc * nu : 0.0, sv = nu0 * sS, pc = j1 ? cc * pre : 0.0;
+  const double pA = pc * Ag, pB = pc * Bg, pU = pc * Ug;
   const double cF0 = nu0 - 0.6 * pU, cF1 = pA - 3.0 * sv - 0.9 * pB;
   const double cF2 = 0.6 * pU * invT, cF3 = (sv + 0.3 * pB) * invT;
   const double cG0 = T * (nu0 - 0.2 * pU), cG1 = T * (pA - sv - 0.3 * pB);
   const double cG2 = 0.6 * pU, cG3 = sv + 0.3 * pB;
+  const double nub = bb - nu0, fx = cc * Fx, cdx = cc * P.inv_dx;
+  double pm[6] = {0, 0, 0, 0, 0, 0};
 #pragma unroll 1
-  for (int k = 0; k < Q; ++k) {
-    double Fb = 0.0, Gb = 0.0;
-    if (!A.first && !A.rhs_mode && valid) {
-      Fb = A.f_n[(long long)k * ntot + gnode];
-      Gb = A.f_n[(long long)(Q + k) * ntot + gnode];
+  for (int k = 0; k < Q / 2; ++k) {
+    // rows r = 0: F_k, 1: F_(Q-1-k), 2: G_k, 3: G_(Q-1-k); p_k < 0
+    const int kr[4] = {k, Q - 1 - k, Q + k, 2 * Q - 1 - k};
+    double fb[4] = {0, 0, 0, 0};
+    if (base) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) fb[r] = A.f_n[(long long)kr[r] * ntot + gnode];
     }
+    // face `lane`, between nodes lane - 1 and lane, upwind by the sign of p:
+    // columns lane + 1 .. lane + 5 from the right, lane .. lane + 4 from the left
+    double v[4][5];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int m = 0; m < 5; ++m) v[r][m] = S.f[kr[r]][lane + m + (r & 1 ? 0 : 1)];
+    const double own[4] = {v[0][2], v[1][3], v[2][2], v[3][3]};
+    // face less the one on the right, the next lane's (lane 63's is not used)
+    double d[4] = {0, 0, 0, 0};
+    auto face = [&](int r) {
+      const double h = r & 1 ? weno5(v[r][0], v[r][1], v[r][2], v[r][3], v[r][4], K)
+                             : weno5(v[r][4], v[r][3], v[r][2], v[r][1], v[r][0], K);
+      d[r] = h - wave_next(h);
+    };
+    // Scalar and LDS loads share a wait counter and scalar loads come back in
+    // any order, so a wait for one is a wait for all: the LDS reads first, then
+    // each half of the pair's coefficients goes out before two faces and is
+    // used behind them (32 scalar registers at a time).
+    asm volatile("" ::"v"(v[3][4]), "v"(v[2][4]), "v"(v[1][4]), "v"(v[0][4]));
+    __builtin_amdgcn_sched_barrier(0);
     const double pk = vel[k];
-    double LF = 0.0, LG = 0.0;
-    if (adv) {
-      // face `lane` of rows k (F) and Q + k (G); upwind by the sign of p_k
-      const bool pos = k >= Q / 2;
-      const int b0 = pos ? lane : lane + 5;
-      const int st = pos ? 1 : -1;
-      const double* fr = &S.f[k][0];
-      const double* gr = &S.f[Q + k][0];
-      const double hF = weno5(fr[b0], fr[b0 + st], fr[b0 + 2 * st], fr[b0 + 3 * st], fr[b0 + 4 * st], K);
-      const double hG = weno5(gr[b0], gr[b0 + st], gr[b0 + 2 * st], gr[b0 + 3 * st], gr[b0 + 4 * st], K);
-      const double hFr = wave_next(hF);  // lane 63's faces are not used
-      const double hGr = wave_next(hG);
-      LF = -pk * (hFr - hF) * P.inv_dx;
-      LG = -pk * (hGr - hG) * P.inv_dx;
-    }
-    double E0 = 0.0, E1 = 0.0;
-    const double* mrow = meq + k * Q;
-#pragma unroll
-    for (int l = 0; l < Q; l += 2) {
-      E0 += mrow[l] * a[l];
-      E1 += mrow[l + 1] * a[l + 1];
-    }
-    const double E = E0 + E1;
-    const double Fk = S.f[k][lane + HF];
-    const double Gk = S.f[Q + k][lane + HF];
+    const double* row = pairs + k * 2 * Q;
+    double dp[4] = {0, 0, 0, 0};
+    double cd[Q];
     if (frc) {
-      const double* drow = dpm + k * Q;
-      double dF0 = 0.0, dF1 = 0.0, dG0 = 0.0, dG1 = 0.0;
 #pragma unroll
-      for (int kk = 0; kk < Q; kk += 2) {
-        dF0 += drow[kk] * Fc[kk];
-        dF1 += drow[kk + 1] * Fc[kk + 1];
-        dG0 += drow[kk] * Gc[kk];
-        dG1 += drow[kk + 1] * Gc[kk + 1];
-      }
-      LF -= Fx * (dF0 + dF1);
-      LG -= Fx * (dG0 + dG1);
+      for (int j = 0; j < Q; ++j) cd[j] = row[Q + j];
     }
-    const double xi = pk - u;
-    const double qF = fma(fma(fma(cF3, xi, cF2), xi, cF1), xi, cF0);
-    const double qG = fma(fma(fma(cG3, xi, cG2), xi, cG1), xi, cG0);
-    LF = fma(E, qF, fma(-nu0, Fk, LF));
-    LG = fma(E, qG, fma(-nu0, Gk, LG));
-    double Fo, Go;
-    if (A.rhs_mode) {
-      Fo = LF;
-      Go = LG;
-    } else {
-      if (A.first) {
-        Fb = Fk;
-        Gb = Gk;
+    __builtin_amdgcn_sched_barrier(0);
+    if (adv) {
+      face(0);
+      face(1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (frc) {
+      // Dp f = odd +- even over mirror pairs
+      double fe = 0.0, fo = 0.0, ge = 0.0, go = 0.0;
+#pragma unroll
+      for (int j = 0; j < Q / 2; ++j) {
+        fe = fma(cd[j], Fc[j], fe);
+        fo = fma(cd[Q / 2 + j], Fc[Q - 1 - j], fo);
+        ge = fma(cd[j], Gc[j], ge);
+        go = fma(cd[Q / 2 + j], Gc[Q - 1 - j], go);
       }
-      Fo = A.alpha * Fb + A.beta * (Fk + P.dt * LF);
-      Go = A.alpha * Gb + A.beta * (Gk + P.dt * LG);
+      dp[0] = fo + fe;
+      dp[1] = fo - fe;
+      dp[2] = go + ge;
+      dp[3] = go - ge;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    double ce[Q];
+#pragma unroll
+    for (int j = 0; j < Q; ++j) ce[j] = row[j];
+    __builtin_amdgcn_sched_barrier(0);
+    if (adv) {
+      face(2);
+      face(3);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // E = even + odd over the Hermite moments
+    double ev = 0.0, od = 0.0;
+#pragma unroll
+    for (int j = 0; j < Q / 2; ++j) {
+      ev = fma(ce[j], a[2 * j], ev);
+      od = fma(ce[Q / 2 + j], a[2 * j + 1], od);
+    }
+    const double E[2] = {ev + od, ev - od};
+    const double cx = cdx * pk, x0 = pk - u, x1 = -pk - u;
+    const double q[4] = {fma(fma(fma(cF3, x0, cF2), x0, cF1), x0, cF0), fma(fma(fma(cF3, x1, cF2), x1, cF1), x1, cF0),
+                         fma(fma(fma(cG3, x0, cG2), x0, cG1), x0, cG0), fma(fma(fma(cG3, x1, cG2), x1, cG1), x1, cG0)};
+    double o[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      double t = fma(r & 1 ? -cx : cx, d[r], nub * own[r]);
+      t = fma(-fx, dp[r], t);
+      t = fma(E[r & 1], q[r], t);
+      o[r] = fma(ca, fb[r], t);
     }
     if (valid) {
-      A.f_out[(long long)k * ntot + gnode] = Fo;
-      A.f_out[(long long)(Q + k) * ntot + gnode] = Go;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) A.f_out[(long long)kr[r] * ntot + gnode] = o[r];
     }
+    const double sF = o[0] + o[1], tF = o[0] - o[1], sG = o[2] + o[3], tG = o[2] - o[3];
     const double p2 = pk * pk;
-    pm[0] += Fo;
-    pm[1] += pk * Fo;
-    pm[2] += p2 * Fo;
-    pm[3] += p2 * pk * Fo;
-    pm[4] += Go;
-    pm[5] += pk * Go;
+    pm[0] += sF;
+    pm[1] = fma(pk, tF, pm[1]);
+    pm[2] = fma(p2, sF, pm[2]);
+    pm[3] = fma(p2 * pk, tF, pm[3]);
+    pm[4] += sG;
+    pm[5] = fma(pk, tG, pm[5]);
   }
 
   // ---- 5. moments of the new state ----------------------------------------
@@ -1370,13 +1427,12 @@ __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile,
   __syncthreads();
 }
 
-template <int Q>
+template <int Q, bool FULL>
 __global__ __launch_bounds__(64) void stage_kernel_col(DevParams P, StageArgs A, const double* __restrict__ vel,
-                                                       const double* __restrict__ meq,
-                                                       const double* __restrict__ dpm) {
+                                                       const double* __restrict__ pairs) {
   __shared__ SmemCol<Q> S;
   // one tile per workgroup (the grid is the tile count)
-  if ((int)blockIdx.x < P.ntiles) stage_tile_col<Q>(P, A, xcd_tile(blockIdx.x, P.ntiles), S, vel, meq, dpm);
+  if ((int)blockIdx.x < P.ntiles) stage_tile_col<Q, FULL>(P, A, xcd_tile(blockIdx.x, P.ntiles), S, vel, pairs);
 }
 
 // Grid-wide barrier for the persistent kernel (all workgroups co-resident:
@@ -1439,8 +1495,7 @@ struct GroupShape {
   static constexpr int NT = W * NG;
   typedef Smem<Q, W, NG> Shared;
   __device__ static void prologue(const DevParams& P, Shared& S) { load_tables<Q, W, NG>(P, S); }
-  __device__ static void tile(const DevParams& P, const StageArgs& A, int t, Shared& S, const double*,
-                              const double*, const double*) {
+  __device__ static void tile(const DevParams& P, const StageArgs& A, int t, Shared& S, const double*, const double*) {
     stage_tile<Q, W, NG>(P, A, t, S);
   }
 };
@@ -1450,8 +1505,7 @@ struct MirrorShape {
   static constexpr int NT = Mirror<Q, W>::NT;
   typedef SmemM<Q, W> Shared;
   __device__ static void prologue(const DevParams&, Shared&) {}
-  __device__ static void tile(const DevParams& P, const StageArgs& A, int t, Shared& S, const double*,
-                              const double*, const double*) {
+  __device__ static void tile(const DevParams& P, const StageArgs& A, int t, Shared& S, const double*, const double*) {
     stage_tile_mirror<Q, W>(P, A, t, S);
   }
 };
@@ -1462,17 +1516,15 @@ struct ColumnShape {
   typedef SmemCol<Q> Shared;
   __device__ static void prologue(const DevParams&, Shared&) {}
   __device__ static void tile(const DevParams& P, const StageArgs& A, int t, Shared& S,
-                              const double* __restrict__ vel, const double* __restrict__ meq,
-                              const double* __restrict__ dpm) {
-    stage_tile_col<Q>(P, A, t, S, vel, meq, dpm);
+                              const double* __restrict__ vel, const double* __restrict__ pairs) {
+    stage_tile_col<Q, false>(P, A, t, S, vel, pairs);
   }
 };
 
 template <class SHAPE>
 __global__ __launch_bounds__(SHAPE::NT) void persistent_kernel(DevParams P, PersistArgs R,
                                                                const double* __restrict__ vel,
-                                                               const double* __restrict__ meq,
-                                                               const double* __restrict__ dpm) {
+                                                               const double* __restrict__ pairs) {
   __shared__ typename SHAPE::Shared S;
   SHAPE::prologue(P, S);
   const double a_s[3] = {0.0, 0.75, 1.0 / 3.0};
@@ -1491,7 +1543,7 @@ __global__ __launch_bounds__(SHAPE::NT) void persistent_kernel(DevParams P, Pers
       A.beta = b_s[s];
       A.first = s == 0;
       A.rhs_mode = 0;
-      for (int b = blockIdx.x; b < P.ntiles; b += gridDim.x) SHAPE::tile(P, A, xcd_tile(b, P.ntiles), S, vel, meq, dpm);
+      for (int b = blockIdx.x; b < P.ntiles; b += gridDim.x) SHAPE::tile(P, A, xcd_tile(b, P.ntiles), S, vel, pairs);
       if (!grid_barrier(P, gridDim.x, epoch++)) return;
     }
   }
@@ -1672,6 +1724,24 @@ std::vector<double> mirror_table(int q, const evlb::HostTables& t) {
   return x;
 }
 
+// Coefficients of the mirror pair (p_k, p_(q-1-k)), k < q / 2: meq[k] over the
+// even, then the odd Hermite moments; (Dp[k][j] + Dp[k][q-1-j]) / 2, then their
+// difference's half, j < q / 2.  (Dp f)_k and (Dp f)_(q-1-k) are odd +- even of
+// these over f_j -+ f_(q-1-j), for Dp[q-1-k][q-1-j] = -Dp[k][j].
+std::vector<double> pair_table(int q, const evlb::HostTables& t) {
+  std::vector<double> x;
+  for (int k = 0; k < q / 2; ++k) {
+    for (int o = 0; o < 2; ++o)
+      for (int j = 0; j < q / 2; ++j) x.push_back(t.meq[(size_t)k * q + 2 * j + o]);
+    for (int o = 0; o < 2; ++o)
+      for (int j = 0; j < q / 2; ++j) {
+        const double d0 = t.dpm[(size_t)k * q + j], d1 = t.dpm[(size_t)k * q + q - 1 - j];
+        x.push_back(0.5 * (o == 0 ? d0 + d1 : d0 - d1));
+      }
+  }
+  return x;
+}
+
 Layout make_layout(const evlb_params* p) {
   Layout L{};
   L.ntot = 0;
@@ -1690,7 +1760,7 @@ Layout make_layout(const evlb_params* p) {
   L.ntables = (size_t)(q + 2 * q * q + 2 * (2 * L.ms + 1) + 3 * mfa);
   off += align256(sizeof(double) * L.ntables);
   L.mx = off;
-  off += align256(sizeof(double) * (64 * (size_t)mirror_operands(q) + NTAB));
+  off += align256(sizeof(double) * (64 * (size_t)mirror_operands(q) + NTAB + (size_t)q * q));
   L.tiles_broad = off;
   off += align256(sizeof(int4) * (size_t)L.ntiles_broad);
   L.tiles_wide = off;
@@ -1792,7 +1862,11 @@ int launch_stage_mirror(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
 template <int Q>
 int launch_stage_col(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
   const DevParams P = params_for(c, WC);
-  hipLaunchKernelGGL((stage_kernel_col<Q>), dim3(P.ntiles), dim3(64), 0, st, P, A, P.vel, P.meq, P.dpm);
+  constexpr int full = EVLB_TERM_ADV | EVLB_TERM_FORCE;
+  if ((P.term_mask & full) == full)
+    hipLaunchKernelGGL((stage_kernel_col<Q, true>), dim3(P.ntiles), dim3(64), 0, st, P, A, P.vel, P.pairs);
+  else
+    hipLaunchKernelGGL((stage_kernel_col<Q, false>), dim3(P.ntiles), dim3(64), 0, st, P, A, P.vel, P.pairs);
   return hipGetLastError() == hipSuccess ? EVLB_OK : EVLB_EHIP;
 }
 
@@ -1814,9 +1888,8 @@ int launch_persistent(evlb_ctx* c, int width, double* f, int nsteps, hipStream_t
   hipLaunchKernelGGL(clear_barrier_kernel, dim3(1), dim3(64), 0, st, P);
   EVLB_HIP(hipGetLastError());
   const double* vel = P.vel;
-  const double* meq = P.meq;
-  const double* dpm = P.dpm;
-  void* args[] = {&P, &R, &vel, &meq, &dpm};
+  const double* pairs = P.pairs;
+  void* args[] = {&P, &R, &vel, &pairs};
   EVLB_HIP(hipLaunchCooperativeKernel((const void*)persistent_kernel<SHAPE>, dim3(grid), dim3(SHAPE::NT), args, 0, st));
   return EVLB_OK;
 }
@@ -1832,17 +1905,18 @@ int run_moments(evlb_ctx* c, const double* f, double* n, double* u, double* T, d
 
 // Tile shape of the per-stage launches: explicit, or by the number of tiles.
 // A stage in us on 256 CUs, narrow / broad / column:
-//   q 8    4096 nodes 4.7 / 5.0 / 11   5120 5.2 / 4.8 / 11   49152 17 / 12 / 13   65536 21 / 14.6 / 17
-//   q 16   4096 nodes 5.0 / 5.6 / 18   5120 5.7 / 5.5 / 18   49152 21 / 18 / 23   65536 26 / 23 / 28
-//   q 24   4096 nodes 5.7 / - / 30     8192 7.5 / - / 31     49152 35 / - / 44    65536 45 / - / 46
+//   q 8    4096 nodes 4.7 / 5.0 / 8.8   5120 5.2 / 4.8 / 8.8   40960 15 / 10.3 / 10.8   49152 17 / 11.7 / 11.0
+//   q 16   4096 nodes 5.0 / 5.6 / 12    5120 5.7 / 5.5 / 12    40960 18 / 15.8 / 15.5   49152 21 / 18.3 / 16.6
+//   q 24   4096 nodes 5.7 / - / 17      8192 7.5 / - / 17      24576 18.3 / - / 18.8    32768 23.6 / - / 20.1
 // Narrow tiles while they fill the CUs once: the stage is one tile's latency,
 // and a broad one's is longer.  Beyond that broad tiles for q 8 and 16, which
 // hold fewer halos and node fields formed twice (q 24 would need two
-// workgroups' lanes).  The column shape once it has four wavefronts per CU to
-// hide its chain of a node's work behind.
+// workgroups' lanes).  The column shape, one wavefront a tile with the fewest
+// instructions per value, from two and a half tiles per CU on, for q 24 one
+// and a half.
 int pick_width(const evlb_ctx* c) {
   if (c->p.tile_nodes) return c->p.tile_nodes;
-  if (c->L.ntiles_col >= 4 * c->cus) return WC;
+  if (2 * c->L.ntiles_col > (c->p.q < 24 ? 5 : 3) * c->cus) return WC;
   return c->p.q < 24 && c->L.ntiles_narrow > c->cus ? BROAD : NARROW;
 }
 
@@ -2242,6 +2316,9 @@ int evlb_init(const evlb_params* params, void* d_workspace, size_t ws_bytes, voi
   std::vector<double> mx = mirror_table(q, t);
   const size_t ntab = mx.size();
   mx.resize(ntab + NTAB, 0.0);
+  const size_t npairs = mx.size();
+  const std::vector<double> pairs = pair_table(q, t);
+  mx.insert(mx.end(), pairs.begin(), pairs.end());
   std::copy(t.savg.begin(), t.savg.end(), mx.begin() + ntab);
   if (L.mf > 0) std::copy(t.cfor.begin(), t.cfor.end(), mx.begin() + ntab + TAB_CF);
   std::vector<int4> tb, tw, tn, tc, ta;
@@ -2290,6 +2367,7 @@ int evlb_init(const evlb_params* params, void* d_workspace, size_t ws_bytes, voi
   d.meq = tab + q;
   d.mx = (const double*)(c->ws + L.mx);
   d.ntab = d.mx + ntab;
+  d.pairs = d.mx + npairs;
   d.dpm = tab + q + q * q;
   d.savg = tab + q + 2 * q * q;
   const int nc = (int)t.cfor.size();
