@@ -191,9 +191,17 @@ struct Smem {
   double cf[MF_MAX];               // EV1 force taps
 };
 
+// i mod n for indices at most 128 beyond either end; the loops only for the
+// systems smaller than that (n is uniform: a scalar branch), whose windows
+// wrap more than once.  The loops alone, two branches on the execution mask
+// each, cost 3% of a small stage (4.06 -> 3.92 us) and 2% of a middling one.
 __device__ __forceinline__ int wrapi(int i, int n) {
-  while (i < 0) i += n;
-  while (i >= n) i -= n;
+  i += i < 0 ? n : 0;
+  i -= i >= n ? n : 0;
+  if (n < 128) {
+    while (i < 0) i += n;
+    while (i >= n) i -= n;
+  }
   return i;
 }
 
@@ -601,7 +609,7 @@ __device__ __forceinline__ double row4_sum(double v) {
 // 4%).  A stage of 16-node tiles in a captured graph, where an empty launch is
 // 1.6 us, against one value per thread, full 16x16x4 products and the partial
 // velocity moments through LDS:
-//   256 nodes   q 8 5.93 -> 3.79   q 16 5.85 -> 4.06   q 24 6.24 -> 4.65 us
+//   256 nodes   q 8 5.93 -> 3.68   q 16 5.85 -> 3.92   q 24 6.24 -> 4.54 us
 // ---------------------------------------------------------------------------
 template <int Q, int W>
 struct Mirror {
