@@ -560,26 +560,6 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 constexpr int WN = 16;  // nodes per narrow tile
 
-// Sum of v over the four lanes j, j + 16, j + 32, j + 48 (every lane gets
-// it): the cross-row swaps of gfx950 exchange 16-lane rows (pairs 0-1, 2-3)
-// and 32-lane halves on the VALU.
-__device__ __forceinline__ double row4_sum(double v) {
-  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-  const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
-  const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-  const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-  const double a = __builtin_bit_cast(double, (unsigned long long)l16[0] | ((unsigned long long)h16[0] << 32));
-  const double c = __builtin_bit_cast(double, (unsigned long long)l16[1] | ((unsigned long long)h16[1] << 32));
-  const double s = a + c;  // rows 0 + 1 in rows 0, 1; rows 2 + 3 in rows 2, 3
-  const unsigned long long sb = __builtin_bit_cast(unsigned long long, s);
-  const unsigned slo = (unsigned)sb, shi = (unsigned)(sb >> 32);
-  const auto l32 = __builtin_amdgcn_permlane32_swap(slo, slo, false, false);
-  const auto h32 = __builtin_amdgcn_permlane32_swap(shi, shi, false, false);
-  const double x = __builtin_bit_cast(double, (unsigned long long)l32[0] | ((unsigned long long)h32[0] << 32));
-  const double y = __builtin_bit_cast(double, (unsigned long long)l32[1] | ((unsigned long long)h32[1] << 32));
-  return x + y;
-}
-
 // ---------------------------------------------------------------------------
 // Mirror shape: a tile of W nodes, wavefronts of column groups and four node
 // wavefronts.  A column wavefront takes NC = 128 / Q neighbouring nodes (Q = 24:
@@ -1634,7 +1614,7 @@ constexpr int BROAD = 1;  // launch shape code: broad mirror tiles
 
 struct Layout {
   size_t tables, mx, tiles_broad, tiles_wide, tiles_narrow, tiles_col, tiles_adj, f1, f2, momA, momB, status, tiso;
-  size_t adj_g, adj_mu2, adj_mu1, adj_fa, adj_fb, adj_mom, adj_part, adj_lam, total;
+  size_t adj_g, adj_mu2, adj_mu1, adj_fa, adj_mom, adj_part, adj_lam, total;
   long long ntot;
   int ntiles_broad, ntiles_wide, ntiles_narrow, ntiles_col, ntiles_adj, ms, mf;
   size_t ntables;
@@ -1796,7 +1776,6 @@ Layout make_layout(const evlb_params* p) {
     L.adj_mu2 = off; off += fbytes;
     L.adj_mu1 = off; off += fbytes;
     L.adj_fa = off; off += align256(sizeof(double) * NFA * (size_t)L.ntot);
-    L.adj_fb = off; off += align256(sizeof(double) * NFB * (size_t)L.ntot);
     L.adj_mom = off; off += mbytes;
     // parameter partials: per VJP one slot per field-adjoint tile (16 nodes) and per node tile, for two
     // steps (a step's partials are summed while the next step runs)
@@ -2041,7 +2020,6 @@ int launch_vjp(evlb_ctx* c, const double* f, const double* mom, const double* v,
   A.v = v;
   A.gdir = (double*)(c->ws + c->L.adj_g);
   A.fa = (double*)(c->ws + c->L.adj_fa);
-  A.fb = (double*)(c->ws + c->L.adj_fb);
   A.out = out;
   A.X1 = X1;
   A.X2 = X2;
@@ -2065,11 +2043,11 @@ int launch_vjp(evlb_ctx* c, const double* f, const double* mom, const double* v,
   A.rslots = nslots;
   A.rdp = dparams;
   A.part = part + (size_t)vjp_index * 2 * (ntn + nta);
-  hipLaunchKernelGGL((adj_fields_kernel<Q>), dim3(ntn + (sum_prev ? 1 : 0)), dim3(WN * Q), 0, st, Pn, A);
+  hipLaunchKernelGGL((adj_fields_kernel<Q>), dim3(ntn + (sum_prev ? 1 : 0)), dim3(WN * Q + 256), 0, st, Pn, A);
   EVLB_HIP(hipGetLastError());
   A.rpart = nullptr;
   A.part = part + ((size_t)vjp_index * (ntn + nta) + ntn) * 2;
-  hipLaunchKernelGGL((adj_column_kernel<Q>), dim3(nta * (2 * Q / NCW)), dim3(64 * NCW), 0, st, P, A,
+  hipLaunchKernelGGL((adj_column_kernel<Q>), dim3(nta * (2 * Q / NCR)), dim3(64 * NCW), 0, st, P, A,
                      final_reduce ? 1 : 0, (const double*)part, nslots, dparams);
   EVLB_HIP(hipGetLastError());
   return EVLB_OK;
