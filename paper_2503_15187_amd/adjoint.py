@@ -2,13 +2,15 @@
 
 Rollout (a torch.autograd.Function) advances a state nsteps TVD-RK3 steps
 and returns the final state together with the history of the mass flux
-sum_k p_k F_k through one node after every step.  The forward pass keeps a
-checkpoint every ceil(sqrt(nsteps)) steps.  The backward pass re-runs each
-segment from its checkpoint with evlb_step_record (states and stage states
-kept) and transposes it with evlb_adjoint_record, walking the segments in
-reverse, the recomputation of the next segment on a second context and
-stream overlapping the transposition of the current one; it returns the gradients with respect to the initial state and to
-the parameters phi_sigma and sigma (the latter two enter as 0-d tensors whose
+sum_k p_k F_k through one node after every step.  A run whose record (states
+and stage states of every step) is small keeps it, and the backward pass
+transposes it with evlb_adjoint_record.  Of a larger one the forward pass
+keeps a checkpoint every ceil(sqrt(nsteps)) steps; the backward pass re-runs
+each segment from its checkpoint with evlb_step_record and transposes it,
+walking the segments in reverse, the recomputation of the next segment on a
+second context and stream overlapping the transposition of the current one.
+It returns the gradients with respect to the initial state and to the
+parameters phi_sigma and sigma (the latter two enter as 0-d tensors whose
 values must equal the context's; they only carry the gradient).
 
 Equilibrium maps (n, u, T) fields to the initial reduced Maxwellian with
@@ -33,42 +35,65 @@ class Equilibrium(torch.autograd.Function):
         return g[0], g[1], g[2], None
 
 
+# Largest record that a run keeps until its backward pass, if it is also at most
+# 1/32 of the device's free memory (many runs may be alive at once).  Keeping it
+# saves the recomputation, a third of the backward pass's launches, whose
+# submission bounds small systems: gradients of 64 steps on 2048 nodes (q 16, a
+# record of 115 MB) take 3.0 ms with it and 4.0 ms from checkpoints.
+RECORD_BYTES = 512 << 20
+
+
+def segment_steps(solver, nsteps, device):
+    """Steps between checkpoints, unless the caller gives them: all of them
+    if their record is small enough to be kept, else ceil(sqrt(nsteps))."""
+    nbytes = 8 * (nsteps + 1) * solver.record_doubles()
+    if nbytes <= RECORD_BYTES and 32 * nbytes <= torch.cuda.mem_get_info(device)[0]:
+        return max(1, nsteps)
+    return max(1, int(math.ceil(math.sqrt(nsteps))))
+
+
 class Rollout(torch.autograd.Function):
     @staticmethod
     def forward(ctx, f0, phi, sigma, solver, nsteps, flux_node, every=None):
         nsteps = int(nsteps)
-        every = int(every) if every else max(1, int(math.ceil(math.sqrt(nsteps))))
+        keep = not every
+        every = int(every) if every else segment_steps(solver, nsteps, f0.device)
+        keep = keep and 0 < nsteps <= every
         dev = f0.device
         vel = torch.tensor(solver.velocities, dtype=torch.float64, device=dev)
         rec = solver.record_buffer(every)
         R = rec.numel() // (every + 1)
         N = solver.n_tot
-        # offsets of F_k(flux_node) inside a record, k = 0..q-1
-        kofs = torch.arange(solver.q, device=dev) * N + flux_node
+        node = int(flux_node)
         f = f0.detach().contiguous()
         ckpt = {}
         flux = torch.empty(nsteps, dtype=torch.float64, device=dev)
         for start in range(0, nsteps, every):
             seg = min(every, nsteps - start)
-            ckpt[start] = f.clone()
+            if not keep:
+                ckpt[start] = f.clone()
             solver.step_record(f, seg, rec)
-            idx = (torch.arange(1, seg + 1, device=dev) * R)[:, None] + kofs[None, :]
-            flux[start:start + seg] = rec[idx] @ vel
+            # F_k(node) of the states 1 .. seg inside the record, k = 0 .. q - 1
+            flux[start:start + seg] = rec.as_strided((seg, solver.q), (R, N), R + node) @ vel
             f = solver.record_state(rec, seg).clone()
         ctx.solver, ctx.nsteps, ctx.every, ctx.flux_node = solver, nsteps, every, flux_node
-        ctx.ckpt, ctx.vel = ckpt, vel
+        ctx.ckpt, ctx.rec, ctx.vel = ckpt, rec if keep else None, vel
+        ctx.shape = f.shape
         return f, flux
 
     @staticmethod
     def backward(ctx, g_f, g_flux):
         solver, nsteps, every, node = ctx.solver, ctx.nsteps, ctx.every, ctx.flux_node
-        lam = torch.zeros_like(ctx.ckpt[0]) if g_f is None else g_f.detach().clone().contiguous()
+        lam = ctx.vel.new_zeros(ctx.shape) if g_f is None else g_f.detach().clone().contiguous()
         obs = w = None
         if g_flux is not None:
             obs = torch.zeros_like(lam)
             obs[0, :, node] = ctx.vel
             w = g_flux.detach().contiguous()
         dparams = torch.zeros(2, dtype=torch.float64, device=lam.device)
+        if ctx.rec is not None:
+            solver.adjoint_record(ctx.rec, nsteps, lam, dparams, obs, w)
+            return lam, dparams[0], dparams[1], None, None, None, None
         # The segments in reverse.  The recomputation of segment i + 1 (a
         # second context on a second stream, into the other record buffer)
         # runs while segment i is transposed: the two chains of small

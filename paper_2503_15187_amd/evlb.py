@@ -330,9 +330,13 @@ class Solver:
         evlb_adjoint_step(self.ctx, f_n, lam_np1, lam_n, dparams, stream)
         return lam_n
 
+    def record_doubles(self):
+        """Size of the record of one step (evlb_step_record), in doubles."""
+        return evlb_record_doubles(self.ctx)
+
     def record_buffer(self, nsteps):
         """Device buffer for evlb_step_record of nsteps steps."""
-        return torch.empty((nsteps + 1) * evlb_record_doubles(self.ctx), dtype=torch.float64, device=self.device)
+        return torch.empty((nsteps + 1) * self.record_doubles(), dtype=torch.float64, device=self.device)
 
     def record_state(self, rec, j):
         """View of the state f^j inside a record buffer."""

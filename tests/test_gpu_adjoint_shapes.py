@@ -69,3 +69,29 @@ def test_tile_edges_dot_product(Q, cells, r_cut, force, mask):
             F1, G1 = step1d.rk3_step(f[0].astype(complex), f[1].astype(complex), tc)
             ref += (np.sum(lam[0] * F1) + np.sum(lam[1] * G1)).imag / H
         assert abs(float(dpar[i]) - ref) <= 1e-10 * max(1.0, abs(ref)), (which, float(dpar[i]), ref)
+
+
+@pytest.mark.parametrize("nsteps", [1, 2, 9])
+def test_kept_record_and_checkpoints_agree(nsteps, monkeypatch):
+    """The rollout's gradients from its kept record, and from checkpoints (a
+    limit of no bytes): the same states are transposed, so only the order of
+    the parameter sums and of the flux product may differ; and a second
+    backward pass over the same graph repeats the first."""
+    from paper_2503_15187_amd import adjoint as AD
+    print(f"rollout record nsteps={nsteps}", flush=True)
+    N, dx = 150, 1 / 4
+    dt = 0.2 * dx / 6.7
+    s = E.Solver(16, dx, dt, N, adjoint=1)
+    x = torch.arange(N, device="cuda", dtype=torch.float64) / N
+    out = []
+    for limit in (AD.RECORD_BYTES, 0):
+        monkeypatch.setattr(AD, "RECORD_BYTES", limit)
+        n0 = (0.3 * (1 + 0.1 * torch.sin(2 * np.pi * x))).requires_grad_(True)
+        par = [torch.ones((), device="cuda", dtype=torch.float64, requires_grad=True) for _ in range(2)]
+        L = AD.slab_loss(n0, *par, s, nsteps, 40, dt, dx, 0.3 + 0 * x, 0.6 + 0 * x)
+        g = torch.autograd.grad(L, [n0, *par], retain_graph=True)
+        for a, b in zip(g, torch.autograd.grad(L, [n0, *par])):
+            assert torch.equal(a, b)
+        out.append([L.detach(), *g])
+    for a, b in zip(*out):
+        assert float((a - b).abs().max()) <= 1e-12 * float(b.abs().max())
