@@ -69,6 +69,7 @@ struct DevParams {
   const int4* tiles;   // {system offset, system nodes, tile start, 0}
   int ntiles;
   int single;          // one system: tile t starts at node t * width
+  int onex;            // small grid: all workgroups on one XCD (grid_index)
   int ms, mf, hn;
   long long ntot;
   double dx, inv_dx, dt;
@@ -1010,6 +1011,20 @@ __device__ __forceinline__ int xcd_tile(int b, int ntiles) {
   return x * q + min(x, r) + i;
 }
 
+// A grid of at most one workgroup per CU of an XCD runs on one alone: eight
+// times as many are launched and those not on the first end at once.  The
+// halos and moments that a stage reads then lie in the L2 that the previous
+// stage wrote; from another XCD's they come over the memory side, a third of
+// the load phase.  A stage of 256 nodes in a captured graph, spread over the
+// XCDs -> on one: q 8 3.68 -> 3.42, q 16 3.91 -> 3.58, q 24 4.53 -> 4.23 us;
+// with two workgroups per CU (1024 nodes, q 16) 3.91 -> 4.65.  The adjoint's
+// kernels, longer chains of which the loads are a smaller part, gain nothing.
+// Index of the workgroup in the grid, negative: not one of the grid's.
+__device__ __forceinline__ int grid_index(const DevParams& P) {
+  const int b = blockIdx.x;
+  return P.onex ? (b & 7 ? -1 : b >> 3) : b;
+}
+
 template <int Q, int W>
 __global__ __launch_bounds__((Mirror<Q, W>::NT)) void stage_kernel_mirror(DevParams P, StageArgs A) {
   __shared__ SmemM<Q, W> S;
@@ -1022,7 +1037,8 @@ __global__ __launch_bounds__((Mirror<Q, W>::NT)) void stage_kernel_mirror(DevPar
   asm volatile("" ::"s"(A.f_prev), "s"(A.f_n), "s"(A.f_out), "s"(A.mom_in), "s"(A.mom_out), "s"(A.alpha),
                "s"(A.beta), "s"(A.first), "s"(A.rhs_mode));
   // one tile per workgroup (the grid is the tile count)
-  if ((int)blockIdx.x < P.ntiles) stage_tile_mirror<Q, W>(P, A, xcd_tile(blockIdx.x, P.ntiles), S);
+  const int b = grid_index(P);
+  if (b >= 0 && b < P.ntiles) stage_tile_mirror<Q, W>(P, A, P.onex ? b : xcd_tile(b, P.ntiles), S);
 }
 
 template <int Q, int W, int NG>
@@ -1539,12 +1555,13 @@ __global__ __launch_bounds__(SHAPE::NT) void persistent_kernel(DevParams P, Pers
 
 // Moments of a state, one thread per node (also the entry moments of a step).
 template <int Q>
-__global__ __launch_bounds__(256) void moments_kernel(DevParams P, const double* __restrict__ f,
+__global__ __launch_bounds__(64) void moments_kernel(DevParams P, const double* __restrict__ f,
                                                       double* __restrict__ n_out, double* __restrict__ u_out,
                                                       double* __restrict__ T_out, double* __restrict__ q_out,
                                                       int stage_input) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P.ntot) return;
+  const int b = grid_index(P);
+  const long long i = (long long)b * 64 + threadIdx.x;
+  if (b < 0 || i >= P.ntot) return;
   const long long nt = P.ntot;
   double F[Q], G[Q];
   double n = 0.0, m1 = 0.0;
@@ -1814,11 +1831,18 @@ template <> struct WideNG<8> { static constexpr int v = 4; };
 template <> struct WideNG<16> { static constexpr int v = 8; };
 template <> struct WideNG<24> { static constexpr int v = 8; };
 
+// whether the narrow tiles, at one per CU, fit one XCD (see grid_index)
+bool one_xcd(const evlb_ctx* c) { return 8 * c->L.ntiles_narrow <= c->cus; }
+
+// workgroups to launch for a grid of n
+unsigned grid_of(const DevParams& P, int n) { return P.onex ? 8u * (unsigned)(n - 1) + 1u : (unsigned)n; }
+
 DevParams params_for(const evlb_ctx* c, int w) {
   DevParams P = c->dp;
   if (w == NARROW) {
     P.tiles = (const int4*)(c->ws + c->L.tiles_narrow);
     P.ntiles = c->L.ntiles_narrow;
+    P.onex = one_xcd(c);
   } else if (w == BROAD) {
     P.tiles = (const int4*)(c->ws + c->L.tiles_broad);
     P.ntiles = c->L.ntiles_broad;
@@ -1842,7 +1866,7 @@ int launch_stage(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
 template <int Q, int W>
 int launch_stage_mirror(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
   const DevParams P = params_for(c, W == NARROW ? NARROW : BROAD);
-  hipLaunchKernelGGL((stage_kernel_mirror<Q, W>), dim3(P.ntiles), dim3(Mirror<Q, W>::NT), 0, st, P, A);
+  hipLaunchKernelGGL((stage_kernel_mirror<Q, W>), dim3(grid_of(P, P.ntiles)), dim3(Mirror<Q, W>::NT), 0, st, P, A);
   return hipGetLastError() == hipSuccess ? EVLB_OK : EVLB_EHIP;
 }
 
@@ -1885,8 +1909,10 @@ template <int Q>
 int run_moments(evlb_ctx* c, const double* f, double* n, double* u, double* T, double* q, hipStream_t st,
                 int stage_input = 1) {
   const long long nt = c->L.ntot;
-  const int blocks = (int)((nt + 255) / 256);
-  hipLaunchKernelGGL((moments_kernel<Q>), dim3(blocks), dim3(256), 0, st, c->dp, f, n, u, T, q, stage_input);
+  DevParams P = c->dp;
+  P.onex = one_xcd(c);
+  hipLaunchKernelGGL((moments_kernel<Q>), dim3(grid_of(P, (int)((nt + 63) / 64))), dim3(64), 0, st, P, f, n, u, T, q,
+                     stage_input);
   return hipGetLastError() == hipSuccess ? EVLB_OK : EVLB_EHIP;
 }
 

@@ -95,3 +95,22 @@ def test_broad_terms_and_windows(mask, cells, r_cut):
             assert not np.any(L)
         else:
             check(L[:, :, off:off + N], ref, 1e-11, what=f"{N} at {off}")
+
+
+# 512 nodes are the last grid kept on one XCD (32 tiles on 256 CUs), 513 the
+# first beyond it; 9 and 16: one tile
+@pytest.mark.parametrize("N", [9, 16, 500, 512, 513, 530])
+def test_one_xcd(N):
+    print(f"1D one XCD N={N}", flush=True)
+    dt = 0.2 * DX / REACH[16]
+    tb = step1d.Tables(Params(Q=16, dx=DX, dt=dt))
+    F, G = moving_state(N, tb)
+    s = E.Solver(16, DX, dt, N)
+    f = td(np.stack([F, G]))
+    ref = step1d.moments(F, G, tb)
+    got = s.moments(f).cpu().numpy()
+    for i in range(4):
+        assert np.max(np.abs(got[i] - ref[i])) <= 1e-13 * np.max(np.abs(ref[i])) + 1e-16, i
+    s.step(f, 2)
+    check(f.cpu().numpy(), step1d.run(F, G, tb, 2), 1e-11, steps=2, what=str(N))
+    assert s.status() == 0
