@@ -116,13 +116,15 @@ __device__ __forceinline__ double wave_next(double v) {
 
 // Constants of the faces; the plain numbers in scalar registers, for as
 // literals the compiler puts them into two-operand fused multiply-adds, each
-// behind a register copy.
+// behind a register copy.  (Not volatile: behind a volatile statement the
+// compiler no longer reads uniform tables through the scalar cache, which
+// doubled the wide kernel's registers and time.)
 struct WenoK {
   double e3, e75, m275, m125, p25;
 };
 __device__ __forceinline__ WenoK weno_k(const DevParams& P) {
   WenoK K{P.weno_e3, P.weno_e75, -2.75, -1.25, 2.5};
-  asm volatile("" : "+s"(K.m275), "+s"(K.m125), "+s"(K.p25));
+  asm("" : "+s"(K.m275), "+s"(K.m125), "+s"(K.p25));
   return K;
 }
 
