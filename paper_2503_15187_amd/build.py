@@ -22,6 +22,8 @@ def build(verbose=False, extra_flags=()):
     tmp = LIB + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           # leading kernel arguments in scalar registers at a wavefront's start
+           "-mllvm", "-amdgpu-kernarg-preload-count=16",
            "-I", os.path.join(ROOT, "include"), "-o", tmp, *SOURCES, *extra_flags]
     if verbose:
         print(" ".join(cmd), flush=True)

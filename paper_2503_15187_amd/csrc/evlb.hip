@@ -592,7 +592,9 @@ constexpr int WN = 16;  // nodes per narrow tile
 // 4%).  A stage of 16-node tiles in a captured graph, where an empty launch is
 // 1.6 us, against one value per thread, full 16x16x4 products and the partial
 // velocity moments through LDS:
-//   256 nodes   q 8 5.93 -> 3.68   q 16 5.85 -> 3.92   q 24 6.24 -> 4.54 us
+//   256 nodes   q 8 5.93 -> 3.33   q 16 5.85 -> 3.46   q 24 6.24 -> 4.14 us
+// (with the loads' side of it on one XCD, see grid_index, and the leading
+// arguments preloaded, see stage_kernel_mirror; 3.68, 3.92 and 4.54 without).
 // ---------------------------------------------------------------------------
 template <int Q, int W>
 struct Mirror {
@@ -692,13 +694,6 @@ __device__ void stage_tile_mirror(const DevParams& P, const StageArgs& A, int ti
   const long long ntot = P.ntot;
   const int hn = P.hn;
   const bool adv = P.term_mask & EVLB_TERM_ADV, frc = P.term_mask & EVLB_TERM_FORCE;
-  // out = ca f_n + bb f + cc L(f)
-  const double cc = A.rhs_mode ? 1.0 : A.beta * P.dt;
-  const double ca = A.rhs_mode || A.first ? 0.0 : A.alpha;
-  const double bb = A.rhs_mode ? 0.0 : (A.first ? A.alpha + A.beta : A.beta);
-
-  const WenoK K = weno_k(P);
-
   // ---- load: one batch of global loads, then the LDS writes ----------------
   // rows of f: LPR lanes a row, NT / LPR rows at a time
   constexpr int FW = W + 2 * HF, LPR = FW <= 32 ? 32 : 64, RPB = NT / LPR, LF = (2 * Q + RPB - 1) / RPB;
@@ -728,6 +723,21 @@ __device__ void stage_tile_mirror(const DevParams& P, const StageArgs& A, int ti
     ov[i] = 0.0;
     if (tid + i * NT < 64 * M::NOP) ov[i] = P.mx[tid + i * NT];
   }
+  // the other arguments into scalar registers before the first branch: one
+  // round trip, behind those loads, instead of one at each first use
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::"s"(P.vel), "s"(P.ntab), "s"(P.status), "s"(P.ms), "s"(P.mf), "s"(P.force_model),
+               "s"(P.term_mask));
+  asm volatile("" ::"s"(P.inv_dx), "s"(P.dt), "s"(P.b), "s"(P.eta_c), "s"(P.mu0c), "s"(P.weno_e3), "s"(P.weno_e75),
+               "s"(P.g_ext), "s"(P.two_a), "s"(P.kappa), "s"(P.T_iso), "s"(P.tiso));
+  asm volatile("" ::"s"(A.f_n), "s"(A.f_out), "s"(A.mom_out), "s"(A.alpha), "s"(A.beta), "s"(A.first),
+               "s"(A.rhs_mode));
+  // out = ca f_n + bb f + cc L(f)
+  const double cc = A.rhs_mode ? 1.0 : A.beta * P.dt;
+  const double ca = A.rhs_mode || A.first ? 0.0 : A.alpha;
+  const double bb = A.rhs_mode ? 0.0 : (A.first ? A.alpha + A.beta : A.beta);
+
+  const WenoK K = weno_k(P);
   // node wavefront 0: the tables; 1: u and T of the tile +-2; 2: q of its nodes
   constexpr int LT = (NTAB + 63) / 64;
   double uv, Tv, qv, tv[LT];
@@ -1027,17 +1037,28 @@ __device__ __forceinline__ int grid_index(const DevParams& P) {
   return P.onex ? (b & 7 ? -1 : b >> 3) : b;
 }
 
+// The leading arguments are what the first loads need: the build has the
+// compiler ask for them in scalar registers at a wavefront's start (kernel
+// argument preload, up to 14 dwords), so that these loads leave before the
+// rest of the arguments, 400 bytes in memory, have come.  A stage of 256 nodes
+// launched call by call: q 8 3.67 -> 3.47, q 16 3.77 -> 3.60, q 24 4.40 -> 4.22
+// us (without the preload, 0.17 us slower than before).  tiles: null for a
+// single system; 32 bits hold the node count of any state that fits.
 template <int Q, int W>
-__global__ __launch_bounds__((Mirror<Q, W>::NT)) void stage_kernel_mirror(DevParams P, StageArgs A) {
+__global__ __launch_bounds__((Mirror<Q, W>::NT)) void stage_kernel_mirror(const double* f_prev, const double* mom_in,
+                                                                           const int4* tiles, const double* mx,
+                                                                           int ntot, int hn, int ntiles, int onex,
+                                                                           DevParams P, StageArgs A) {
   __shared__ SmemM<Q, W> S;
-  // every kernel argument into SGPRs before the first branch: one scalar
-  // round trip at entry instead of one at each first use
-  asm volatile("" ::"s"(P.mx), "s"(P.vel), "s"(P.ntab), "s"(P.tiles), "s"(P.status), "s"(P.ntiles), "s"(P.single),
-               "s"(P.ms), "s"(P.mf), "s"(P.hn), "s"(P.ntot), "s"(P.force_model), "s"(P.term_mask));
-  asm volatile("" ::"s"(P.inv_dx), "s"(P.dt), "s"(P.b), "s"(P.eta_c), "s"(P.mu0c), "s"(P.weno_e3), "s"(P.weno_e75),
-               "s"(P.g_ext), "s"(P.two_a), "s"(P.kappa), "s"(P.T_iso), "s"(P.tiso));
-  asm volatile("" ::"s"(A.f_prev), "s"(A.f_n), "s"(A.f_out), "s"(A.mom_in), "s"(A.mom_out), "s"(A.alpha),
-               "s"(A.beta), "s"(A.first), "s"(A.rhs_mode));
+  A.f_prev = f_prev;
+  A.mom_in = mom_in;
+  P.tiles = tiles;
+  P.mx = mx;
+  P.ntot = ntot;
+  P.hn = hn;
+  P.ntiles = ntiles;
+  P.single = tiles == nullptr;
+  P.onex = onex;
   // one tile per workgroup (the grid is the tile count)
   const int b = grid_index(P);
   if (b >= 0 && b < P.ntiles) stage_tile_mirror<Q, W>(P, A, P.onex ? b : xcd_tile(b, P.ntiles), S);
@@ -1557,10 +1578,13 @@ __global__ __launch_bounds__(SHAPE::NT) void persistent_kernel(DevParams P, Pers
 
 // Moments of a state, one thread per node (also the entry moments of a step).
 template <int Q>
-__global__ __launch_bounds__(64) void moments_kernel(DevParams P, const double* __restrict__ f,
+__global__ __launch_bounds__(64) void moments_kernel(const double* __restrict__ f, const double* __restrict__ vel,
+                                                     int ntot, int onex, DevParams P,
                                                       double* __restrict__ n_out, double* __restrict__ u_out,
                                                       double* __restrict__ T_out, double* __restrict__ q_out,
                                                       int stage_input) {
+  P.onex = onex;
+  P.ntot = ntot;
   const int b = grid_index(P);
   const long long i = (long long)b * 64 + threadIdx.x;
   if (b < 0 || i >= P.ntot) return;
@@ -1572,13 +1596,13 @@ __global__ __launch_bounds__(64) void moments_kernel(DevParams P, const double* 
     F[k] = f[k * nt + i];
     G[k] = f[(Q + k) * nt + i];
     n += F[k];
-    m1 += P.vel[k] * F[k];
+    m1 += vel[k] * F[k];
   }
   const double u = m1 / n;
   double e = 0.0, q = 0.0;
 #pragma unroll
   for (int k = 0; k < Q; ++k) {
-    const double xi = P.vel[k] - u;
+    const double xi = vel[k] - u;
     const double ek = 0.5 * xi * xi * F[k] + G[k];
     e += ek;
     q += xi * ek;
@@ -1868,7 +1892,8 @@ int launch_stage(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
 template <int Q, int W>
 int launch_stage_mirror(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
   const DevParams P = params_for(c, W == NARROW ? NARROW : BROAD);
-  hipLaunchKernelGGL((stage_kernel_mirror<Q, W>), dim3(grid_of(P, P.ntiles)), dim3(Mirror<Q, W>::NT), 0, st, P, A);
+  hipLaunchKernelGGL((stage_kernel_mirror<Q, W>), dim3(grid_of(P, P.ntiles)), dim3(Mirror<Q, W>::NT), 0, st, A.f_prev, A.mom_in,
+                     P.single ? nullptr : P.tiles, P.mx, (int)P.ntot, P.hn, P.ntiles, P.onex, P, A);
   return hipGetLastError() == hipSuccess ? EVLB_OK : EVLB_EHIP;
 }
 
@@ -1913,8 +1938,8 @@ int run_moments(evlb_ctx* c, const double* f, double* n, double* u, double* T, d
   const long long nt = c->L.ntot;
   DevParams P = c->dp;
   P.onex = one_xcd(c);
-  hipLaunchKernelGGL((moments_kernel<Q>), dim3(grid_of(P, (int)((nt + 63) / 64))), dim3(64), 0, st, P, f, n, u, T, q,
-                     stage_input);
+  hipLaunchKernelGGL((moments_kernel<Q>), dim3(grid_of(P, (int)((nt + 63) / 64))), dim3(64), 0, st, f, P.vel,
+                     (int)nt, P.onex, P, n, u, T, q, stage_input);
   return hipGetLastError() == hipSuccess ? EVLB_OK : EVLB_EHIP;
 }
 
@@ -2071,12 +2096,15 @@ int launch_vjp(evlb_ctx* c, const double* f, const double* mom, const double* v,
   A.rslots = nslots;
   A.rdp = dparams;
   A.part = part + (size_t)vjp_index * 2 * (ntn + nta);
-  hipLaunchKernelGGL((adj_fields_kernel<Q>), dim3(ntn + (sum_prev ? 1 : 0)), dim3(WN * Q + 256), 0, st, Pn, A);
+  hipLaunchKernelGGL((adj_fields_kernel<Q>), dim3(ntn + (sum_prev ? 1 : 0)), dim3(WN * Q + 256), 0, st, A.f, A.mom, A.v,
+                     Pn.single ? nullptr : Pn.tiles, (int)Pn.ntot, Pn.hn, ntn, Pn, A);
   EVLB_HIP(hipGetLastError());
   A.rpart = nullptr;
   A.part = part + ((size_t)vjp_index * (ntn + nta) + ntn) * 2;
-  hipLaunchKernelGGL((adj_column_kernel<Q>), dim3(nta * (2 * Q / NCR)), dim3(64 * NCW), 0, st, P, A,
-                     final_reduce ? 1 : 0, (const double*)part, nslots, dparams);
+  hipLaunchKernelGGL((adj_column_kernel<Q>), dim3(nta * (2 * Q / NCR)), dim3(64 * NCW), 0, st, A.f, A.mom, A.v, A.fa,
+                     P.single ? nullptr : P.tiles, (int)P.ntot, nta, P.ms,
+                     P.force_model == EVLB_FORCE_EV1 ? P.mf : 0, P, A, final_reduce ? 1 : 0, (const double*)part,
+                     nslots, dparams);
   EVLB_HIP(hipGetLastError());
   return EVLB_OK;
 }
