@@ -583,11 +583,18 @@ __global__ __launch_bounds__(SH::NT) void fields_kernel(Dev D, const double* __r
 // wavefront's 16 velocities of a node are one 128-byte line, read as two
 // halves by consecutive loads.
 //
-// What bounds it: the instructions issued per row (four wavefronts per SIMD).
-// Against a version with 16 x 16 x 4 matrix instructions, right faces by DPP,
-// per-lane coefficients and addresses formed every row, this one runs a
-// 1024 x 1024 step (three stages and the entry sums) in 13.4 instead of 16.4
-// ms and 333 x 270 in 1.64 instead of 2.09 ms per step.
+// What bounds it: the instructions issued per row (four wavefronts per SIMD)
+// and, beside them, the address lookups of the march's loads and stores: lanes
+// of one instruction lie on 8 nodes' lines, neighbours never on one, so that an
+// instruction takes some 54 lookups (the unit is busy 92% of a 1024 x 1024
+// stage).  Whole lines per instruction through LDS, two values a lane, take 8;
+// in the march that cost as much LDS work and registers (1024 x 1024 3.80 ->
+// 4.03 ms a stage), so only the prologue loads that way, and the halo columns
+// go 16 lanes to a line (64 x 48 37.1 -> 34.2 us a stage with its fields, 333 x
+// 270 320 -> 311).  Against a version with 16 x 16 x 4 matrix instructions, right
+// faces by DPP, per-lane coefficients and addresses formed every row, this one
+// runs a 1024 x 1024 step (three stages and the entry sums) in 12.4 instead of
+// 16.4 ms and 333 x 270 in 1.07 instead of 2.09 ms per step.
 //
 // Every wavefront sees one sign of p_k (k < 8: p_k < 0) and every register
 // slot one sign of p_l.  Wavefronts of p_k < 0 hold the strip mirrored (lane
@@ -765,6 +772,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const double* base) {
 // A buffer of 2^31 bytes: an access at BUF_DROP is out of range with any row
 // offset below 2^31, so a store there is dropped.
 constexpr unsigned BUF_DROP = 0x80000000u;
+__device__ __forceinline__ dbl2 bload2(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so) {
+  return __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(r, vo, so, 0));
+}
 __device__ __forceinline__ double bload(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so) {
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0));
 }
@@ -892,6 +902,19 @@ __device__ __forceinline__ void fused_raw_sum(const Dev& D, const FusedArgs& A, 
   }
 }
 
+// LDS traffic between the lanes of one wavefront, in program order
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Where the 16 velocities of wavefront w at node column c are staged, in a row
+// slot: two planes apart, and two values further for the first of four columns,
+// so that lanes r of four columns are on distinct banks; within columns 0 .. 21 of
+// the planes, which are written again every row.
+__device__ __forceinline__ int stage_line(int w, int c) { return w * KS + 2 * PS * c + 2 * (c & 3); }
+
 template <int N>
 struct RotC {
   static constexpr int value = N;
@@ -941,12 +964,15 @@ __global__ __launch_bounds__(SNT) void fused_kernel(Dev D, FusedArgs A, const do
   const unsigned vo0 = ((unsigned)wrapx(x0 + nc) * (unsigned)V + 16u * (unsigned)w + (unsigned)r) * 8u;
   const unsigned vo1 = vo0 + (unsigned)(15 - 2 * r) * 8u;
   const unsigned vs0 = x0 + nc < nx ? vo0 : BUF_DROP, vs1 = x0 + nc < nx ? vo1 : BUF_DROP;
+  // the prologue's loads: velocities (w, 2 (L & 7)) and the next of node column
+  // L >> 3, whole lines
+  const unsigned vol = ((unsigned)wrapx(x0 + (L >> 3)) * (unsigned)V + 16u * (unsigned)w + 2u * (unsigned)(L & 7)) * 8u;
   const unsigned rowb = (unsigned)nx * (unsigned)V * 8u;
   // the wavefront's halo, 16 velocities x 6 columns (a 128-byte line each):
-  // lane L takes l = L >> 2 of column -3, -2, -1, 8 for L & 3 = 0 .. 3, and
-  // l = (L & 31) >> 1 of column 9 + (L & 1) (lanes 32 - 63 repeat 0 - 31)
-  const int hcA = (L & 3) < 3 ? (L & 3) - 3 : SW, hcB = SW + 1 + (L & 1);
-  const int hlA = L >> 2, hlB = (L & 31) >> 1;
+  // lane L takes l = L & 15 of column -3, -2, -1, 8 for L >> 4 = 0 .. 3, and
+  // of column 9 + (L >> 4 & 1) (lanes 32 - 63 repeat 0 - 31)
+  const int hcA = L < 48 ? (L >> 4) - 3 : SW, hcB = SW + 1 + ((L >> 4) & 1);
+  const int hlA = L & 15, hlB = L & 15;
   const unsigned hvoA = ((unsigned)wrapx(colx(hcA)) * (unsigned)V + (unsigned)(16 * w + hlA)) * 8u;
   const unsigned hvoB = ((unsigned)wrapx(colx(hcB)) * (unsigned)V + (unsigned)(16 * w + hlB)) * 8u;
   // node fields [NF][ntot]: thread t < NF SW loads field t / SW of column t % SW
@@ -992,17 +1018,9 @@ __global__ __launch_bounds__(SNT) void fused_kernel(Dev D, FusedArgs A, const do
   double fpre[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) fpre[i] = bload(rf, fvo, rowsf(ya + i));
-  double R5[2][5];
+  dbl2 line[7];  // rows ya - 3 .. ya + 3
 #pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    R5[0][i] = bload(rs, vo0, rowso(ya - 1 + i));
-    R5[1][i] = bload(rs, vo1, rowso(ya - 2 + i));
-  }
-  double e0 = 0.0, e1 = 0.0;
-  if (ADV) {
-    e0 = bload(rs, vo0, rowso(ya - 2));
-    e1 = bload(rs, vo1, rowso(ya - 3));
-  }
+  for (int i = 0; i < 7; ++i) line[i] = bload2(rs, vol, rowso(ya - 3 + i));
   // f^n and the halo of row ya, node fields of row ya + 4
   double f0v[2] = {0.0, 0.0}, hv[2];
   if (!FIRST) {
@@ -1026,6 +1044,34 @@ __global__ __launch_bounds__(SNT) void fused_kernel(Dev D, FusedArgs A, const do
   __syncthreads();
   if (w < 4) fused_rowtab(S, (ya + (w >> 1)) & 3, S.tab[w >> 1], w & 1, L);
   double fyl[2] = {0.0, 0.0};
+  // The ring from the lines, through the wavefront's own planes of the row
+  // slots, four lines at a time.
+  double R5[2][5], e0, e1;
+  {
+    double* const ln = &S.U[0][stage_line(w, L >> 3) + 2 * (L & 7)];
+    const double *const n0 = &S.U[0][stage_line(w, nc) + r], *const n1 = &S.U[0][stage_line(w, nc) + 15 - r];
+    auto at = [](int a) { return a / 2 * USLOT + a % 2 * PS; };
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *(dbl2*)(ln + at(i)) = line[i];
+    wave_fence();
+    e1 = n1[at(0)];
+    e0 = n0[at(1)];
+    R5[1][0] = n1[at(1)];
+    R5[0][0] = n0[at(2)];
+    R5[1][1] = n1[at(2)];
+    R5[0][1] = n0[at(3)];
+    R5[1][2] = n1[at(3)];
+    wave_fence();
+#pragma unroll
+    for (int i = 4; i < 7; ++i) *(dbl2*)(ln + at(i - 4)) = line[i];
+    wave_fence();
+    R5[0][2] = n0[at(0)];
+    R5[1][3] = n1[at(0)];
+    R5[0][3] = n0[at(1)];
+    R5[1][4] = n1[at(1)];
+    R5[0][4] = n0[at(2)];
+    wave_fence();
+  }
   if (ADV) {  // the face between rows ya - 1 and ya
     fyl[0] = weno5(R5[0][3], R5[0][2], R5[0][1], R5[0][0], e0, K);
     fyl[1] = weno5(e1, R5[1][0], R5[1][1], R5[1][2], R5[1][3], K);
