@@ -160,10 +160,11 @@ int evlb_init(const evlb_params* params, void* d_workspace, size_t ws_bytes,
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): evlb_init with
  * the library's own workspace, a static device array of
- * EVLB_NOALLOC_MAX_BYTES per device that the library holds until the
- * process ends, instead of a caller buffer.  Calls no hipMalloc or other
+ * EVLB_NOALLOC_MAX_BYTES (and 512 KiB for launch tables) per device that the
+ * library holds until the process ends, instead of a caller buffer.  Calls no hipMalloc or other
  * allocating routine.  Returns EVLB_EWORKSPACE if
- * evlb_workspace_bytes(params) exceeds EVLB_NOALLOC_MAX_BYTES, EVLB_EHIP if
+ * evlb_workspace_bytes(params), less those tables, exceeds
+ * EVLB_NOALLOC_MAX_BYTES, EVLB_EHIP if
  * the array's device address cannot be obtained.  Every context made this
  * way on one device shares that device's array: a new one re-initialises it
  * and invalidates the previous one (its later calls give undefined

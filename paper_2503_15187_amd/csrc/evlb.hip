@@ -1,8 +1,8 @@
 // EV-FDLB time step for MI355X (gfx950): fused HIP kernels and the C ABI
 // declared in include/evlb.h.
 //
-// One TVD-RK3 stage is ONE kernel.  A workgroup owns a tile of W = 64
-// consecutive nodes of one periodic system and all q velocities:
+// One TVD-RK3 stage is ONE kernel.  A workgroup owns a tile of consecutive
+// nodes of one periodic system and all q velocities (phases of the wide tile):
 //   1. load     F, G rows of the tile plus a 3-node halo (WENO-5) into LDS;
 //               the density window (force / averaged density halo) and
 //               u, T (gradient halo) from the moments of the previous stage.
@@ -1659,6 +1659,7 @@ struct Layout {
   size_t tables, mx, tiles_broad, tiles_wide, tiles_narrow, tiles_col, tiles_adj, f1, f2, momA, momB, status, tiso;
   size_t adj_g, adj_mu2, adj_mu1, adj_fa, adj_mom, adj_part, adj_lam, total;
   long long ntot;
+  size_t mirror;  // bytes of the mirror shapes' tables and broad tiles
   int ntiles_broad, ntiles_wide, ntiles_narrow, ntiles_col, ntiles_adj, ms, mf;
   size_t ntables;
 };
@@ -1794,6 +1795,7 @@ Layout make_layout(const evlb_params* p) {
   off += align256(sizeof(double) * (64 * (size_t)mirror_operands(q) + NTAB + (size_t)q * q));
   L.tiles_broad = off;
   off += align256(sizeof(int4) * (size_t)L.ntiles_broad);
+  L.mirror = off - L.mx;
   L.tiles_wide = off;
   off += align256(sizeof(int4) * (size_t)L.ntiles_wide);
   L.tiles_narrow = off;
@@ -2253,7 +2255,11 @@ bool device_matches(const evlb_ctx* c) {
 // code object.  Host code reaches it only through the address that
 // hipGetSymbolAddress returns with that device current (the array's name in
 // host code is a host-side stand-in, not a device address).
-static __device__ __align__(256) unsigned char scratch[EVLB_NOALLOC_MAX_BYTES];
+// The limit does not count the mirror shapes' tables and broad tiles, for which
+// it has NOALLOC_TABLES more: 15 KiB and 16 bytes per broad tile (in systems of
+// the 8 nodes that a system has at least, and q 8, one per 2.5 KiB).
+constexpr size_t NOALLOC_TABLES = (size_t)512 << 10;
+static __device__ __align__(256) unsigned char scratch[EVLB_NOALLOC_MAX_BYTES + NOALLOC_TABLES];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -2288,13 +2294,15 @@ int evlb_init_noalloc(const evlb_params* params, void* hip_stream, evlb_ctx** ou
   *out = nullptr;
   const int rc = validate(params);
   if (rc) return rc;
-  if (evlb_workspace_bytes(params) > EVLB_NOALLOC_MAX_BYTES) return EVLB_EWORKSPACE;
+  const size_t need = evlb_workspace_bytes(params);
+  const size_t tables = params->dim == 2 ? 0 : make_layout(params).mirror;
+  if (need - tables > EVLB_NOALLOC_MAX_BYTES || need > sizeof(scratch)) return EVLB_EWORKSPACE;
   int device = -1;
   if (hipGetDevice(&device) != hipSuccess) return EVLB_EHIP;
   void* ws = nullptr;
   const int sc = scratch_address(device, &ws);
   if (sc) return sc;
-  return evlb_init(params, ws, EVLB_NOALLOC_MAX_BYTES, hip_stream, out);
+  return evlb_init(params, ws, sizeof(scratch), hip_stream, out);
 }
 
 int evlb_init(const evlb_params* params, void* d_workspace, size_t ws_bytes, void* hip_stream, evlb_ctx** out) {

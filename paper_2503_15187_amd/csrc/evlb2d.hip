@@ -8,8 +8,8 @@
 // mean-field force of eq:force integrated along z, and the averaged density
 // of Sec. II A integrated along z.
 //
-// State d_f[2][16][16][ny][nx] (plane d*256 + k*16 + l, node fastest).  One
-// TVD-RK3 stage is two kernels:
+// State d_f[2][ny][nx][16][16]: node-major, the 256 velocities of a node
+// contiguous.  One TVD-RK3 stage is two kernels:
 //   fields_kernel  32 x 16 (small grids: 16 x 8) nodes per workgroup, density
 //                  tile with the force
 //                  radius as halo in LDS: n, u, T, q from the raw velocity
@@ -1306,6 +1306,7 @@ Layout make_layout(const evlb_params* p, const evlb::DiscTables& t) {
   const size_t fbytes = align256(sizeof(double) * 2 * (size_t)V * (size_t)N);
   L.f1 = off; off += fbytes;
   L.f2 = off; off += fbytes;
+  off += align256(sizeof(double) * 6 * (size_t)N);  // unused: the size of a workspace stays what callers know
   L.raw = off; off += align256(sizeof(double) * NRAW * (size_t)N);
   L.fld = off; off += align256(sizeof(double) * NF * (size_t)N);
   L.status = off; off += 256;
