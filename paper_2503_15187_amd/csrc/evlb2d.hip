@@ -590,8 +590,8 @@ __global__ __launch_bounds__(SH::NT) void fields_kernel(Dev D, const double* __r
 // stage).  Whole lines per instruction through LDS, two values a lane, take 8;
 // in the march that cost as much LDS work and registers (1024 x 1024 3.80 ->
 // 4.03 ms a stage), so only the prologue loads that way, and the halo columns
-// go 16 lanes to a line (64 x 48 37.1 -> 34.2 us a stage with its fields, 333 x
-// 270 320 -> 311).  Against a version with 16 x 16 x 4 matrix instructions, right
+// go four lanes to 32 bytes (64 x 48 37.1 -> 33.5 us a stage with its fields,
+// 333 x 270 320 -> 311).  Against a version with 16 x 16 x 4 matrix instructions, right
 // faces by DPP, per-lane coefficients and addresses formed every row, this one
 // runs a 1024 x 1024 step (three stages and the entry sums) in 12.4 instead of
 // 16.4 ms and 333 x 270 in 1.07 instead of 2.09 ms per step.
@@ -969,10 +969,13 @@ __global__ __launch_bounds__(SNT) void fused_kernel(Dev D, FusedArgs A, const do
   const unsigned vol = ((unsigned)wrapx(x0 + (L >> 3)) * (unsigned)V + 16u * (unsigned)w + 2u * (unsigned)(L & 7)) * 8u;
   const unsigned rowb = (unsigned)nx * (unsigned)V * 8u;
   // the wavefront's halo, 16 velocities x 6 columns (a 128-byte line each):
-  // lane L takes l = L & 15 of column -3, -2, -1, 8 for L >> 4 = 0 .. 3, and
-  // of column 9 + (L >> 4 & 1) (lanes 32 - 63 repeat 0 - 31)
-  const int hcA = L < 48 ? (L >> 4) - 3 : SW, hcB = SW + 1 + ((L >> 4) & 1);
-  const int hlA = L & 15, hlB = L & 15;
+  // four neighbouring lanes take 32 bytes of a line: fewer lookups than one
+  // line per lane, and fewer bank conflicts at the write to LDS than 16 lanes to
+  // a line (1024 x 1024 3.78 -> 3.73 ms a stage).  Lane L takes l = (L & 3) + 4
+  // (L >> 4) of column -3, -2, -1, 8 for L >> 2 & 3 = 0 .. 3, and l = (L & 3) + 4
+  // (L >> 3 & 3) of column 9 + (L >> 2 & 1) (lanes 32 - 63 repeat 0 - 31)
+  const int hcA = (L & 12) < 12 ? ((L >> 2) & 3) - 3 : SW, hcB = SW + 1 + ((L >> 2) & 1);
+  const int hlA = (L & 3) + 4 * (L >> 4), hlB = (L & 3) + 4 * ((L >> 3) & 3);
   const unsigned hvoA = ((unsigned)wrapx(colx(hcA)) * (unsigned)V + (unsigned)(16 * w + hlA)) * 8u;
   const unsigned hvoB = ((unsigned)wrapx(colx(hcB)) * (unsigned)V + (unsigned)(16 * w + hlB)) * 8u;
   // node fields [NF][ntot]: thread t < NF SW loads field t / SW of column t % SW
