@@ -37,8 +37,8 @@ HBM_PEAK_GBS = 8000.0
 # stage 1 reads f^n and writes f^(1) (16 + 16 B), stages 2 and 3 each read
 # f^(s-1) and f^n and write f^(s) (48 B); node fields and halo re-reads excluded
 BYTES_PER_UPDATE_STEP = 128.0
-KERNEL_NAMES = {0: "stage_kernel_mirror<{q},32>", 16: "stage_kernel_mirror<{q},16>",
-                63: "stage_kernel_col<{q},true>", 64: "stage_kernel<{q},64,8>"}
+KERNEL_NAMES = {0: "stage_kernel_mirror<{q},32,15>", 16: "stage_kernel_mirror<{q},16,15>",
+                63: "stage_kernel_col<{q},15>", 64: "stage_kernel<{q},64,8>"}
 
 
 def cpu_baseline(c, n, u, T, target_s=8.0):

@@ -96,6 +96,19 @@ struct StageArgs {
   int rhs_mode;          // write L(f_prev) instead of a stage
 };
 
+// The right-hand-side terms that a kernel is compiled for: all of them, or
+// advection and force as in TERMS (0 .. 3) and the collision terms by the
+// call's mask, or (ANY_TERMS) every one by the mask.  A term that is off adds
+// zeros, not zero times what a node without a density or a temperature gives
+// it.
+constexpr int ANY_TERMS = -1;
+template <int TERMS>
+__device__ __forceinline__ bool term_on(const DevParams& P, int bit) {
+  if (TERMS == EVLB_TERM_ALL) return true;
+  if (TERMS != ANY_TERMS && (bit == EVLB_TERM_ADV || bit == EVLB_TERM_FORCE)) return TERMS & bit;
+  return P.term_mask & bit;
+}
+
 // 1/x from the hardware reciprocal (within 2^-24.4) and one third-order step r
 // <- r (1 + d + d^2), d = 1 - x r: within an ulp or two of the quotient, with
 // a shorter dependency chain than the correctly rounded division
@@ -674,7 +687,7 @@ __device__ __forceinline__ double mirror_blocks(double v) {  // sum over the blo
   return v;
 }
 
-template <int Q, int W>
+template <int Q, int W, int TERMS>
 __device__ void stage_tile_mirror(const DevParams& P, const StageArgs& A, int tile, SmemM<Q, W>& S) {
   using M = Mirror<Q, W>;
   constexpr int NT = M::NT, KT = M::KT, NC = M::NC, NR = M::NR, NCW = M::NCW, FS = M::FS;
@@ -693,7 +706,8 @@ __device__ void stage_tile_mirror(const DevParams& P, const StageArgs& A, int ti
   }
   const long long ntot = P.ntot;
   const int hn = P.hn;
-  const bool adv = P.term_mask & EVLB_TERM_ADV, frc = P.term_mask & EVLB_TERM_FORCE;
+  const bool adv = term_on<TERMS>(P, EVLB_TERM_ADV), frc = term_on<TERMS>(P, EVLB_TERM_FORCE);
+  const bool j0 = term_on<TERMS>(P, EVLB_TERM_J0), j1 = term_on<TERMS>(P, EVLB_TERM_J1);
   // ---- load: one batch of global loads, then the LDS writes ----------------
   // rows of f: LPR lanes a row, NT / LPR rows at a time
   constexpr int FW = W + 2 * HF, LPR = FW <= 32 ? 32 : 64, RPB = NT / LPR, LF = (2 * Q + RPB - 1) / RPB;
@@ -871,16 +885,20 @@ __device__ void stage_tile_mirror(const DevParams& P, const StageArgs& A, int ti
   } else if (wave == NCW + 1) {
     if (lane < W) {
       // Hermite moments a_0 = n, a_1 = n u, a_{l+1} = u a_l + l (T - 1) a_{l-1}
-      const double n = S.n[lane + hn], u = S.u[lane + 2], tm1 = S.T[lane + 2] - 1.0;
-      double am = n, a = n * u;
-      S.a[0][lane] = am;
-      S.a[1][lane] = a;
+      if (j0 || j1) {
+        const double n = S.n[lane + hn], u = S.u[lane + 2], tm1 = S.T[lane + 2] - 1.0;
+        double am = n, a = n * u;
+        S.a[0][lane] = am;
+        S.a[1][lane] = a;
 #pragma unroll
-      for (int l = 1; l < Q - 1; ++l) {
-        const double an = fma(u, a, (double)l * tm1 * am);
-        am = a;
-        a = an;
-        S.a[l + 1][lane] = a;
+        for (int l = 1; l < Q - 1; ++l) {
+          const double an = fma(u, a, (double)l * tm1 * am);
+          am = a;
+          a = an;
+          S.a[l + 1][lane] = a;
+        }
+      } else {
+        for (int l = 0; l < Q; ++l) S.a[l][lane] = 0.0;
       }
     }
   } else if (wave == NCW + 2) {
@@ -917,12 +935,15 @@ __device__ void stage_tile_mirror(const DevParams& P, const StageArgs& A, int ti
     // with a cubic c per node and distribution (see the column shape)
     const double idx12 = P.inv_dx * (1.0 / 12.0);
     const int w = lane, j = w - 2;
-    if (j >= 0 && j < W) {
+    if (!j1) {
+      if (j >= 0 && j < W)
+        for (int m = 0; m < 4; ++m) S.co[MC_F + m][j] = S.co[MC_G + m][j] = 0.0;
+    } else if (j >= 0 && j < W) {
       const double T = S.T[w], iT = rcpn(T);
       const double Ag = (S.X[w - 2] - 8.0 * S.X[w - 1] + 8.0 * S.X[w + 1] - S.X[w + 2]) * idx12 * rcpn(S.X[w]);
       const double Bg = (S.T[w - 2] - 8.0 * S.T[w - 1] + 8.0 * S.T[w + 1] - S.T[w + 2]) * idx12 * iT;
       const double Ug = (S.u[w - 2] - 8.0 * S.u[w - 1] + 8.0 * S.u[w + 1] - S.u[w + 2]) * idx12;
-      const double pre = P.term_mask & EVLB_TERM_J1 ? -P.b * nn * chi * cc : 0.0;
+      const double pre = -P.b * nn * chi * cc;
       const double pA = pre * Ag, pB = pre * Bg, pU = pre * Ug;
       S.co[MC_F][j] = -0.6 * pU;
       S.co[MC_F + 1][j] = pA - 0.9 * pB;
@@ -939,11 +960,16 @@ __device__ void stage_tile_mirror(const DevParams& P, const StageArgs& A, int ti
 #pragma unroll
       for (int q = 1; q < 64 / W; ++q) Fx += S.fp[q][lane];
       S.co[MC_FX][lane] = frc ? cc * (P.g_ext + Fx) : 0.0;
-      S.co[MC_U][lane] = S.u[lane + 2];
+      S.co[MC_U][lane] = j0 || j1 ? S.u[lane + 2] : 0.0;
     }
   } else if (wave == NCW + 2) {
     // transport: mu (eq:viscosity), tau (eq:tau), Pr (eq:prandtl); J0
-    if (lane < W) {
+    if (!j0) {
+      if (lane < W) {
+        S.co[MC_NUB][lane] = bb;
+        for (int m = 4; m < 7; ++m) S.co[MC_F + m][lane] = S.co[MC_G + m][lane] = 0.0;
+      }
+    } else if (lane < W) {
       const double T = S.T[lane + 2], n = S.n[lane + hn], chi = S.chi[lane + 2];
       const double bn = P.b * n;
       const double y = bn * chi;
@@ -954,7 +980,7 @@ __device__ void stage_tile_mirror(const DevParams& P, const StageArgs& A, int ti
       const double Pr = (2.0 / 3.0) * (1.0 + 0.6 * y) * (1.0 + 0.8 * y + c12 * y * y) *
                         rcpn((1.0 + 0.4 * y) * (1.0 + 1.2 * y + c32 * y * y));
       const double iT = rcpn(T);
-      const double nu = P.term_mask & EVLB_TERM_J0 ? cc * chi * n * T * (1.0 + 0.4 * y) * rcpn(mu) : 0.0;
+      const double nu = cc * chi * n * T * (1.0 + 0.4 * y) * rcpn(mu);
       const double sv = nu * ((1.0 - Pr) * qv * (0.2 * iT * iT) * rcpn(n));
       S.co[MC_NUB][lane] = bb - nu;
       S.co[MC_F + 4][lane] = nu;
@@ -1044,7 +1070,7 @@ __device__ __forceinline__ int grid_index(const DevParams& P) {
 // launched call by call: q 8 3.67 -> 3.47, q 16 3.77 -> 3.60, q 24 4.40 -> 4.22
 // us (without the preload, 0.17 us slower than before).  tiles: null for a
 // single system; 32 bits hold the node count of any state that fits.
-template <int Q, int W>
+template <int Q, int W, int TERMS>
 __global__ __launch_bounds__((Mirror<Q, W>::NT)) void stage_kernel_mirror(const double* f_prev, const double* mom_in,
                                                                            const int4* tiles, const double* mx,
                                                                            int ntot, int hn, int ntiles, int onex,
@@ -1061,7 +1087,7 @@ __global__ __launch_bounds__((Mirror<Q, W>::NT)) void stage_kernel_mirror(const 
   P.onex = onex;
   // one tile per workgroup (the grid is the tile count)
   const int b = grid_index(P);
-  if (b >= 0 && b < P.ntiles) stage_tile_mirror<Q, W>(P, A, P.onex ? b : xcd_tile(b, P.ntiles), S);
+  if (b >= 0 && b < P.ntiles) stage_tile_mirror<Q, W, TERMS>(P, A, P.onex ? b : xcd_tile(b, P.ntiles), S);
 }
 
 template <int Q, int W, int NG>
@@ -1108,7 +1134,7 @@ struct SmemCol {
   double cf[MF_MAX];                 // EV1 force taps
 };
 
-template <int Q, bool FULL>
+template <int Q, int TERMS>
 __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile, SmemCol<Q>& S,
                                const double* __restrict__ vel, const double* __restrict__ pairs) {
   const int lane = threadIdx.x;  // 0..63
@@ -1274,7 +1300,10 @@ __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile,
   const double chA = __shfl(chv[0], csrc), chB = __shfl(chv[LU - 1], csrc);
   const double chi = c < 64 ? chA : chB;
   __syncthreads();
-  const double u = S.w.g.u[c], T = S.w.g.T[c];
+  // without collision terms the moments in them are those of an empty node at
+  // rest
+  const bool j0 = term_on<TERMS>(P, EVLB_TERM_J0), j1 = term_on<TERMS>(P, EVLB_TERM_J1);
+  const double u = j0 || j1 ? S.w.g.u[c] : 0.0, T = j0 || j1 ? S.w.g.T[c] : 1.0;
   const double invT = rcpn(T);
   const double* Xs = S.w.g.X;
   const double* Ts = S.w.g.T;
@@ -1294,8 +1323,8 @@ __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile,
   const double pre = -bn * chi;
   // Hermite moments a_0 = n, a_1 = n u, a_{l+1} = u a_l + l (T - 1) a_{l-1}
   double a[Q];
-  a[0] = n;
-  a[1] = n * u;
+  a[0] = j0 || j1 ? n : 0.0;
+  a[1] = a[0] * u;
 #pragma unroll
   for (int l = 1; l < Q - 1; ++l) a[l + 1] = fma(u, a[l], (double)l * (T - 1.0) * a[l - 1]);
   // even and odd parts of the columns over mirror pairs, f_j +- f_(Q-1-j)
@@ -1315,19 +1344,15 @@ __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile,
   const double bb = A.rhs_mode ? 0.0 : (A.first ? A.alpha + A.beta : A.beta);
   const bool base = !A.first && !A.rhs_mode && valid;
   const WenoK K = weno_k(P);
-  // FULL: advection and force known to be on
-  const bool adv = FULL || (P.term_mask & EVLB_TERM_ADV);
-  const bool frc = FULL || (P.term_mask & EVLB_TERM_FORCE);
-  const bool j0 = P.term_mask & EVLB_TERM_J0;
-  const bool j1 = P.term_mask & EVLB_TERM_J1;
+  const bool adv = term_on<TERMS>(P, EVLB_TERM_ADV), frc = term_on<TERMS>(P, EVLB_TERM_FORCE);
   // Shakhov relaxation and J1 of velocity k: -nu f_k + E_k c(xi) with
   // xi = p_k - u and a cubic c per node and distribution.  For F,
   //   nu (1 + sS xi (xi^2/T - 3)) + pre (xi (A + 0.3 (xi^2/T - 3) B) + 0.6 (xi^2/T - 1) U),
   // for G,
   //   nu T (1 + sS xi (xi^2/T - 1)) + pre T (xi (A + 0.3 (xi^2/T - 1) B) + 0.2 (3 xi^2/T - 1) U),
   // expanded in powers of xi and scaled by cc.
-  const double nu0 = j0 ? cc * nu : 0.0, sv = nu0 * sS, pc = j1 ? cc * pre : 0.0;
-  const double pA = pc * Ag, pB = pc * Bg, pU = pc * Ug;
+  const double nu0 = j0 ? cc * nu : 0.0, sv = j0 ? nu0 * sS : 0.0, pc = cc * pre;
+  const double pA = j1 ? pc * Ag : 0.0, pB = j1 ? pc * Bg : 0.0, pU = j1 ? pc * Ug : 0.0;
   const double cF0 = nu0 - 0.6 * pU, cF1 = pA - 3.0 * sv - 0.9 * pB;
   const double cF2 = 0.6 * pU * invT, cF3 = (sv + 0.3 * pB) * invT;
   const double cG0 = T * (nu0 - 0.2 * pU), cG1 = T * (pA - sv - 0.3 * pB);
@@ -1454,12 +1479,12 @@ __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile,
   __syncthreads();
 }
 
-template <int Q, bool FULL>
+template <int Q, int TERMS>
 __global__ __launch_bounds__(64) void stage_kernel_col(DevParams P, StageArgs A, const double* __restrict__ vel,
                                                        const double* __restrict__ pairs) {
   __shared__ SmemCol<Q> S;
   // one tile per workgroup (the grid is the tile count)
-  if ((int)blockIdx.x < P.ntiles) stage_tile_col<Q, FULL>(P, A, xcd_tile(blockIdx.x, P.ntiles), S, vel, pairs);
+  if ((int)blockIdx.x < P.ntiles) stage_tile_col<Q, TERMS>(P, A, xcd_tile(blockIdx.x, P.ntiles), S, vel, pairs);
 }
 
 // Grid-wide barrier for the persistent kernel (all workgroups co-resident:
@@ -1533,7 +1558,7 @@ struct MirrorShape {
   typedef SmemM<Q, W> Shared;
   __device__ static void prologue(const DevParams&, Shared&) {}
   __device__ static void tile(const DevParams& P, const StageArgs& A, int t, Shared& S, const double*, const double*) {
-    stage_tile_mirror<Q, W>(P, A, t, S);
+    stage_tile_mirror<Q, W, ANY_TERMS>(P, A, t, S);
   }
 };
 
@@ -1544,7 +1569,7 @@ struct ColumnShape {
   __device__ static void prologue(const DevParams&, Shared&) {}
   __device__ static void tile(const DevParams& P, const StageArgs& A, int t, Shared& S,
                               const double* __restrict__ vel, const double* __restrict__ pairs) {
-    stage_tile_col<Q, false>(P, A, t, S, vel, pairs);
+    stage_tile_col<Q, ANY_TERMS>(P, A, t, S, vel, pairs);
   }
 };
 
@@ -1894,7 +1919,11 @@ int launch_stage(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
 template <int Q, int W>
 int launch_stage_mirror(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
   const DevParams P = params_for(c, W == NARROW ? NARROW : BROAD);
-  hipLaunchKernelGGL((stage_kernel_mirror<Q, W>), dim3(grid_of(P, P.ntiles)), dim3(Mirror<Q, W>::NT), 0, st, A.f_prev, A.mom_in,
+  // The branches on the mask lie in the node wavefronts' chains: with all terms
+  // known a stage of 256 nodes (q 16) takes 3.38, by the mask 3.47 us.
+  const auto kernel = P.term_mask == EVLB_TERM_ALL ? stage_kernel_mirror<Q, W, EVLB_TERM_ALL>
+                                                   : stage_kernel_mirror<Q, W, ANY_TERMS>;
+  hipLaunchKernelGGL(kernel, dim3(grid_of(P, P.ntiles)), dim3(Mirror<Q, W>::NT), 0, st, A.f_prev, A.mom_in,
                      P.single ? nullptr : P.tiles, P.mx, (int)P.ntot, P.hn, P.ntiles, P.onex, P, A);
   return hipGetLastError() == hipSuccess ? EVLB_OK : EVLB_EHIP;
 }
@@ -1902,11 +1931,11 @@ int launch_stage_mirror(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
 template <int Q>
 int launch_stage_col(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
   const DevParams P = params_for(c, WC);
-  constexpr int full = EVLB_TERM_ADV | EVLB_TERM_FORCE;
-  if ((P.term_mask & full) == full)
-    hipLaunchKernelGGL((stage_kernel_col<Q, true>), dim3(P.ntiles), dim3(64), 0, st, P, A, P.vel, P.pairs);
-  else
-    hipLaunchKernelGGL((stage_kernel_col<Q, false>), dim3(P.ntiles), dim3(64), 0, st, P, A, P.vel, P.pairs);
+  constexpr int af = EVLB_TERM_ADV | EVLB_TERM_FORCE;
+  const auto kernel = P.term_mask == EVLB_TERM_ALL ? stage_kernel_col<Q, EVLB_TERM_ALL>
+                      : (P.term_mask & af) == af   ? stage_kernel_col<Q, af>
+                                                   : stage_kernel_col<Q, ANY_TERMS>;
+  hipLaunchKernelGGL(kernel, dim3(P.ntiles), dim3(64), 0, st, P, A, P.vel, P.pairs);
   return hipGetLastError() == hipSuccess ? EVLB_OK : EVLB_EHIP;
 }
 

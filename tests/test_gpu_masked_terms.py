@@ -1,0 +1,71 @@
+"""Right-hand sides without the collision terms, or with one of them, of states
+that hold nodes without a density or a temperature: a term that is off adds
+nothing, so only the terms that are on may carry such a node's moments."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import step1d  # noqa: E402
+from oracle.model import Params  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+E = None
+DX = 1 / 8
+
+
+def setup_module(module):
+    global E
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2503_15187_amd import evlb as _E
+    E = _E
+
+
+def td(a):
+    return torch.tensor(np.ascontiguousarray(a), dtype=torch.float64, device="cuda")
+
+
+def state(N, Q, tb):
+    """A smooth non-Maxwellian state with an empty node, one of negative
+    temperature and one whose values lie on a single velocity (temperature
+    zero)."""
+    x = np.arange(N) / N
+    F, G = step1d.initial_state(0.3 * (1 + 0.08 * np.sin(2 * np.pi * x)), 0.04 * np.cos(2 * np.pi * x),
+                                0.6 + 0.02 * np.sin(2 * np.pi * x), tb)
+    w = tb.w[:, None] / tb.w.max()
+    bump = 1 + 0.03 * w * np.sin(0.37 * np.arange(N) + 1.3 * np.arange(Q)[:, None])
+    F, G = F * bump, G * bump[::-1]
+    F[:, 20], G[:, 20] = 0.0, 0.0
+    G[:, 63] *= -1.5
+    F[:, 110], G[:, 110] = 0.0, 0.0
+    F[Q // 2, 110] = 0.3
+    return F, G
+
+
+# the tiles of 16, 63 and 64 nodes; 40 copies by the library's choice (tiles of
+# 32 nodes at q 8 and 16).  Masks: advection, force, both, the relaxation with
+# and without them, J1
+@pytest.mark.parametrize("Q", [8, 16, 24])
+@pytest.mark.parametrize("tile,copies", [(16, 1), (63, 1), (64, 1), (0, 40)])
+@pytest.mark.parametrize("mask", [0, 1, 2, 3, 4, 5, 8, 7])
+def test_terms_that_are_off_add_nothing(Q, tile, copies, mask):
+    print(f"masked terms Q={Q} tile={tile} copies={copies} mask={mask}", flush=True)
+    N = 150
+    dt = 0.2 * DX / 8.6
+    tb = step1d.Tables(Params(Q=Q, dx=DX, dt=dt, term_mask=mask))
+    F, G = state(N, Q, tb)
+    s = E.Solver(Q, DX, dt, [N] * copies, exec_mode=1, tile_nodes=tile, term_mask=mask)
+    L = s.rhs(td(np.concatenate([np.stack([F, G])] * copies, axis=2))).cpu().numpy()
+    with np.errstate(all="ignore"):
+        ref = np.stack(step1d.rhs(F, G, tb))
+    ok = np.isfinite(ref).all(axis=(0, 1))
+    assert ok.sum() == N if not mask & 12 else N - 16 < ok.sum() < N
+    for c in range(copies):
+        got = L[:, :, c * N:(c + 1) * N][:, :, ok]
+        assert np.isfinite(got).all(), np.argwhere(~np.isfinite(got).all(axis=(0, 1))).ravel()
+        for d in range(2):
+            # the bar of one right-hand side in the plane measure
+            scale = np.max(np.abs(ref[d][:, ok]))
+            assert np.max(np.abs(got[d] - ref[d][:, ok])) <= 1e-11 * scale, (c, d)
