@@ -1552,13 +1552,13 @@ struct GroupShape {
   }
 };
 
-template <int Q, int W>
+template <int Q, int W, int TERMS>
 struct MirrorShape {
   static constexpr int NT = Mirror<Q, W>::NT;
   typedef SmemM<Q, W> Shared;
   __device__ static void prologue(const DevParams&, Shared&) {}
   __device__ static void tile(const DevParams& P, const StageArgs& A, int t, Shared& S, const double*, const double*) {
-    stage_tile_mirror<Q, W, ANY_TERMS>(P, A, t, S);
+    stage_tile_mirror<Q, W, TERMS>(P, A, t, S);
   }
 };
 
@@ -2036,7 +2036,10 @@ int run_step(evlb_ctx* c, double* f, int nsteps, hipStream_t st) {
   if (mode == EVLB_EXEC_AUTO) mode = EVLB_EXEC_PER_STAGE;
   const int w = mode == EVLB_EXEC_PERSISTENT ? pick_width_persistent(c) : pick_width(c);
   if (mode == EVLB_EXEC_PERSISTENT) {
-    if (w == NARROW) return launch_persistent<MirrorShape<Q, NARROW>>(c, w, f, nsteps, st);
+    if (w == NARROW)
+      return c->p.term_mask == EVLB_TERM_ALL
+                 ? launch_persistent<MirrorShape<Q, NARROW, EVLB_TERM_ALL>>(c, w, f, nsteps, st)
+                 : launch_persistent<MirrorShape<Q, NARROW, ANY_TERMS>>(c, w, f, nsteps, st);
     if (w == WC) return launch_persistent<ColumnShape<Q>>(c, w, f, nsteps, st);
     return launch_persistent<GroupShape<Q, WIDE, WideNG<Q>::v>>(c, w, f, nsteps, st);
   }
