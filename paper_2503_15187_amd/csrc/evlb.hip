@@ -38,6 +38,7 @@
 
 #include "../../include/evlb.h"
 #include "evlb2d.h"
+#include "resident.h"
 #include "tables.h"
 
 namespace {
@@ -1944,6 +1945,14 @@ int launch_persistent(evlb_ctx* c, int width, double* f, int nsteps, hipStream_t
   int per_cu = 0;
   EVLB_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persistent_kernel<SHAPE>, SHAPE::NT, 0));
   if (per_cu < 1) return EVLB_EHIP;
+  // every workgroup waits for all others at the grid barrier: only as many as
+  // are sure to be resident (a workgroup takes further tiles in turn)
+  constexpr int waves = SHAPE::NT / 64;
+  if (evlb::uneven(waves)) {
+    hipFuncAttributes attr;
+    EVLB_HIP(hipFuncGetAttributes(&attr, (const void*)persistent_kernel<SHAPE>));
+    per_cu = evlb::resident_per_cu(per_cu, waves, attr.numRegs);
+  }
   DevParams P = params_for(c, width);
   int grid = per_cu * c->cus;
   if (grid > P.ntiles) grid = P.ntiles;
