@@ -105,6 +105,9 @@ __device__ __forceinline__ Moments finish_moments(const Raw& m, int* status, dou
 }
 
 typedef double dbl2 __attribute__((ext_vector_type(2)));
+// two values of a caller's array, which need not start on 16 bytes (the loads
+// and stores are 16 bytes wide all the same: they need 4-byte alignment)
+typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
 
 // ---------------------------------------------------------------------------
 // raw velocity sums of a state (first stage of a step, evlb_moments).  State
@@ -136,8 +139,8 @@ __device__ __forceinline__ void velocity_sums(const Dev& D, const double* __rest
                                               const double* __restrict__ vel, double (*S)[MNODES]) {
   const int slot = threadIdx.x >> 3, q = threadIdx.x & 7;
   const long long node = min((long long)blockIdx.x * MNODES + slot, D.ntot - 1);
-  const dbl2* F = (const dbl2*)(f + node * V) + q;
-  const dbl2* G = (const dbl2*)(f + (D.ntot + node) * V) + q;
+  const dbl2u* F = (const dbl2u*)(f + node * V) + q;
+  const dbl2u* G = (const dbl2u*)(f + (D.ntot + node) * V) + q;
   dbl2 Fv[Q], Gv[Q];
 #pragma unroll
   for (int k = 0; k < Q; ++k) Fv[k] = F[k * (Q / 2)];
@@ -271,8 +274,8 @@ __global__ __launch_bounds__(256) void equilibrium_kernel(Dev D, const double* _
     const dbl2 y = *(const dbl2*)&se[1][i + h][2 * lp];
     const dbl2 E = {e * y[0], e * y[1]};
     const double g = 0.5 * sT[i + h];
-    *(dbl2*)(f + node * V + Q * kk + 2 * lp) = E;
-    *(dbl2*)(f + (N + node) * V + Q * kk + 2 * lp) = dbl2{g * E[0], g * E[1]};
+    *(dbl2u*)(f + node * V + Q * kk + 2 * lp) = E;
+    *(dbl2u*)(f + (N + node) * V + Q * kk + 2 * lp) = dbl2{g * E[0], g * E[1]};
   }
 }
 
