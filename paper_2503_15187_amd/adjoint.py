@@ -4,7 +4,8 @@ Rollout (a torch.autograd.Function) advances a state nsteps TVD-RK3 steps
 and returns the final state together with the history of the mass flux
 sum_k p_k F_k through one node after every step.  A run whose record (states
 and stage states of every step) is small keeps it, and the backward pass
-transposes it with evlb_adjoint_record.  Of a larger one the forward pass
+transposes it with evlb_adjoint_record; without a gradient to come nothing is
+kept.  Of a larger one the forward pass
 keeps a checkpoint every ceil(sqrt(nsteps)) steps; the backward pass re-runs
 each segment from its checkpoint with evlb_step_record and transposes it,
 walking the segments in reverse, the recomputation of the next segment on a
@@ -35,31 +36,43 @@ class Equilibrium(torch.autograd.Function):
         return g[0], g[1], g[2], None
 
 
-# Largest record that a run keeps until its backward pass, if it is also at most
-# 1/32 of the device's free memory (many runs may be alive at once).  Keeping it
-# saves the recomputation, a third of the backward pass's launches, whose
-# submission bounds small systems: gradients of 64 steps on 2048 nodes (q 16, a
-# record of 115 MB) take 3.0 ms with it and 4.0 ms from checkpoints.
+# Largest record that a run keeps, if it is also at most 1/32 of the device's free
+# memory (many runs may be alive at once: a graph holds its record as long as
+# its outputs live).  Keeping it saves the recomputation, a third of the backward
+# pass's launches.  It is faster at every size, so the line is what memory a
+# graph may hold, not a crossover; what a longer run gives up for it:
+#   gradient, record / checkpoints   64 steps           512              2000
+#   2048 nodes  q 8                  2.9 / 4.2 ms    19.6 / 26.1    76 /  97 (1.9 GB)
+#               q 16                 3.1 / 3.9       21.5 / 24.1    84 /  97 (3.5 GB)
+#               q 24                 3.7 / 4.3       25.9 / 28.6   100 / 108 (5.1 GB)
 RECORD_BYTES = 512 << 20
+
+
+def keeps_record(solver, nsteps, device):
+    """Whether a run of nsteps steps keeps its record for the backward pass."""
+    nbytes = 8 * (nsteps + 1) * solver.record_doubles()
+    return 0 < nsteps and nbytes <= RECORD_BYTES and 32 * nbytes <= torch.cuda.mem_get_info(device)[0]
+
+
+def checkpoint_steps(nsteps):
+    return max(1, int(math.ceil(math.sqrt(nsteps))))
 
 
 def segment_steps(solver, nsteps, device):
     """Steps between checkpoints, unless the caller gives them: all of them
     if their record is small enough to be kept, else ceil(sqrt(nsteps))."""
-    nbytes = 8 * (nsteps + 1) * solver.record_doubles()
-    if nbytes <= RECORD_BYTES and 32 * nbytes <= torch.cuda.mem_get_info(device)[0]:
-        return max(1, nsteps)
-    return max(1, int(math.ceil(math.sqrt(nsteps))))
+    return nsteps if keeps_record(solver, nsteps, device) else checkpoint_steps(nsteps)
 
 
 class Rollout(torch.autograd.Function):
     @staticmethod
     def forward(ctx, f0, phi, sigma, solver, nsteps, flux_node, every=None):
         nsteps = int(nsteps)
-        keep = not every
-        every = int(every) if every else segment_steps(solver, nsteps, f0.device)
-        keep = keep and 0 < nsteps <= every
         dev = f0.device
+        # without a gradient to come neither a record nor checkpoints are kept
+        grad = any(ctx.needs_input_grad[:3])
+        keep = grad and not every and keeps_record(solver, nsteps, dev)
+        every = int(every) if every else (nsteps if keep else checkpoint_steps(nsteps))
         vel = torch.tensor(solver.velocities, dtype=torch.float64, device=dev)
         rec = solver.record_buffer(every)
         R = rec.numel() // (every + 1)
@@ -70,7 +83,7 @@ class Rollout(torch.autograd.Function):
         flux = torch.empty(nsteps, dtype=torch.float64, device=dev)
         for start in range(0, nsteps, every):
             seg = min(every, nsteps - start)
-            if not keep:
+            if grad and not keep:
                 ckpt[start] = f.clone()
             solver.step_record(f, seg, rec)
             # F_k(node) of the states 1 .. seg inside the record, k = 0 .. q - 1
@@ -133,6 +146,8 @@ class Rollout(torch.autograd.Function):
 
 
 def rollout(f0, phi, sigma, solver, nsteps, flux_node, every=None):
+    if not torch.is_grad_enabled():  # a Function sees its inputs' flags, not the mode
+        f0, phi, sigma = (x.detach() if torch.is_tensor(x) else x for x in (f0, phi, sigma))
     return Rollout.apply(f0, phi, sigma, solver, nsteps, flux_node, every)
 
 
