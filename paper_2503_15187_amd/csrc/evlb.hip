@@ -1932,10 +1932,16 @@ int launch_stage_mirror(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
 template <int Q>
 int launch_stage_col(evlb_ctx* c, const StageArgs& A, hipStream_t st) {
   const DevParams P = params_for(c, WC);
-  constexpr int af = EVLB_TERM_ADV | EVLB_TERM_FORCE;
+  // The faces and the momentum derivative known to be in or out: behind runtime
+  // conditions they spill up to 142 scalar registers in the loop over the pairs.
+  // A right-hand side of the force alone, q 24: 25000 nodes 25.8 -> 18.5, 40000
+  // 33.8 -> 23.1, 64000 38.5 -> 27.5 us.
+  const int af = P.term_mask & (EVLB_TERM_ADV | EVLB_TERM_FORCE);
   const auto kernel = P.term_mask == EVLB_TERM_ALL ? stage_kernel_col<Q, EVLB_TERM_ALL>
-                      : (P.term_mask & af) == af   ? stage_kernel_col<Q, af>
-                                                   : stage_kernel_col<Q, ANY_TERMS>;
+                      : af == 0                    ? stage_kernel_col<Q, 0>
+                      : af == EVLB_TERM_ADV        ? stage_kernel_col<Q, EVLB_TERM_ADV>
+                      : af == EVLB_TERM_FORCE      ? stage_kernel_col<Q, EVLB_TERM_FORCE>
+                                                   : stage_kernel_col<Q, EVLB_TERM_ADV | EVLB_TERM_FORCE>;
   hipLaunchKernelGGL(kernel, dim3(P.ntiles), dim3(64), 0, st, P, A, P.vel, P.pairs);
   return hipGetLastError() == hipSuccess ? EVLB_OK : EVLB_EHIP;
 }
