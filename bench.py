@@ -322,7 +322,7 @@ def measure(E, torch, dev, q, dx, dt, nx, n, u, T, steps, warmup, mode=None, til
         raise RuntimeError("device status not ok after the timed run")
     updates = n_tot * q * 3 * steps
     launches = 1 if persistent else 3 * steps
-    kname = KERNEL_NAMES[tile].format(q=q)
+    kname = KERNEL_NAMES[tile or default_tile(nx, q)].format(q=q)
     if persistent:
         kname = f"persistent_kernel<{kname}>"
     alg_bytes = BYTES_PER_UPDATE_STEP * n_tot * q * steps / launches

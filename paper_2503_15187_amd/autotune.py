@@ -1,16 +1,20 @@
 """Launch-shape autotuner and graph-captured stepping.
 
-The stage kernel comes in three tile shapes (16-node narrow tiles with one
-velocity per thread, 63-node column tiles with one node per thread, 64-node
-tiles with velocity groups) and two launch modes (one kernel per stage, or one
-persistent cooperative kernel for all steps).  Which is fastest depends on
-the grid size: the autotuner times every candidate for a few steps on the
-caller's problem and caches the winner per problem signature.
+The stage kernel comes in four tile shapes (tiles of 16 and of 32 nodes with a
+mirror pair of velocities per lane, 63-node column tiles with one node per
+thread, 64-node tiles with velocity groups) and two launch modes (one kernel
+per stage, or one persistent cooperative kernel for all steps).  Which is
+fastest depends on the grid size: the autotuner times every candidate for a few
+steps on the caller's problem, the library's own choice (tile_nodes 0, the only
+way to the 32-node tiles) among them, and caches the winner per problem,
+library build and device.
 
 GraphStepper captures a fixed number of steps of the chosen per-stage
 launches in a HIP graph (through torch.cuda.graph) and replays it, so a long
 run costs one graph launch per chunk.
 """
+import functools
+import hashlib
 import json
 import os
 import time
@@ -19,8 +23,8 @@ import torch
 
 from . import evlb as E
 
-CANDIDATES = [(E.EVLB_EXEC_PER_STAGE, 16), (E.EVLB_EXEC_PER_STAGE, 63), (E.EVLB_EXEC_PER_STAGE, 64),
-              (E.EVLB_EXEC_PERSISTENT, 16), (E.EVLB_EXEC_PERSISTENT, 63)]
+CANDIDATES = [(E.EVLB_EXEC_PER_STAGE, 0), (E.EVLB_EXEC_PER_STAGE, 16), (E.EVLB_EXEC_PER_STAGE, 63),
+              (E.EVLB_EXEC_PER_STAGE, 64), (E.EVLB_EXEC_PERSISTENT, 16), (E.EVLB_EXEC_PERSISTENT, 63)]
 
 _CACHE_PATH = os.environ.get("EVLB_TUNE_CACHE", os.path.join(os.path.expanduser("~"), ".cache", "evlb_tune.json"))
 _memo = {}
@@ -29,6 +33,22 @@ _memo = {}
 def signature(q, nx, **kw):
     nxs = [int(nx)] if isinstance(nx, int) else [int(v) for v in nx]
     return f"q{q}-n{sum(nxs)}-s{len(nxs)}-max{max(nxs)}-" + "-".join(f"{k}{v}" for k, v in sorted(kw.items()))
+
+
+@functools.lru_cache(maxsize=None)
+def _build_id():
+    """Hash of the library: its kernels' times hold for this build alone."""
+    with open(E.LIB_PATH, "rb") as fh:
+        return hashlib.sha256(fh.read()).hexdigest()[:16]
+
+
+def _problem(q, nx, dx, device, kw):
+    """Signature of a tuning run: the system sizes, what the kernels' work
+    depends on, the library build and the device."""
+    iso = bool(kw.get("T_iso")) or kw.get("T_iso_sys") is not None
+    known = {k: v for k, v in kw.items() if k in ("force_model", "term_mask", "sigma", "r_cut")}
+    return signature(q, nx, dx=dx, iso=int(iso), lib=_build_id(),
+                     dev=torch.cuda.get_device_name(device).replace(" ", "_"), **known)
 
 
 def _load_cache():
@@ -51,7 +71,7 @@ def _store_cache(d):
 def tune(q, dx, dt, nx, f0, steps=10, candidates=CANDIDATES, use_cache=True, verbose=False, **kw):
     """Returns (exec_mode, tile_nodes, seconds per step) of the fastest
     candidate on this problem.  f0: a representative state (not modified)."""
-    sig = signature(q, nx, **{k: v for k, v in kw.items() if k in ("force_model", "term_mask")})
+    sig = _problem(q, nx, dx, f0.device, kw)
     if use_cache:
         if sig in _memo:
             return _memo[sig]
