@@ -1058,6 +1058,13 @@ __device__ __forceinline__ int xcd_tile(int b, int ntiles) {
 // XCDs -> on one: q 8 3.68 -> 3.42, q 16 3.91 -> 3.58, q 24 4.53 -> 4.23 us;
 // with two workgroups per CU (1024 nodes, q 16) 3.91 -> 4.65.  The adjoint's
 // kernels, longer chains of which the loads are a smaller part, gain nothing.
+// Several contexts on streams of their own share that XCD and still gain: at
+// most four hardware queues run at once, so a CU holds four workgroups at most.
+// A stage of every context, captured, spread -> on one, us:
+//   512 nodes   q 8   1 context 3.62 -> 3.38   2 4.00 -> 3.58   4 4.44 -> 3.67   8  8.84 ->  7.33
+//               q 16            3.86 -> 3.61     4.30 -> 3.76     4.83 -> 3.92      9.44 ->  7.72
+//               q 24            4.44 -> 4.39     4.79 -> 4.55     9.52 -> 9.00     14.77 -> 13.46
+//   64 nodes    q 16            3.91 -> 3.58     4.10 -> 3.72     8.15 -> 7.41      8.83 ->  7.47
 // Index of the workgroup in the grid, negative: not one of the grid's.
 __device__ __forceinline__ int grid_index(const DevParams& P) {
   const int b = blockIdx.x;
@@ -1999,7 +2006,10 @@ int run_moments(evlb_ctx* c, const double* f, double* n, double* u, double* T, d
 // hold fewer halos and node fields formed twice (q 24 would need two
 // workgroups' lanes).  The column shape, one wavefront a tile with the fewest
 // instructions per value, from two and a half tiles per CU on, for q 24 one
-// and a half.
+// and a half.  The tile of 64 nodes is not in the rule.  It is ahead of what the
+// rule takes only about where that changes to the column shape, captured, rule /
+// 64: q 24 16384 nodes 11.5 / 11.2, 24576 17.8 / 16.3, 32768 19.1 / 17.6, 40960
+// 19.8 / 23.6; q 16 40960 14.3 / 17.3; q 8 65536 13.1 / 12.8.
 int pick_width(const evlb_ctx* c) {
   if (c->p.tile_nodes) return c->p.tile_nodes;
   if (2 * c->L.ntiles_col > (c->p.q < 24 ? 5 : 3) * c->cus) return WC;
