@@ -656,8 +656,8 @@ constexpr int USLOT = Q * KS;
 // with P0 = c0 + xi_x (c1 + xi_x (c2 + c3 xi_x)), P1 = d0 + xi_x (d1 + d2 xi_x),
 // P2 = e0 + c3 xi_x, P3 = d2 (a rearrangement of the reduced Shakhov and J1
 // terms), plus u_x and, scaled by the stage's c, tf n; then what every lane of
-// the node takes: u_y, the factor b - c nu of f^(s-1), c F_x, c F_y
-enum { CF_C0, CF_C1, CF_C2, CF_C3, CF_D0, CF_D1, CF_D2, CF_E0, CF_UX, CF_TFN, CF_UY, CF_NUB, CF_FX, CF_FY, NCF };
+// the node takes: u_y, c nu, c F_x, c F_y
+enum { CF_C0, CF_C1, CF_C2, CF_C3, CF_D0, CF_D1, CF_D2, CF_E0, CF_UX, CF_TFN, CF_UY, CF_NU, CF_FX, CF_FY, NCF };
 
 struct FusedArgs {
   const double* fs;   // f^(s-1)
@@ -674,7 +674,7 @@ struct FusedArgs {
 // what the lanes of a row read of its node quantities
 struct RowTab {
   double P[Q][SW][4];   // (k, node): c tf n e_k(u_x) (P0, P1, P2, P3)
-  double E[SW][SW][6];  // (r, node): u_y, b - c nu, c F_x, c F_y and e_l(u_y) for l = r, 15 - r
+  double E[SW][SW][6];  // (r, node): u_y, c nu, c F_x, c F_y and e_l(u_y) for l = r, 15 - r
 };
 
 struct FusedSmem {
@@ -808,8 +808,8 @@ __device__ __forceinline__ void fused_hermite(FusedSmem& S, int s, int t) {
 
 // Per-node coefficients of the collision row polynomial of one
 // distribution (d: F or G) from the node fields of column c (fl[s]) into
-// CF[s]; bb: the factor of f^(s-1) outside L.
-__device__ __forceinline__ void fused_coeffs(const Dev& D, FusedSmem& S, int s, int c, int d, double bb, double cc) {
+// CF[s].
+__device__ __forceinline__ void fused_coeffs(const Dev& D, FusedSmem& S, int s, int c, int d, double cc) {
   const double* fl = &S.fl[s][0][0];
 #define FL(i) fl[(i) * SW + c]
   const bool j0 = (D.term_mask & EVLB_TERM_J0) != 0;
@@ -834,7 +834,7 @@ __device__ __forceinline__ void fused_coeffs(const Dev& D, FusedSmem& S, int s, 
   cf[CF_UX * SW] = FL(F_UX);
   cf[CF_TFN * SW] = (j0 || j1) ? cc * (d == 0 ? 1.0 : 0.5 * T) * FL(F_N) : 0.0;
   cf[CF_UY * SW] = FL(F_UY);
-  cf[CF_NUB * SW] = fma(-cc, nu, bb);
+  cf[CF_NU * SW] = cc * nu;
   cf[CF_FX * SW] = cc * FL(F_FX);
   cf[CF_FY * SW] = cc * FL(F_FY);
 #undef FL
@@ -1044,7 +1044,7 @@ __global__ __launch_bounds__(SNT) void fused_kernel(Dev D, FusedArgs A, const do
   }
   __syncthreads();
   if (w == 1) fused_hermite(S, (ya + (L >> 4)) & 3, L & 15);
-  if (w == 3 && L < 32) fused_coeffs(D, S, (ya + (L >> 3)) & 3, L & 7, d, bb, A.c);
+  if (w == 3 && L < 32) fused_coeffs(D, S, (ya + (L >> 3)) & 3, L & 7, d, A.c);
   __syncthreads();
   if (w < 3) fused_expansions(S, (ya + w) & 3, L);
   __syncthreads();
@@ -1128,13 +1128,8 @@ __global__ __launch_bounds__(SNT) void fused_kernel(Dev D, FusedArgs A, const do
       lds(hB, U0) = hv[1];
       if (fthr) S.fl[y & 3][tid / SW][tid & (SW - 1)] = fq;  // row y + 4
       const dbl2 nA = lds2(tE + TAB, 0), nB = lds2(tE + TAB, 1);
-      if (FIRST) {
-        accN[0] = nA[1] * cur0;
-        accN[1] = nA[1] * cur1;
-      } else {
-        accN[0] = fma(A.a, f0v[0], nA[1] * cur0);
-        accN[1] = fma(A.a, f0v[1], nA[1] * cur1);
-      }
+      accN[0] = -nA[1] * cur0;
+      accN[1] = -nA[1] * cur1;
       if (ADV) {
         // y faces: j = 0 upwind from above, j = 1 from below
         const double fyr0 = weno5(R(0, 4), R(0, 3), R(0, 2), R(0, 1), R(0, 0), K);
@@ -1156,6 +1151,13 @@ __global__ __launch_bounds__(SNT) void fused_kernel(Dev D, FusedArgs A, const do
       const double xy0 = pr - nA[0], xy1 = -pr - nA[0];
       accN[0] = fma(el[0], fma(xy0, fma(xy0, fma(PB[1], xy0, PB[0]), PA[1]), PA[0]), accN[0]);
       accN[1] = fma(el[1], fma(xy1, fma(xy1, fma(PB[1], xy1, PB[0]), PA[1]), PA[0]), accN[1]);
+      // the states behind these, so that few roundings are of the size of the result
+      accN[0] = fma(bb, cur0, accN[0]);
+      accN[1] = fma(bb, cur1, accN[1]);
+      if (!FIRST) {
+        accN[0] = fma(A.a, f0v[0], accN[0]);
+        accN[1] = fma(A.a, f0v[1], accN[1]);
+      }
     }
     // in flight across the rest of this iteration: node fields of row y + 5
     // (issued first: the wait for it in the next iteration then leaves the
@@ -1235,7 +1237,7 @@ __global__ __launch_bounds__(SNT) void fused_kernel(Dev D, FusedArgs A, const do
       if (y + 3 < yb) fused_expansions(S, (y + 3) & 3, Lq);
     } else if (w == 3) {
       if (y + 2 < yb) fused_rowtab(S, (y + 2) & 3, S.tab[p], 1, Lq);
-      if (y + 4 < yb && Lq < SW) fused_coeffs(D, S, y & 3, Lq, d, bb, A.c);
+      if (y + 4 < yb && Lq < SW) fused_coeffs(D, S, y & 3, Lq, d, A.c);
     } else if (w >= 8) {
       if (FRC && y < yb) {
         // (Dp x I) f for l = 2 (w - 8) + lh, lane (k = r, column)

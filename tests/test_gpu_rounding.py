@@ -6,13 +6,14 @@ x spread evenly in its logarithm).  A stage that sums c L(f) first and then adds
 b f^(s-1) and a f^n rounds once at b f and once at f; over the three stages of a
 step (b = 1, 1/4, 2/3) that is 6.5e-17.  The 2D stage adds two terms of L behind
 these: 1.05e-16.  The bars leave 1.3 and 1.25 of these for the rounding of L;
-the terms of L added to the states one by one gave 9.5e-17 and 1.5e-16."""
+the terms of L added to the states one by one gave 9.4 to 10e-17 and 1.5e-16."""
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
-from oracle import step1d  # noqa: E402
+import workloads  # noqa: E402
+from oracle import step1d, step2d  # noqa: E402
 from oracle.model import Params  # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -60,3 +61,20 @@ def test_step_1d(Q, reach, tile):
     e = rms(f.cpu().numpy(), ref)
     print(f"Q={Q} tile={tile} rms {e:.2e}", flush=True)
     assert e <= 1.3 * 6.5e-17
+
+
+@needs_extended
+def test_step_2d():
+    nx, ny = 40, 24
+    c, n, ux, uy, T = workloads.phase_separation_2d(nx=nx, ny=ny)
+    yy, xx = np.meshgrid(np.arange(ny), np.arange(nx), indexing="ij")
+    tb = step2d.Tables2D(Params(Q=16, dx=c["dx"], dt=c["dt"]))
+    F, G = step2d.initial_state(n, 0.03 * np.sin(2 * np.pi * xx / nx), -0.02 * np.cos(2 * np.pi * yy / ny), T, tb)
+    s = E.Solver(16, c["dx"], c["dt"], nx, ny=ny)
+    f = E.Solver.from_planes(td(np.stack([F, G])))
+    s.step(f, 1)
+    ref = np.stack(step2d.run(F.astype(np.longdouble), G.astype(np.longdouble), tb, 1))
+    assert ref.dtype == np.longdouble
+    e = rms(E.Solver.planes(f).cpu().numpy(), ref)
+    print(f"2D rms {e:.2e}", flush=True)
+    assert e <= 1.25 * 1.05e-16
