@@ -606,9 +606,10 @@ constexpr int WN = 16;  // nodes per narrow tile
 // 4%).  A stage of 16-node tiles in a captured graph, where an empty launch is
 // 1.6 us, against one value per thread, full 16x16x4 products and the partial
 // velocity moments through LDS:
-//   256 nodes   q 8 5.93 -> 3.33   q 16 5.85 -> 3.46   q 24 6.24 -> 4.14 us
+//   256 nodes   q 8 5.93 -> 3.40   q 16 5.85 -> 3.44   q 24 6.24 -> 4.07 us
 // (with the loads' side of it on one XCD, see grid_index, and the leading
-// arguments preloaded, see stage_kernel_mirror; 3.68, 3.92 and 4.54 without).
+// arguments preloaded, see stage_kernel_mirror; 3.68, 3.92 and 4.54 without; the
+// terms known at compile time, see launch_stage_mirror).
 // ---------------------------------------------------------------------------
 template <int Q, int W>
 struct Mirror {
@@ -1122,7 +1123,7 @@ __global__ __launch_bounds__(W * NG) void stage_kernel(DevParams P, StageArgs A)
 // the latency of the state's loads, which no other wavefront covers at small
 // grids.  Requesting f_n an iteration ahead changed nothing.  A stage of 1.18 M
 // nodes, value by value with full contractions -> by mirror pairs:
-//   q 16  270 -> 224 us (4.0 TB/s of the state)   q 24  511 -> 350 us
+//   q 16  270 -> 224 us (4.0 TB/s of the state)   q 24  511 -> 348 us
 // ---------------------------------------------------------------------------
 constexpr int WC = 63;
 

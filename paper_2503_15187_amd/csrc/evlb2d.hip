@@ -647,7 +647,9 @@ constexpr int NRAW = 11;         // raw velocity sums per node: 8 of F, 3 of G
 // wavefront k's orientation at 0 .. 13 of it, its x faces and then (Dp x I) f
 // of columns 0 .. 7 at 14 .. 21, a zero at 22, the strip-edge face at 23.
 // Lanes of one LDS pass differ in the column and in r (PS = 24 = 8 mod 16) or
-// in the column and in k (KS = 8 mod 32): distinct banks either way.
+// in the column and in k (KS = 8 mod 32): distinct banks either way for these.
+// Over all accesses of the march the counters show 945 conflict cycles per row
+// and CU, an eighth of the row's time.
 constexpr int PS = 24, KS = 16 * PS + 8;
 constexpr int CDX = 14, CZERO = 22, CEDGE = 23;
 constexpr int USLOT = Q * KS;
@@ -1314,7 +1316,7 @@ Layout make_layout(const evlb_params* p, const evlb::DiscTables& t) {
   const size_t fbytes = align256(sizeof(double) * 2 * (size_t)V * (size_t)N);
   L.f1 = off; off += fbytes;
   L.f2 = off; off += fbytes;
-  off += align256(sizeof(double) * 6 * (size_t)N);  // unused: the size of a workspace stays what callers know
+  off += align256(sizeof(double) * 6 * (size_t)N);  // unused: evlb_workspace_bytes stays as it was
   L.raw = off; off += align256(sizeof(double) * NRAW * (size_t)N);
   L.fld = off; off += align256(sizeof(double) * NF * (size_t)N);
   L.status = off; off += 256;
