@@ -1366,7 +1366,7 @@ __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile,
   const double cF2 = 0.6 * pU * invT, cF3 = (sv + 0.3 * pB) * invT;
   const double cG0 = T * (nu0 - 0.2 * pU), cG1 = T * (pA - sv - 0.3 * pB);
   const double cG2 = 0.6 * pU, cG3 = sv + 0.3 * pB;
-  const double fx = cc * Fx, cdx = cc * P.inv_dx;
+  const double nub = bb - nu0, fx = cc * Fx, cdx = cc * P.inv_dx;
   double pm[6] = {0, 0, 0, 0, 0, 0};
 #pragma unroll 1
   for (int k = 0; k < Q / 2; ++k) {
@@ -1451,11 +1451,11 @@ __device__ void stage_tile_col(const DevParams& P, const StageArgs& A, int tile,
     double o[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      // cc L(f) first, the states last: two roundings of the size of the result
-      double t = fma(r & 1 ? -cx : cx, d[r], -nu0 * own[r]);
-      t = fma(-fx, dp[r], t);
+      // the other terms of cc L(f) first, the states last: two roundings of the
+      // size of the result, and that of nub
+      double t = fma(-fx, dp[r], (r & 1 ? -cx : cx) * d[r]);
       t = fma(E[r & 1], q[r], t);
-      o[r] = fma(ca, fb[r], fma(bb, own[r], t));
+      o[r] = fma(ca, fb[r], fma(nub, own[r], t));
     }
     if (valid) {
 #pragma unroll
