@@ -1123,7 +1123,7 @@ __global__ __launch_bounds__(W * NG) void stage_kernel(DevParams P, StageArgs A)
 // the latency of the state's loads, which no other wavefront covers at small
 // grids.  Requesting f_n an iteration ahead changed nothing.  A stage of 1.18 M
 // nodes, value by value with full contractions -> by mirror pairs:
-//   q 16  270 -> 224 us (4.0 TB/s of the state)   q 24  511 -> 348 us
+//   q 16  270 -> 224 us (3.6 TB/s of algorithmic bytes, 4.0 of traffic)   q 24  511 -> 348 us
 // ---------------------------------------------------------------------------
 constexpr int WC = 63;
 
